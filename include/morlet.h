@@ -303,7 +303,10 @@ morlet_status morlet_plan_set_boundary(morlet_plan_t plan, morlet_boundary bound
  * without outputs), a second (one block per row) turns those into each segment's incoming
  * state, and a third runs the segments with outputs, each block carrying the state through its
  * segment's tiles as in the rows schedule (the input is read twice; no block waits on another).
- * For more rows it acts as AUTO. MORLET_SCHED_AUTO (default): rows when the longest row has no
+ * For more rows it acts as AUTO. MORLET_SCHED_AUTO (default): at tile shape R = 16 and float32, mixed
+ * or default accumulation the granule scan (rows cut into pieces of 256-position granules, each piece
+ * summing the window before it, so no wave waits on another and the workspace is not used; float64
+ * states), except single signals whose window is much longer than a piece; else rows when the longest row has no
  * more tiles than one block's share of all tiles; else segments for at most eight rows with at
  * least two tiles per resident block; else tiles. The schedules are deterministic; they differ
  * only in the float64 rounding of the carried states. The adjoint and gradient passes use tiles
@@ -331,7 +334,8 @@ morlet_status morlet_plan_set_segments(morlet_plan_t plan, int32_t tiles_per_seg
  * trial outputs: any buffer of the forward's output size, overwritten. A setup call: it
  * allocates and frees its own workspace and events, rebuilds the tables synchronously and
  * synchronizes the stream, so it must not run under graph capture. R_out, schedule_out
- * (nullable) report the choice (MORLET_SCHED_TILES, _ROWS or _SEGMENTS). Errors as
+ * (nullable) report the choice (MORLET_SCHED_TILES, _ROWS or _SEGMENTS; MORLET_SCHED_AUTO when the
+ * automatic choice, timed first, won). Errors as
  * morlet_forward, MORLET_ERR_ALLOC if the trial workspace cannot be allocated; on error the
  * plan keeps its tile shape and schedule.
  * Persisted choices: when the environment variable MORLET_TUNE_CACHE names a file, a choice

@@ -14,11 +14,12 @@ BUILD = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 # Packed FP32 instructions are disabled for all device code.
-DEVICE_FLAGS = ["--offload-arch=" + ARCH, "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# Matrix products leave their results in vector registers (no moves from accumulation registers).
+DEVICE_FLAGS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "--offload-arch=" + ARCH, "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function", "-I", os.path.join(HERE, "..", "include")]
 
 HOST_SOURCES = ["plan.cpp", "api.cpp"]
-DEVICE_SOURCES = ["scan_dispatch.hip", "direct_conv.hip", "multiply.hip", "image2d.hip", "tree.hip", "boundary.hip", "noalloc.hip"]
+DEVICE_SOURCES = ["granule_scan.hip", "scan_dispatch.hip", "direct_conv.hip", "multiply.hip", "image2d.hip", "tree.hip", "boundary.hip", "noalloc.hip"]
 # scan kernel instantiation sets: scan_inst.hip once per (terms K, samples per thread R)
 TERMS = range(1, 13)
 TILES = (4, 8, 16, 32)

@@ -18,6 +18,7 @@
 
 #include "../../include/morlet.h"
 #include "boundary.h"
+#include "granule.h"
 #include "image2d.h"
 #include "launch.h"
 #include "multiply.h"
@@ -182,6 +183,77 @@ void build_row_queues(morlet_plan_s* p) {
   p->qstart[nq] = (int32_t)p->row_order.size();
 }
 
+// Whether all rows have one length and one scale (images, the multiplication method).
+bool equal_rows(const morlet_plan_s* p) {
+  if (p->S != 1) return false;
+  for (int64_t n : p->lengths)
+    if (n != p->lengths[0]) return false;
+  return true;
+}
+
+// Pieces of the rows for the granule scan, in launch order. Workgroups are dispatched to the XCDs
+// round-robin, so position k of the list runs on XCD k mod 8: like the row queues, the pieces of one
+// signal's rows, which read the same input, go to one XCD (signals longest first, each to the XCD with
+// the least work; with fewer than 4 signals per XCD the pieces are dealt in turn), the lists
+// interleaved.
+void build_gran_segs(morlet_plan_s* p) {
+  p->gran_segs.clear();
+  if (equal_rows(p)) return;   // their pieces follow from the index
+  const int S = p->S > 0 ? p->S : 1;
+  if ((int64_t)p->rows.size() != (int64_t)p->B * S) return;
+  auto window = [](const mk::Row& r) { return (2 * r.L + mk::kGran - 1) / mk::kGran; };
+  std::vector<mk::GranRow> shapes;
+  int64_t ng_max = 0;
+  for (const mk::Row& r : p->rows) {
+    const mk::GranRow g{mk::granules_for(r.N), window(r), 1};
+    ng_max = std::max(ng_max, g.ng);
+    if (g.ng == 0) continue;
+    if (!shapes.empty() && shapes.back().ng == g.ng && shapes.back().nw == g.nw) ++shapes.back().count;
+    else shapes.push_back(g);
+  }
+  if (shapes.empty() || ng_max > INT32_MAX) return;
+  const mk::GranSplit split = mk::split_granules(shapes, p->num_cus);
+  const int nq = mk::kQueues;
+  const bool by_signal = (int64_t)p->B >= 4 * nq;
+  std::vector<int> order(p->B);
+  for (int b = 0; b < p->B; ++b) order[b] = b;
+  if (by_signal) std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return p->lengths[a] > p->lengths[b]; });
+  // a row's scale decides its window: the widest first, theirs are the longest pieces
+  std::vector<int> so(S);
+  std::vector<int64_t> piece(S);
+  for (int s = 0; s < S; ++s) {
+    so[s] = s;
+    piece[s] = split.piece(window(p->rows[s]));
+  }
+  std::stable_sort(so.begin(), so.end(), [&](int x, int y) { return p->rows[x].L > p->rows[y].L; });
+  std::vector<std::vector<mk::GranSeg>> q(by_signal ? nq : 1);
+  std::vector<int64_t> load(q.size(), 0);
+  for (int b : order) {
+    size_t best = 0;
+    for (size_t i = 1; i < q.size(); ++i)
+      if (load[i] < load[best]) best = i;
+    load[best] += p->lengths[b];
+    const int64_t ng = mk::granules_for(p->lengths[b]);
+    if (ng == 0) continue;
+    for (int s : so) {
+      const int64_t ns = (ng + piece[s] - 1) / piece[s];
+      for (int64_t k = 0; k < ns; ++k) {   // ns pieces of nearly equal length
+        const int64_t g0 = ng * k / ns;
+        q[best].push_back({(int32_t)(b * S + s), (int32_t)(ng * (k + 1) / ns - g0), g0});
+      }
+    }
+  }
+  std::vector<size_t> at(q.size(), 0);
+  for (bool any = true; any;) {
+    any = false;
+    for (size_t i = 0; i < q.size(); ++i)
+      if (at[i] < q[i].size()) {
+        p->gran_segs.push_back(q[i][at[i]++]);
+        any = true;
+      }
+  }
+}
+
 // Rows are signal-major: row b*S + s filters signal b at scale s. The output of row (b, s)
 // starts at S * offset_b + s * len_b (layout [signal][scale][n]).
 void build_rows(morlet_plan_s* p) {
@@ -212,16 +284,18 @@ void build_rows(morlet_plan_s* p) {
   p->ntiles = tile0;
   p->ntiles_max = tmax;
   build_row_queues(p);
+  build_gran_segs(p);
 }
 
 void build_batched_tables(morlet_plan_s* p) {
-  const mk::TabLayout lay{p->K, p->R};
-  const size_t tb = lay.bytes();
+  const size_t tb = mk::scale_bytes(p->K, p->R), go = mk::TabLayout{p->K, p->R}.bytes();
   p->h_tab.assign(tb * p->S, 0);
   for (int s = 0; s < p->S; ++s) {
     const ScaleParams& sp = p->scales[s];
     mk::fill_table(p->h_tab.data() + tb * s, p->kind, p->K, p->R, sp.L, sp.P_S, sp.sigma, sp.xi, p->mode,
                    p->mode == 1 ? sp.n0_asft : 0, sp.cc, sp.sc, sp.jac);
+    mk::fill_granules(p->h_tab.data() + tb * s + go, mk::out_kind(p), p->K, sp.L, sp.P_S, sp.sigma, sp.xi, p->mode,
+                      p->mode == 1 ? sp.n0_asft : 0, sp.cc, sp.sc);
   }
 }
 
@@ -230,7 +304,8 @@ morlet_status upload_batched(morlet_plan_s* p) {
   if (s != MORLET_OK || !p->d_tab) return s;
   const size_t rb = p->rows.size() * sizeof(mk::Row), tb = p->tile_row.size() * sizeof(int32_t);
   const size_t ob = p->row_order.size() * sizeof(int32_t);
-  const size_t need = rb + tb + ob + 16;
+  const size_t go = (rb + tb + ob + 15) / 16 * 16, gb = p->gran_segs.size() * sizeof(mk::GranSeg);
+  const size_t need = go + gb + 16;
   if (p->d_rows && p->rows_bytes < need) {
     (void)hipFree(p->d_rows);
     p->d_rows = nullptr;
@@ -243,10 +318,12 @@ morlet_status upload_batched(morlet_plan_s* p) {
     }
     p->rows_bytes = need;
   }
-  if ((rb && hipMemcpy(p->d_rows, p->rows.data(), rb, hipMemcpyHostToDevice) != hipSuccess) ||
-      (tb && hipMemcpy(static_cast<char*>(p->d_rows) + rb, p->tile_row.data(), tb, hipMemcpyHostToDevice) != hipSuccess) ||
-      (ob && hipMemcpy(static_cast<char*>(p->d_rows) + rb + tb, p->row_order.data(), ob, hipMemcpyHostToDevice) !=
-                 hipSuccess)) {
+  std::vector<unsigned char> lists(go + gb);   // one copy for all of them
+  if (rb) std::memcpy(lists.data(), p->rows.data(), rb);
+  if (tb) std::memcpy(lists.data() + rb, p->tile_row.data(), tb);
+  if (ob) std::memcpy(lists.data() + rb + tb, p->row_order.data(), ob);
+  if (gb) std::memcpy(lists.data() + go, p->gran_segs.data(), gb);
+  if (!lists.empty() && hipMemcpy(p->d_rows, lists.data(), lists.size(), hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipGetLastError();
     return fail(MORLET_ERR_HIP, "hipMemcpy of the row table failed");
   }
@@ -338,6 +415,44 @@ morlet_status init_morlet_rows(morlet_plan_s* p, int B, int64_t len, double sigm
   return upload_batched(p);
 }
 
+// Granule scan: a forward or adjoint launch under the automatic schedule and tile shape, float32 or mixed
+// accumulation. Returns whether the launch takes it (a.row0 set for a single row).
+bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant) {
+  a.gran_nseg = 0;
+  // not for the adjoint of an edge-extended row: its fold adds up 2L outputs whose sum is smaller by
+  // orders of magnitude, and the rounding of the run weights does not average out in it
+  if (variant == mk::kVarParamGrad || (variant == mk::kVarAdjoint && plan->boundary == 1) ||
+      (plan->row_serial != -1 && !(plan->row_serial == 2 && a.nrows > mk::kQueues)) || plan->R != 16 ||
+      (a.acc != mk::kAccF32 && a.acc != mk::kAccMixed))
+    return false;
+  a.gran_tabs = a.tabs + mk::TabLayout{plan->K, plan->R}.bytes();
+  const int64_t nrows = plan->batched ? (int64_t)plan->rows.size() : 1;
+  if (plan->batched && !equal_rows(plan)) {
+    if (plan->gran_segs.empty() || plan->gran_segs.size() > (size_t)INT32_MAX) return false;
+    const size_t rb = plan->rows.size() * sizeof(mk::Row);
+    const size_t lists = (plan->tile_row.size() + plan->row_order.size()) * sizeof(int32_t);
+    a.gran_segs = reinterpret_cast<const mk::GranSeg*>(static_cast<const char*>(plan->d_rows) + (rb + lists + 15) / 16 * 16);
+    a.gran_nseg = (int64_t)plan->gran_segs.size();
+    return true;
+  }
+  const mk::Row& row = plan->batched ? plan->rows[0] : a.row0;
+  const int64_t ng = mk::granules_for(row.N), nw = (2 * row.L + mk::kGran - 1) / mk::kGran;
+  if (ng == 0) return false;
+  const mk::GranSplit split = mk::split_granules({{ng, nw, nrows}}, plan->num_cus);
+  const int64_t n = split.piece(nw), ns = (ng + n - 1) / n;
+  if (ns * nrows > INT32_MAX) return false;
+  // A window much longer than a piece is summed by every piece: the tiles schedule, whose tiles hand
+  // their states on, takes about 16 us for one round of tiles and 0.03 us per tile, the granule scan
+  // 2.6 us per unit of the split's cost (N = 102400, 2L = 65536: 16 against 91 us; N = 2^22,
+  // 2L = 8192: 60 against 37).
+  if (2.6 * split.cost > 16.0 + 0.03 * (double)a.ntiles) return false;
+  a.gran_segs = nullptr;
+  a.gran_pieces = (int32_t)ns;
+  a.gran_n = (int32_t)((ng + ns - 1) / ns);
+  a.gran_nseg = ns * nrows;
+  return true;
+}
+
 // Fill the launch descriptor for this plan (rows, tables, tiles, workspace, grid).
 // recompute = true: a forward pass recomputed inside a gradient call; under the default
 // accumulation it runs the mixed scan (float64 chunk sums), whose rounding stays below what the
@@ -363,9 +478,7 @@ morlet_status make_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int v
                                                                                           : mk::kAccMixed)
           : accum == MORLET_ACC_KAHAN  ? mk::kAccKahan
                                        : accum;
-  // differentials: 2 real output from the sines (SFT, first), 1 from the cosines (SFT,
-  // second), 3 from both (ASFT)
-  a.kind = plan->deriv == 0 ? plan->kind : plan->mode == MORLET_SCAN_ASFT ? 3 : plan->deriv == 1 ? 2 : 1;
+  a.kind = mk::out_kind(plan);
   a.row0.x_off = 0;
   a.row0.w_off = 0;
   a.row0.N = plan->N;
@@ -390,10 +503,11 @@ morlet_status make_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int v
   }
   a.ntiles = ntiles;
   a.tabs = static_cast<const unsigned char*>(plan->d_tab);
-  a.tab_stride = (int64_t)mk::TabLayout{plan->K, plan->R}.bytes();
+  a.tab_stride = (int64_t)mk::scale_bytes(plan->K, plan->R);
   a.f32_bytes = (int64_t)mk::TabLayout{plan->K, plan->R}.f32Bytes();
   a.ws = ws;
   a.dtype = dtype;
+  if (gran_launch(plan, a, variant)) return MORLET_OK;
   const int occ = mk::scan_occupancy(a.K, a.R, variant, a.acc, a.kind, mom, dtype);
   if (occ <= 0) return fail(MORLET_ERR_UNSUPPORTED, "no kernel for this configuration");
   const int64_t cap = (int64_t)occ * plan->num_cus;
@@ -448,6 +562,7 @@ morlet_status make_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int v
 // Workspace bytes a forward launch reads and writes: the header; the tiles schedule adds a tile
 // state per tile, the segments schedule a float64 state vector per segment.
 size_t launch_ws_bytes(const mk::ScanLaunch& a, int K, int64_t ntiles) {
+  if (a.gran_nseg > 0) return 0;
   if (a.nseg > 0) return sizeof(mk::WsHeader) + (size_t)a.nseg * 2 * (size_t)K * sizeof(double);
   return a.serial ? sizeof(mk::WsHeader) : mk::workspace_bytes(K, ntiles);
 }
@@ -491,6 +606,20 @@ EdgeLayout edge_layout(morlet_plan_t plan) {
   return e;
 }
 
+// The launch of a single-signal plan moved onto its padded row of Ne samples.
+void pad_launch(morlet_plan_t plan, mk::ScanLaunch& a, int64_t Ne, int variant, int mom, int dtype) {
+  const int64_t jend = Ne + plan->L - plan->n0;
+  const int64_t ntiles = tiles_for(jend, plan->R);
+  a.row0.N = Ne;
+  a.row0.jend = jend;
+  a.row0.ntiles = (int32_t)ntiles;
+  a.ntiles = ntiles;
+  if (gran_launch(plan, a, variant)) return;
+  const int occ = mk::scan_occupancy(a.K, a.R, variant, a.acc, a.kind, mom, dtype);
+  const int64_t cap = (int64_t)(occ > 0 ? occ : 1) * plan->num_cus;
+  a.grid = (int)(ntiles < cap ? ntiles : cap);
+}
+
 // Edge extension (Sec. II): every output reads at most 2L samples outside [0, N-1], so the
 // signal is padded by 2L edge copies on each side, scanned as one zero-extended row of
 // N + 4L samples, and the central N outputs are copied out.
@@ -514,13 +643,7 @@ morlet_status run_edge(morlet_plan_t plan, const void* x, int dtype, void* out, 
   mk::ScanLaunch a;
   const morlet_status st = make_launch(plan, a, ws, mk::kVarForward, 0, 0);
   if (st != MORLET_OK) return st;
-  a.row0.N = Ne;
-  a.row0.jend = jend;
-  a.row0.ntiles = (int32_t)ntiles;
-  a.ntiles = ntiles;
-  const int occ = mk::scan_occupancy(a.K, a.R, mk::kVarForward, a.acc, a.kind, 0, 0);
-  const int64_t cap = (int64_t)(occ > 0 ? occ : 1) * plan->num_cus;
-  a.grid = (int)(ntiles < cap ? ntiles : cap);
+  pad_launch(plan, a, Ne, mk::kVarForward, 0, 0);
   a.x = xe;
   a.dtype = 0;
   a.out = oe;
@@ -729,19 +852,6 @@ EdgeBwdLayout edge_bwd_layout(morlet_plan_t plan) {
   b.gx_off = up(b.g_off + (size_t)Ne * esize);
   b.total = b.gx_off + (size_t)Ne * sizeof(float);
   return b;
-}
-
-// The launch of a single-signal plan moved onto its padded row of Ne samples.
-void pad_launch(morlet_plan_t plan, mk::ScanLaunch& a, int64_t Ne, int variant, int mom, int dtype) {
-  const int64_t jend = Ne + plan->L - plan->n0;
-  const int64_t ntiles = tiles_for(jend, plan->R);
-  a.row0.N = Ne;
-  a.row0.jend = jend;
-  a.row0.ntiles = (int32_t)ntiles;
-  a.ntiles = ntiles;
-  const int occ = mk::scan_occupancy(a.K, a.R, variant, a.acc, a.kind, mom, dtype);
-  const int64_t cap = (int64_t)(occ > 0 ? occ : 1) * plan->num_cus;
-  a.grid = (int)(ntiles < cap ? ntiles : cap);
 }
 
 // Backward with edge extension: the forward is W = C A E x (E the extension, A the scan of the
@@ -1170,7 +1280,7 @@ bool tune_lookup(const std::string& key, int& R, int& rows) {
     int r = 0, w = 0;
     if (std::sscanf(line.c_str() + t1 + 1, "%d\t%d", &r, &w) == 2 && (r == 4 || r == 8 || r == 16 || r == 32)) {
       R = r;
-      rows = w ? 1 : 0;
+      rows = w >= -1 && w <= 2 ? w : 0;
       found = true;
     }
   }
@@ -1697,6 +1807,7 @@ morlet_status morlet_plan_autotune(morlet_plan_t plan, const void* x, morlet_dty
       return st;
     }
     need = std::max(need, b);
+    if (R == 16) cands.push_back({R, -1});   // the automatic choice: the granule scan where it applies
     cands.push_back({R, 0});
     if (nrows > 1) cands.push_back({R, 1});
     if (nrows <= (size_t)mk::kQueues) cands.push_back({R, 2});

@@ -1,0 +1,71 @@
+// Granule scan (granule_scan.h): the constants it reads, the pieces of rows it runs and its launch.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "layout.h"
+
+namespace mk {
+
+constexpr int kRun = 16;                 // positions per run
+constexpr int kGran = 16 * kRun;         // positions per granule (16 runs)
+
+// Constants of one scale, behind its TabLayout table: powers of a_p laid out for the matrix cores,
+// one value per lane. Lane l = 16 q + c of a wave owns run c of a granule and the states q, q + 4,
+// q + 8 (slot s holds state 4 s + q; slots past the last term are zero). Float32 part first, then
+// float64.
+struct GranLayout {
+  int K;
+  MK_HD int NS() const { return (K + 3) / 4; }            // state slots per lane
+  MK_HD int MB() const { return K > 8 ? 2 : 1; }          // matrix blocks of the run sums
+  // float32, 64 lanes each: run outputs from run inputs, T[4 q + kb -> r] (lane 16 q + r), real then
+  // imaginary component; run outputs from the state before the run, component k = 2 s + (0 re, 1 im)
+  MK_HD int fTre(int kb) const { return 64 * kb; }
+  MK_HD int fTim(int kb) const { return 64 * (4 + kb); }
+  MK_HD int fCre(int k) const { return 64 * (8 + k); }
+  MK_HD int fCim(int k) const { return 64 * (8 + 2 * NS() + k); }
+  // scalars: weight of y[j - 2L] in the output (real, imaginary component)
+  MK_HD int fYre() const { return 64 * (8 + 4 * NS()); }
+  MK_HD int fYim() const { return fYre() + 1; }
+  MK_HD int nFloats() const { return (fYre() + 4 + 31) / 32 * 32; }
+  // float64: run sums B = sum_r a^{15 - r} dy[r], lane 16 q + m holding the weight of input 4 q + kb for
+  // row m of the product; a^{16 c} per lane (64); a^{16 2^d}, one value per q; a^{256 k}, k in [0, 16];
+  // e^{-2 alpha L}. Parts of slot s: 0 real, 1 imaginary
+  MK_HD int dP(int mb, int kb) const { return 64 * (4 * mb + kb); }
+  MK_HD int dLANE(int s, int part) const { return 64 * (4 * MB() + 2 * s + part); }
+  MK_HD int dSC(int d, int s, int part) const { return 64 * (4 * MB() + 2 * NS()) + 4 * ((d * NS() + s) * 2 + part); }
+  MK_HD int dG(int k, int s, int part) const { return dSC(4, 0, 0) + 4 * ((k * NS() + s) * 2 + part); }
+  MK_HD int dD() const { return dG(17, 0, 0); }
+  MK_HD int nDoubles() const { return dD() + 1; }
+  MK_HD size_t bytes() const { return ((size_t)nFloats() * 4 + (size_t)nDoubles() * 8 + 255) / 256 * 256; }
+};
+
+// A piece of a row for one wave: granules [g0, g0 + n) of the row. Granule g holds the outputs
+// [256 g - m, 256 g - m + 256), m the outputs by which the row starts past a 128-byte line.
+struct GranSeg {
+  int32_t row;
+  int32_t n;
+  int64_t g0;
+};
+
+// Granules that cover a row of N outputs at any alignment.
+inline int64_t granules_for(int64_t N) { return N <= 0 ? 0 : (N + 31 + kGran - 1) / kGran; }
+
+struct GranLaunch {
+  int K, kind, dtype;           // kind: 0 complex transform, else real
+  int adjoint;                  // x is the cotangent, out the float32 gradient
+  const void* x;
+  void* out;
+  // pieces, one wave each: the device list segs, or (segs null, rows of one length) piece k of row
+  // r at index r pieces + k, seg_n granules long
+  const GranSeg* segs;
+  int64_t nseg;
+  int32_t pieces, seg_n;
+  Row row0;                     // the only row when nrows == 1
+  const Row* rows;              // device rows
+  int nrows;
+  const unsigned char* tabs;    // granule constants of scale 0
+  int64_t tab_stride;
+};
+hipError_t launch_granules(const GranLaunch& a, hipStream_t s);
+
+}  // namespace mk

@@ -9,6 +9,7 @@ namespace mk {
 // Scan arithmetic: float32 tile scan with float64 carries, float64 throughout, float64 chunk
 // sums and wave scan with a float32 recurrence, the float32 tile scan in compensated
 // (float-float) arithmetic.
+struct GranSeg;   // granule.h
 enum ScanAcc { kAccF32 = 0, kAccF64 = 1, kAccMixed = 2, kAccKahan = 3 };
 
 struct ScanLaunch {
@@ -41,6 +42,12 @@ struct ScanLaunch {
   int64_t nseg;                 // 0: not this schedule
   int32_t seg_start[kQueues + 1];
   double* segstate;             // device [nseg][2 K] float64 (re, im per term), in the workspace
+  // Granule scan (granule.h), when gran_nseg > 0: a forward or adjoint launch that needs no workspace. One wave
+  // per piece of a row: gran_segs (device), or gran_pieces pieces of gran_n granules of every row.
+  const GranSeg* gran_segs;
+  int64_t gran_nseg;
+  int32_t gran_pieces, gran_n;
+  const unsigned char* gran_tabs;   // granule constants of scale 0 (stride tab_stride)
 };
 
 enum ScanVariant { kVarForward = 0, kVarAdjoint = 1, kVarParamGrad = 2, kVarSegSum = 3 };

@@ -380,45 +380,117 @@ void fill_table(unsigned char* dst, int kind, int K, int R, int64_t L, int P_S, 
   // float32 remainders of every entry, for float-float arithmetic
   float* tl = (float*)(dst + lay.f32Bytes() + lay.f64Bytes());
   for (int v = 0; v < lay.nValues(); ++v) tl[v] = (float)(td[v] - (double)tf[v]);
-  // run matrices of the matrix-core recurrence (Morlet output): with v_t after r + 1 steps
-  //   v_t[r] = a_t^{r+1} S_t + sum_{r' <= r} a_t^{r - r'} dy[r'],
-  //   o_re = gre A + gim B, o_im = gim A - gre B, A = cx y + sum_t mw_t Re v_t, B = sum_t lw_t Im v_t
-  if (kind == 0) {
-    float* tm = (float*)(dst + lay.mfmaOff());
-    const int RN = TabLayout::kRun, CW = lay.mCW();
-    std::vector<double> Tre(RN * RN, 0.0), Tim(RN * RN, 0.0), Cre(RN * CW, 0.0), Cim(RN * CW, 0.0);
-    for (int i = 0; i < K; ++i) {
-      const int64_t p = P_S + i;
-      const double mw = td[lay.rMW() * K + i], lw = td[lay.rLW() * K + i];
-      for (int r = 0; r < RN; ++r) {
-        for (int rp = 0; rp <= r; ++rp) {
-          double re, im;
-          apow(p, r - rp, L, alpha, re, im);
-          Tre[RN * r + rp] += gre * mw * re + gim * lw * im;
-          Tim[RN * r + rp] += gim * mw * re - gre * lw * im;
-        }
-        double re, im;
-        apow(p, r + 1, L, alpha, re, im);
-        Cre[CW * r + 2 * i] = gre * mw * re + gim * lw * im;
-        Cre[CW * r + 2 * i + 1] = -gre * mw * im + gim * lw * re;
-        Cim[CW * r + 2 * i] = gim * mw * re - gre * lw * im;
-        Cim[CW * r + 2 * i + 1] = -gim * mw * im - gre * lw * re;
-      }
+}
+
+size_t scale_bytes(int K, int R) { return TabLayout{K, R}.bytes() + GranLayout{K}.bytes(); }
+
+int out_kind(const morlet_plan_s* p) {
+  // differentials: 2 real output from the sines (SFT, first), 1 from the cosines (SFT, second),
+  // 3 from both (ASFT)
+  return p->deriv == 0 ? p->kind : p->mode == 1 ? 3 : p->deriv == 1 ? 2 : 1;
+}
+
+void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, double sigma, double xi, int mode,
+                   int64_t n0, const std::vector<double>& cc, const std::vector<double>& sc) {
+  const GranLayout lay{K};
+  std::memset(dst, 0, lay.bytes());
+  float* tf = (float*)dst;
+  double* td = (double*)(tf + lay.nFloats());
+  const double alpha = (mode == 1) ? (double)n0 / (sigma * sigma) : 0.0;
+  const double up = std::exp(alpha * (double)L), dn = std::exp(-alpha * (double)L);
+  const double s = mode == 1 ? std::exp(-(double)n0 * (double)n0 / (2.0 * sigma * sigma)) : 1.0;
+  const double gre = mode == 1 && okind == 0 ? s * std::cos(xi * (double)n0) : s;
+  const double gim = mode == 1 && okind == 0 ? s * std::sin(xi * (double)n0) : 0.0;
+  // output: (gre + i gim)(A - iB) for the wavelet, gre (A - B) for real output, with
+  // A = cx y + sum_t mw_t Re v_t, B = sum_t lw_t Im v_t; weights of Re v, Im v per component
+  double T[2][kRun] = {}, cx = 0;
+  for (int i = 0; i < K; ++i) {
+    const int64_t p = P_S + i;
+    const int slot = i / 4, q = i % 4;
+    const double sgn = (p & 1) ? -1.0 : 1.0;
+    const double mw = okind == 2 ? 0.0 : sgn * cc[i] * up, lw = okind == 1 ? 0.0 : sgn * sc[i] * up;
+    const double wr[2] = {gre * mw, gim * mw};
+    const double wi[2] = {okind == 0 ? gim * lw : -gre * lw, okind == 0 ? -gre * lw : 0.0};
+    if (okind != 2) cx += sgn * cc[i] * dn;
+    double re, im;
+    for (int d = 0; d < kRun; ++d) {
+      apow(p, d, L, alpha, re, im);
+      for (int c = 0; c < 2; ++c) T[c][d] += wr[c] * re + wi[c] * im;
+      // run sums: input r = 15 - d; lane 16 (r / 4) + row, block kb = r % 4
+      const int r = kRun - 1 - d, b = slot / 2, lq = 16 * (r / 4), kb = r % 4;
+      const int v = 2 * (slot % 2);   // result registers v, v + 1 of lane row q: rows q + 4 v, q + 4 (v + 1)
+      td[lay.dP(b, kb) + lq + q + 4 * v] = re;
+      td[lay.dP(b, kb) + lq + q + 4 * (v + 1)] = im;
+      // outputs at position d from the state before the run
+      apow(p, d + 1, L, alpha, re, im);
+      tf[lay.fCre(2 * slot) + 16 * q + d] = (float)(wr[0] * re + wi[0] * im);
+      tf[lay.fCre(2 * slot + 1) + 16 * q + d] = (float)(-wr[0] * im + wi[0] * re);
+      tf[lay.fCim(2 * slot) + 16 * q + d] = (float)(wr[1] * re + wi[1] * im);
+      tf[lay.fCim(2 * slot + 1) + 16 * q + d] = (float)(-wr[1] * im + wi[1] * re);
+      apow(p, (int64_t)kRun * d, L, alpha, re, im);
+      td[lay.dLANE(slot, 0) + 16 * q + d] = re;
+      td[lay.dLANE(slot, 1) + 16 * q + d] = im;
     }
-    for (int v = 0; v < RN * RN; ++v) {
-      tm[lay.mTre() + v] = (float)Tre[v];
-      tm[lay.mTim() + v] = (float)Tim[v];
+    for (int d = 0; d < 4; ++d) {
+      apow(p, (int64_t)kRun << d, L, alpha, re, im);
+      td[lay.dSC(d, slot, 0) + q] = re;
+      td[lay.dSC(d, slot, 1) + q] = im;
     }
-    for (int v = 0; v < RN * CW; ++v) {
-      tm[lay.mCre() + v] = (float)Cre[v];
-      tm[lay.mCim() + v] = (float)Cim[v];
+    for (int k = 0; k <= 16; ++k) {
+      apow(p, (int64_t)kGran * k, L, alpha, re, im);
+      td[lay.dG(k, slot, 0) + q] = re;
+      td[lay.dG(k, slot, 1) + q] = im;
     }
   }
+  for (int r = 0; r < kRun; ++r)
+    for (int rp = 0; rp <= r; ++rp) {
+      tf[lay.fTre(rp % 4) + 16 * (rp / 4) + r] = (float)T[0][r - rp];
+      tf[lay.fTim(rp % 4) + 16 * (rp / 4) + r] = (float)T[1][r - rp];
+    }
+  tf[lay.fYre()] = (float)(gre * cx);
+  tf[lay.fYim()] = (float)(gim * cx);
+  td[lay.dD()] = std::exp(-2.0 * alpha * (double)L);
+}
+
+int64_t GranSplit::piece(int64_t nw) const {
+  const int64_t n = (int64_t)std::ceil(per_warm * (double)nw);
+  return std::min<int64_t>(std::max(base, n), (int64_t)1 << 30);
+}
+
+GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus) {
+  // A granule of the window costs about 0.3 of one with outputs. Four waves per SIMD share it; a wave
+  // alone runs a granule in about 0.4 of the time. Longer pieces sum fewer windows, shorter ones fill
+  // the device and end together.
+  const double kWarm = 0.3, kAlone = 0.4, slots = 16.0 * num_cus;
+  GranSplit best;
+  best.cost = -1;
+  for (double pw : {0.0, 0.5, 2.0})
+    for (int64_t base = 1; base <= 1024; base *= 2) {
+      GranSplit t;
+      t.base = base;
+      t.per_warm = pw;
+      double work = 0, longest = 0;
+      for (const GranRow& r : rows) {
+        const int64_t n = t.piece(r.nw), ns = (r.ng + n - 1) / n;
+        // windows before the first piece's end reach the row's start
+        const double full = kWarm * (double)r.nw;
+        double warm = 0;
+        const int64_t part = std::min<int64_t>(ns, r.nw / n + 1);   // pieces whose window is cut short
+        warm += kWarm * (double)n * 0.5 * (double)(part - 1) * (double)part;
+        warm += full * (double)(ns - part);
+        work += (double)r.count * ((double)r.ng + warm);
+        longest = std::max(longest, (double)std::min(n, r.ng) + (ns > part ? full : kWarm * (double)n * (double)(part - 1)));
+      }
+      t.cost = std::max(work / slots, kAlone * longest) + 0.25 * longest;
+      if (best.cost < 0 || t.cost < best.cost) best = t;
+    }
+  return best;
 }
 
 bool build_table(morlet_plan_s* p, std::string* err) {
-  TabLayout lay{p->K, p->R};
-  p->h_tab.assign(lay.bytes(), 0);
+  p->h_tab.assign(scale_bytes(p->K, p->R), 0);
+  fill_granules(p->h_tab.data() + TabLayout{p->K, p->R}.bytes(), out_kind(p), p->K, p->L, p->P_S, p->sigma, p->xi,
+                p->mode, p->n0, p->cc, p->sc);
   fill_table(p->h_tab.data(), p->kind, p->K, p->R, p->L, p->P_S, p->sigma, p->xi, p->mode, p->n0, p->cc, p->sc,
              p->jac);
   (void)err;

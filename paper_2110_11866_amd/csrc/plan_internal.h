@@ -4,6 +4,7 @@
 #include <string>
 #include <vector>
 
+#include "granule.h"
 #include "layout.h"
 
 // One scale of a batched plan.
@@ -57,7 +58,8 @@ struct morlet_plan_s {
   int32_t qstart[mk::kQueues + 1] = {0};   // queue q is row_order[qstart[q] .. qstart[q + 1])
   int64_t max_row_tiles = 0;
   int64_t ntiles = 0, ntiles_max = 0;
-  void* d_rows = nullptr;                  // device rows, then tile_row, then row_order
+  std::vector<mk::GranSeg> gran_segs;      // granule scan: pieces of the rows in launch order
+  void* d_rows = nullptr;                  // device rows, then tile_row, row_order, gran_segs
   size_t rows_bytes = 0;
   // exact taps of the direct-convolution baseline (uploaded on its first call)
   void* d_direct = nullptr;
@@ -105,5 +107,26 @@ bool build_table(morlet_plan_s* p, std::string* err);
 void fill_table(unsigned char* dst, int kind, int K, int R, int64_t L, int P_S, double sigma, double xi,
                 int mode, int64_t n0, const std::vector<double>& cc, const std::vector<double>& sc,
                 const std::vector<double>& jac);
+// Constants of the granule scan for one scale (GranLayout). okind: the launch's kind (0 complex
+// output, 1 cosine components, 2 sine components, 3 both).
+void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, double sigma, double xi, int mode,
+                   int64_t n0, const std::vector<double>& cc, const std::vector<double>& sc);
+// Bytes of one scale's constants: its TabLayout table, then its granule constants.
+size_t scale_bytes(int K, int R);
+// Output kind of a plan's forward scan.
+int out_kind(const morlet_plan_s* p);
+
+// Pieces of rows for the granule scan: granules per piece of a row of ng granules whose window spans
+// nw granules (2L positions), from the load of the whole launch.
+struct GranSplit {
+  int64_t base = 1;      // granules per piece, at least
+  double per_warm = 0;   // and at least this many per granule of the window
+  double cost = 0;       // estimated time of the launch, in granule times of a wave on a full device
+  int64_t piece(int64_t nw) const;
+};
+struct GranRow {
+  int64_t ng, nw, count;   // granules, window granules, rows of this shape
+};
+GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus);
 
 }  // namespace mk

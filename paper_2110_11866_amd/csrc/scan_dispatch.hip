@@ -6,6 +6,7 @@
 
 #include <algorithm>
 
+#include "granule.h"
 #include "launch.h"
 #include "scan_common.h"
 
@@ -297,6 +298,17 @@ hipError_t launch_seg_combine(const ScanLaunch& a, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_scan(const ScanLaunch& a, int variant, int mom, hipStream_t s) {
+  if (a.gran_nseg > 0) {
+    if ((variant != kVarForward && variant != kVarAdjoint) || a.nrows < 1) return hipErrorInvalidValue;
+    GranLaunch g{};
+    g.K = a.K; g.kind = a.kind; g.dtype = a.dtype;
+    g.adjoint = variant == kVarAdjoint;
+    g.x = a.x; g.out = a.out;
+    g.row0 = a.row0; g.rows = a.rows; g.nrows = a.nrows; g.segs = a.gran_segs;
+    g.nseg = a.gran_nseg; g.pieces = a.gran_pieces; g.seg_n = a.gran_n;
+    g.tabs = a.gran_tabs; g.tab_stride = a.tab_stride;
+    return launch_granules(g, s);
+  }
   KernelFn fn = select_kernel(a.K, a.R, variant, a.acc, a.kind, mom, variant == kVarAdjoint ? 0 : a.dtype);
   if (!fn) return hipErrorInvalidValue;
   if (a.nseg > 0) {

@@ -559,6 +559,41 @@ morlet_status make_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int v
   return MORLET_OK;
 }
 
+// The launch of an image's second axis (plan: its batched plan over lines of length H) down the columns
+// of an H x cols float32 matrix, where the granule scan would take its lines (taken = true). A wave
+// runs 32 columns; pieces of the rows fill the device, two waves per SIMD (four, with shorter pieces and
+// more windows, 94 against 92 us a 4096 x 4096 image). With 16-row runs the sums over the window before a
+// piece cost about half of a run with outputs.
+morlet_status column_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int variant, int64_t cols, bool& taken) {
+  taken = false;
+  const morlet_status st = make_launch(plan, a, ws, variant, 0, 0);
+  if (st != MORLET_OK || a.gran_nseg == 0) return st;
+  const int64_t nw = (2 * plan->rows[0].L + mk::kRun - 1) / mk::kRun, ng = (plan->rows[0].N + mk::kRun - 1) / mk::kRun;
+  const int64_t blocks = (cols + mk::kColWave - 1) / mk::kColWave;
+  const mk::GranSplit split = mk::split_granules({{ng, nw, blocks}}, plan->num_cus / 2, 0.5);
+  const int64_t np = (ng + split.piece(nw) - 1) / split.piece(nw);
+  a.col_cols = cols;
+  a.col_piece = mk::kRun * ((ng + np - 1) / np);
+  if (np > 65535) a.col_piece = mk::kRun * ((ng + 65534) / 65535);
+  a.row0 = plan->rows[0];
+  taken = true;
+  return MORLET_OK;
+}
+
+// The columns' pass (forward or adjoint) of an image from in to out, both H x cols float32, where
+// column_launch takes it.
+morlet_status run_columns(morlet_plan_t axis, int variant, const void* in, void* out, void* ws, int64_t cols, void* stream,
+                          bool& taken) {
+  mk::ScanLaunch a;
+  const morlet_status st = column_launch(axis, a, ws, variant, cols, taken);
+  if (st != MORLET_OK || !taken) return st;
+  a.x = in;
+  a.out = out;
+  const hipError_t e = mk::launch_scan(a, variant, 0, static_cast<hipStream_t>(stream));
+  if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
+  return MORLET_OK;
+}
+
 // Workspace bytes a forward launch reads and writes: the header; the tiles schedule adds a tile
 // state per tile, the segments schedule a float64 state vector per segment.
 size_t launch_ws_bytes(const mk::ScanLaunch& a, int K, int64_t ntiles) {
@@ -784,7 +819,12 @@ morlet_status run_gabor2d(morlet_plan_t plan, const void* x, int dtype, void* y,
   a.dtype = dtype;
   a.out = Z;
   hipError_t e = mk::launch_scan(a, mk::kVarForward, 0, s);
-  if (e == hipSuccess) e = mk::launch_transpose_c2p(Z, P, H, W, s);
+  if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
+  // the real filter of the columns acts on the real and imaginary parts alike: 2W real columns
+  bool columns = false;
+  st = run_columns(plan->axis[1], mk::kVarForward, Z, y, ws, 2 * W, stream, columns);
+  if (st != MORLET_OK || columns) return st;
+  e = mk::launch_transpose_c2p(Z, P, H, W, s);
   if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
   st = make_launch(plan->axis[1], a, ws, mk::kVarForward, 0, 0);
   if (st != MORLET_OK) return st;
@@ -819,7 +859,11 @@ morlet_status run_image2d(morlet_plan_t plan, const void* x, int dtype, float* y
   a.dtype = dtype;
   a.out = A;
   hipError_t e = mk::launch_scan(a, mk::kVarForward, 0, s);
-  if (e == hipSuccess) e = mk::launch_transpose(A, B, H, W, s);
+  if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
+  bool columns = false;
+  st = run_columns(plan->axis[1], mk::kVarForward, A, y, ws, W, stream, columns);
+  if (st != MORLET_OK || columns) return st;
+  e = mk::launch_transpose(A, B, H, W, s);
   if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
   st = make_launch(plan->axis[1], a, ws, mk::kVarForward, 0, 0);
   if (st != MORLET_OK) return st;
@@ -1008,8 +1052,10 @@ morlet_status run_deriv_backward(morlet_plan_t plan, const float* gy, float* gx,
   return MORLET_OK;
 }
 
+// adjoint = false: the parameter gradients alone (gx unused).
 morlet_status run_backward(morlet_plan_t plan, const void* x, int dtype, const void* g, float* gx, double* gparams,
-                           void* ws, size_t ws_bytes, void* stream, int want_kind, bool want_batched) {
+                           void* ws, size_t ws_bytes, void* stream, int want_kind, bool want_batched,
+                           bool adjoint = true) {
   if (!plan) return fail(MORLET_ERR_INVALID_ARG, "null plan");
   if (plan->multiply) {
     if (want_kind != 0 || want_batched) return fail(MORLET_ERR_INVALID_ARG, "plan kind does not match the call");
@@ -1031,25 +1077,31 @@ morlet_status run_backward(morlet_plan_t plan, const void* x, int dtype, const v
     if (gparams) return fail(MORLET_ERR_UNSUPPORTED, "parameter gradients of an empty signal are not computed");
     return MORLET_OK;
   }
-  if (!g || !gx || !ws || (gparams && !x)) return fail(MORLET_ERR_INVALID_ARG, "null pointer");
+  if (!g || (adjoint && !gx) || !ws || (gparams && !x)) return fail(MORLET_ERR_INVALID_ARG, "null pointer");
   if (ntiles > ((int64_t)1 << 31)) return fail(MORLET_ERR_UNSUPPORTED, "too many tiles");
   const BwdLayout L = bwd_layout(plan);
   if (ws_bytes < L.total) return fail(MORLET_ERR_WORKSPACE, "workspace too small for the backward pass");
   if (!plan->d_tab) return fail(MORLET_ERR_HIP, "plan has no device table (created without a HIP device)");
   hipStream_t s = static_cast<hipStream_t>(stream);
   unsigned char* wsb = static_cast<unsigned char*>(ws);
-  // 1. adjoint: dLoss/dx (per scale into the scratch for batched plans, then summed)
+  // 1. adjoint: dLoss/dx, per scale into the scratch for batched plans, then summed (one scale: its
+  // adjoint is the sum, and its rows lie where the signals do)
   mk::ScanLaunch a;
-  morlet_status st = make_launch(plan, a, ws, mk::kVarAdjoint, 0, 0);
-  if (st != MORLET_OK) return st;
-  a.x = g;
-  a.dtype = 0;
-  a.out = plan->batched ? static_cast<void*>(wsb + L.scratch_off) : static_cast<void*>(gx);
-  hipError_t e = mk::launch_scan(a, mk::kVarAdjoint, 0, s);
-  if (e == hipSuccess && plan->batched)
-    e = mk::launch_sum_scales(reinterpret_cast<const float*>(wsb + L.scratch_off), gx, a.rows, plan->B, plan->S,
-                              plan->N, s);
-  if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
+  morlet_status st = MORLET_OK;
+  hipError_t e = hipSuccess;
+  if (adjoint) {
+    st = make_launch(plan, a, ws, mk::kVarAdjoint, 0, 0);
+    if (st != MORLET_OK) return st;
+    a.x = g;
+    a.dtype = 0;
+    const bool sum = plan->batched && plan->S > 1;
+    a.out = sum ? static_cast<void*>(wsb + L.scratch_off) : static_cast<void*>(gx);
+    e = mk::launch_scan(a, mk::kVarAdjoint, 0, s);
+    if (e == hipSuccess && sum)
+      e = mk::launch_sum_scales(reinterpret_cast<const float*>(wsb + L.scratch_off), gx, a.rows, plan->B, plan->S,
+                                plan->N, s);
+    if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
+  }
   if (!gparams) return MORLET_OK;
   // 2. parameter gradients: forward scan of x reduced against g, then the finalize kernel
   const int mom = plan->mode == 1 ? 1 : 0;
@@ -1101,9 +1153,13 @@ morlet_status run_image2d_backward(morlet_plan_t plan, const float* gy, float* g
   float* B = reinterpret_cast<float*>(wsb + m.b_off);
   void* aw = ws;
   const size_t aw_bytes = m.axis_bytes;
+  bool columns = false;
+  morlet_status st = run_columns(plan->axis[1], mk::kVarAdjoint, gy, A, ws, W, stream, columns);
+  if (st != MORLET_OK) return st;
+  if (columns) return run_backward(plan->axis[0], nullptr, 0, A, gx, nullptr, aw, aw_bytes, stream, 1, true);
   hipError_t e = mk::launch_transpose(gy, A, H, W, s);   // W x H: the column lines' cotangents
   if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
-  morlet_status st = run_backward(plan->axis[1], nullptr, 0, A, B, nullptr, aw, aw_bytes, stream, 1, true);
+  st = run_backward(plan->axis[1], nullptr, 0, A, B, nullptr, aw, aw_bytes, stream, 1, true);
   if (st != MORLET_OK) return st;
   e = mk::launch_transpose(B, A, W, H, s);                // H x W: the row lines' cotangents
   if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
@@ -1131,7 +1187,10 @@ morlet_status run_image2d_grad(morlet_plan_t plan, const void* x, int dtype, con
   float* C = reinterpret_cast<float*>(wsb + m.c_off);
   double* gp = reinterpret_cast<double*>(wsb + m.gp_off);
   mk::ScanLaunch a;
-  morlet_status st = make_launch(plan->axis[0], a, ws, mk::kVarForward, 0, dtype, true);
+  bool columns = false;   // whether the columns' adjoint reads the image as it lies
+  morlet_status st = column_launch(plan->axis[1], a, ws, mk::kVarAdjoint, W, columns);
+  if (st != MORLET_OK) return st;
+  st = make_launch(plan->axis[0], a, ws, mk::kVarForward, 0, dtype, true);
   if (st != MORLET_OK) return st;
   a.x = x;
   a.dtype = dtype;
@@ -1140,9 +1199,10 @@ morlet_status run_image2d_grad(morlet_plan_t plan, const void* x, int dtype, con
   if (e == hipSuccess) e = mk::launch_transpose(A, B, H, W, s);  // its columns (W x H)
   if (e == hipSuccess) e = mk::launch_transpose(gy, C, H, W, s); // their cotangents (W x H)
   if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
-  st = run_backward(plan->axis[1], B, 0, C, A, gp, ws, m.axis_bytes, stream, 1, true);
+  st = run_backward(plan->axis[1], B, 0, C, A, gp, ws, m.axis_bytes, stream, 1, true, !columns);
+  if (st == MORLET_OK && columns) st = run_columns(plan->axis[1], mk::kVarAdjoint, gy, B, ws, W, stream, columns);
   if (st != MORLET_OK) return st;
-  e = mk::launch_transpose(A, B, W, H, s);                       // g1 (H x W)
+  if (!columns) e = mk::launch_transpose(A, B, W, H, s);         // g1 (H x W)
   if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
   st = run_backward(plan->axis[0], x, dtype, B, gx, gp + 2, ws, m.axis_bytes, stream, 1, true);
   if (st != MORLET_OK) return st;
@@ -1181,9 +1241,13 @@ morlet_status run_gabor2d_backward(morlet_plan_t plan, const void* gW, float* gx
   unsigned char* wsb = static_cast<unsigned char*>(ws);
   float* A = reinterpret_cast<float*>(wsb + m.a_off);
   float* B = reinterpret_cast<float*>(wsb + m.b_off);
+  bool columns = false;
+  morlet_status st = run_columns(plan->axis[1], mk::kVarAdjoint, gW, A, ws, 2 * W, stream, columns);
+  if (st != MORLET_OK) return st;
+  if (columns) return run_backward(plan->axis[0], nullptr, 0, A, gx, nullptr, ws, m.axis_bytes, stream, 0, true);
   hipError_t e = mk::launch_transpose_c2p(static_cast<const float2*>(gW), B, H, W, s);
   if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
-  morlet_status st = run_backward(plan->axis[1], nullptr, 0, B, A, nullptr, ws, m.axis_bytes, stream, 1, true);
+  st = run_backward(plan->axis[1], nullptr, 0, B, A, nullptr, ws, m.axis_bytes, stream, 1, true);
   if (st != MORLET_OK) return st;
   e = mk::launch_transpose_p2c(A, reinterpret_cast<float2*>(B), H, W, s);   // the rows' complex cotangent
   if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
@@ -1211,7 +1275,10 @@ morlet_status run_gabor2d_grad(morlet_plan_t plan, const void* x, int dtype, con
   float* C = reinterpret_cast<float*>(wsb + m.c_off);
   double* gp = reinterpret_cast<double*>(wsb + m.gp_off);
   mk::ScanLaunch a;
-  morlet_status st = make_launch(plan->axis[0], a, ws, mk::kVarForward, 0, dtype, true);
+  bool columns = false;   // whether the columns' adjoint reads the image as it lies
+  morlet_status st = column_launch(plan->axis[1], a, ws, mk::kVarAdjoint, W, columns);
+  if (st != MORLET_OK) return st;
+  st = make_launch(plan->axis[0], a, ws, mk::kVarForward, 0, dtype, true);
   if (st != MORLET_OK) return st;
   a.x = x;
   a.dtype = dtype;
@@ -1220,9 +1287,10 @@ morlet_status run_gabor2d_grad(morlet_plan_t plan, const void* x, int dtype, con
   if (e == hipSuccess) e = mk::launch_transpose_c2p(reinterpret_cast<const float2*>(A), B, H, W, s);
   if (e == hipSuccess) e = mk::launch_transpose_c2p(static_cast<const float2*>(gW), C, H, W, s);
   if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
-  st = run_backward(plan->axis[1], B, 0, C, A, gp, ws, m.axis_bytes, stream, 1, true);
+  st = run_backward(plan->axis[1], B, 0, C, A, gp, ws, m.axis_bytes, stream, 1, true, !columns);
+  if (st == MORLET_OK && columns) st = run_columns(plan->axis[1], mk::kVarAdjoint, gW, B, ws, 2 * W, stream, columns);
   if (st != MORLET_OK) return st;
-  e = mk::launch_transpose_p2c(A, reinterpret_cast<float2*>(B), H, W, s);   // the rows' cotangent
+  if (!columns) e = mk::launch_transpose_p2c(A, reinterpret_cast<float2*>(B), H, W, s);   // the rows' cotangent
   if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
   st = run_backward(plan->axis[0], x, dtype, B, gx, gp + 2, ws, m.axis_bytes, stream, 0, true);
   if (st != MORLET_OK) return st;

@@ -68,4 +68,16 @@ struct GranLaunch {
 };
 hipError_t launch_granules(const GranLaunch& a, hipStream_t s);
 
+// Column scan (column_scan.hip): a real filter along the columns of a rows x cols float32 matrix.
+constexpr int kColWave = 32;    // columns per wave
+struct ColumnLaunch {
+  int K, adjoint;
+  const float* x;
+  float* out;                   // not x
+  int64_t rows, cols, L, jout0;
+  int64_t piece;                // output rows per wave
+  const unsigned char* tabs;    // granule constants
+};
+hipError_t launch_columns(const ColumnLaunch& a, hipStream_t s);
+
 }  // namespace mk

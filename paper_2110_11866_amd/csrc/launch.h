@@ -48,6 +48,9 @@ struct ScanLaunch {
   int64_t gran_nseg;
   int32_t gran_pieces, gran_n;
   const unsigned char* gran_tabs;   // granule constants of scale 0 (stride tab_stride)
+  // Column scan (granule.h), when col_cols > 0: row0 runs down the columns of a float32 matrix of row0.N
+  // rows and col_cols columns, col_piece output rows per wave.
+  int64_t col_cols, col_piece;
 };
 
 enum ScanVariant { kVarForward = 0, kVarAdjoint = 1, kVarParamGrad = 2, kVarSegSum = 3 };

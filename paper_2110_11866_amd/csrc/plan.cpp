@@ -457,11 +457,11 @@ int64_t GranSplit::piece(int64_t nw) const {
   return std::min<int64_t>(std::max(base, n), (int64_t)1 << 30);
 }
 
-GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus) {
-  // A granule of the window costs about 0.3 of one with outputs. Four waves per SIMD share it; a wave
+GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus, double kWarm) {
+  // A granule of the window costs kWarm of one with outputs. Four waves per SIMD share it; a wave
   // alone runs a granule in about 0.4 of the time. Longer pieces sum fewer windows, shorter ones fill
   // the device and end together.
-  const double kWarm = 0.3, kAlone = 0.4, slots = 16.0 * num_cus;
+  const double kAlone = 0.4, slots = 16.0 * num_cus;
   GranSplit best;
   best.cost = -1;
   for (double pw : {0.0, 0.5, 2.0})

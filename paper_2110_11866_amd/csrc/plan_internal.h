@@ -127,6 +127,7 @@ struct GranSplit {
 struct GranRow {
   int64_t ng, nw, count;   // granules, window granules, rows of this shape
 };
-GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus);
+// warm: cost of a window granule relative to one with outputs.
+GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus, double warm = 0.3);
 
 }  // namespace mk

@@ -298,6 +298,16 @@ hipError_t launch_seg_combine(const ScanLaunch& a, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_scan(const ScanLaunch& a, int variant, int mom, hipStream_t s) {
+  if (a.col_cols > 0) {
+    if ((variant != kVarForward && variant != kVarAdjoint) || a.kind == 0 || !a.gran_tabs) return hipErrorInvalidValue;
+    ColumnLaunch c{};
+    c.K = a.K; c.adjoint = variant == kVarAdjoint;
+    c.x = static_cast<const float*>(a.x); c.out = static_cast<float*>(a.out);
+    c.rows = a.row0.N; c.cols = a.col_cols; c.L = a.row0.L; c.jout0 = a.row0.jout0;
+    c.piece = a.col_piece;
+    c.tabs = a.gran_tabs;
+    return launch_columns(c, s);
+  }
   if (a.gran_nseg > 0) {
     if ((variant != kVarForward && variant != kVarAdjoint) || a.nrows < 1) return hipErrorInvalidValue;
     GranLaunch g{};

@@ -109,3 +109,45 @@ def test_non_finite_input_reaches_no_earlier_output(bad):
             assert np.isfinite(got[:first]).all()
             assert _rel(got[:first], clean[:first]) <= TOL
             assert not np.isfinite(got[first:first + 2 * L + 1]).any()
+
+
+@pytest.mark.parametrize("H,W", [(1, 1), (15, 63), (16, 64), (17, 65), (33, 130), (200, 31), (5, 300)])
+@pytest.mark.parametrize("K", [4, 6, 12])
+def test_columns(H, W, K):
+    # the image filters' second axis: rows around a run, columns around a wave's 64, both directions
+    import paper_2110_11866_amd as M
+    img = np.random.default_rng(H * W + K).standard_normal((H, W)).astype(np.float32)
+    xt = torch.from_numpy(img).cuda()
+    for mode in ("sft", "asft"):
+        _say("columns", H, W, K, mode)
+        plan = M.Gauss2DPlan(H, W, 5.0, 4.0, K, 19, 15, mode=mode)
+        px, py = (O.plan_gauss(s, K, L, mode=mode, n0=plan.axis_info(a)["n0"] if mode == "asft" else None)
+                  for a, s, L in ((0, 4.0, 15), (1, 5.0, 19)))
+        assert _rel(plan.forward(xt).cpu().numpy(), O.gauss_smooth_2d(img, px, py)) <= TOL
+        want = np.stack([O.adjoint(img[:, c].astype(np.complex128), py) for c in range(W)], axis=1)
+        want = np.stack([O.adjoint(r.astype(np.complex128), px) for r in want])
+        assert _rel(plan.backward(xt).cpu().numpy(), want) <= TOL
+        gab = M.Gabor2DPlan(H, W, 4.0, 1.2, K, 5.0, 4, 15, 19, mode=mode)
+        gx, gy = gab.axis_info(0), gab.axis_info(1)
+        px = O.plan_morlet(4.0, 1.2, K, 15, mode=mode, n0=gx["n0"] if mode == "asft" else None)
+        py = O.plan_gauss(5.0, 4, 19, mode=mode, n0=gy["n0"] if mode == "asft" else None)
+        assert _rel(gab.forward(xt).cpu().numpy(), O.gabor_2d(img, px, py)) <= TOL
+        g = np.random.default_rng(K).standard_normal((H, W, 2)).astype(np.float32).view(np.complex64)[..., 0]
+        assert _rel(gab.backward(torch.from_numpy(g).cuda()).cpu().numpy(), O.gabor_2d_adjoint(g, px, py)) <= TOL
+
+
+def test_columns_in_pieces_and_non_finite():
+    # 900 rows in several pieces; an infinite pixel reaches no row before its window
+    import paper_2110_11866_amd as M
+    H, W, L = 900, 70, 54
+    img = np.random.default_rng(4).standard_normal((H, W)).astype(np.float32)
+    plan = M.Gauss2DPlan(H, W, 16.0, 2.0, 4, L, 7, mode="sft")
+    px, py = O.plan_gauss(2.0, 4, 7), O.plan_gauss(16.0, 4, L)
+    clean = plan.forward(torch.from_numpy(img).cuda()).cpu().numpy()
+    assert _rel(clean, O.gauss_smooth_2d(img, px, py)) <= TOL
+    for at in (400, 415, 416):
+        bad = img.copy()
+        bad[at, 33] = np.inf
+        got = plan.forward(torch.from_numpy(bad).cuda()).cpu().numpy()
+        assert np.array_equal(got[:at - L, :], clean[:at - L, :]) or _rel(got[:at - L], clean[:at - L]) <= TOL
+        assert not np.isfinite(got[at - L:at + L + 1, 33]).any()

@@ -218,6 +218,9 @@ void build_gran_segs(morlet_plan_s* p) {
   std::vector<int> order(p->B);
   for (int b = 0; b < p->B; ++b) order[b] = b;
   if (by_signal) std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return p->lengths[a] > p->lengths[b]; });
+  p->gran_two = split.two();
+  const int64_t unit = p->gran_two ? 2 : 1;
+  auto units = [&](int64_t ng) { return (ng + unit - 1) / unit; };
   // a row's scale decides its window: the widest first, theirs are the longest pieces
   std::vector<int> so(S);
   std::vector<int64_t> piece(S);
@@ -237,9 +240,9 @@ void build_gran_segs(morlet_plan_s* p) {
     if (ng == 0) continue;
     for (int s : so) {
       const int64_t ns = (ng + piece[s] - 1) / piece[s];
-      for (int64_t k = 0; k < ns; ++k) {   // ns pieces of nearly equal length
-        const int64_t g0 = ng * k / ns;
-        q[best].push_back({(int32_t)(b * S + s), (int32_t)(ng * (k + 1) / ns - g0), g0});
+      for (int64_t k = 0; k < ns; ++k) {   // ns pieces of nearly equal length, in units of one or two granules
+        const int64_t g0 = units(ng) * k / ns * unit, g1 = units(ng) * (k + 1) / ns * unit;
+        q[best].push_back({(int32_t)(b * S + s), (int32_t)((g1 < ng ? g1 : ng) - g0), g0});
       }
     }
   }
@@ -433,6 +436,7 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant) {
     const size_t lists = (plan->tile_row.size() + plan->row_order.size()) * sizeof(int32_t);
     a.gran_segs = reinterpret_cast<const mk::GranSeg*>(static_cast<const char*>(plan->d_rows) + (rb + lists + 15) / 16 * 16);
     a.gran_nseg = (int64_t)plan->gran_segs.size();
+    a.gran_two = plan->gran_two;
     return true;
   }
   const mk::Row& row = plan->batched ? plan->rows[0] : a.row0;
@@ -448,7 +452,12 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant) {
   if (2.6 * split.cost > 16.0 + 0.03 * (double)a.ntiles) return false;
   a.gran_segs = nullptr;
   a.gran_pieces = (int32_t)ns;
-  a.gran_n = (int32_t)((ng + ns - 1) / ns);
+  a.gran_two = split.two();
+  a.gran_n = (int32_t)n;
+  if (ns > 1) {   // pieces of nearly equal length
+    const int64_t u = a.gran_two ? 2 : 1;
+    a.gran_n = (int32_t)((ng + u * ns - 1) / (u * ns) * u);
+  }
   a.gran_nseg = ns * nrows;
   return true;
 }

@@ -28,15 +28,26 @@ struct GranLayout {
   MK_HD int fYim() const { return fYre() + 1; }
   MK_HD int nFloats() const { return (fYre() + 4 + 31) / 32 * 32; }
   // float64: run sums B = sum_r a^{15 - r} dy[r], lane 16 q + m holding the weight of input 4 q + kb for
-  // row m of the product; a^{16 c} per lane (64); a^{16 2^d}, one value per q; a^{256 k}, k in [0, 16];
+  // row m of the product; a^{16 c} per lane (64); a^{16 2^d}, d < 6, one value per q; a^{256 k},
+  // k in [0, 16];
   // e^{-2 alpha L}. Parts of slot s: 0 real, 1 imaginary
   MK_HD int dP(int mb, int kb) const { return 64 * (4 * mb + kb); }
   MK_HD int dLANE(int s, int part) const { return 64 * (4 * MB() + 2 * s + part); }
   MK_HD int dSC(int d, int s, int part) const { return 64 * (4 * MB() + 2 * NS()) + 4 * ((d * NS() + s) * 2 + part); }
-  MK_HD int dG(int k, int s, int part) const { return dSC(4, 0, 0) + 4 * ((k * NS() + s) * 2 + part); }
+  MK_HD int dG(int k, int s, int part) const { return dSC(6, 0, 0) + 4 * ((k * NS() + s) * 2 + part); }
   MK_HD int dD() const { return dG(17, 0, 0); }
-  MK_HD int nDoubles() const { return dD() + 1; }
-  MK_HD size_t bytes() const { return ((size_t)nFloats() * 4 + (size_t)nDoubles() * 8 + 255) / 256 * 256; }
+  MK_HD int nDoubles() const { return (dD() + 32) / 32 * 32; }
+  // bfloat16 thirds of the float32 weights (value = high + middle + low, exactly), four per lane:
+  // T[4 q + e -> r] of component c, and the weights of state components 4 set + e (0 past the last)
+  MK_HD int SETS() const { return NS() > 2 ? 2 : 1; }
+  MK_HD int bT(int c, int third) const { return 64 * (3 * c + third); }
+  MK_HD int bC(int c, int set, int third) const { return 64 * (6 + 3 * (c * SETS() + set) + third); }
+  // run sums: lane 16 q + 4 u + v holds the weights of inputs 4 q + e for component v of the states u, u + 4
+  // (block 0: real and imaginary parts of slots 0, 1) or u + 8 (block 1)
+  MK_HD int bP(int mb, int third) const { return 64 * (6 + 6 * SETS() + 3 * mb + third); }
+  MK_HD int nQuads() const { return 64 * (6 + 6 * SETS() + 3 * MB()); }
+  MK_HD size_t quadOff() const { return (size_t)nFloats() * 4 + (size_t)nDoubles() * 8; }
+  MK_HD size_t bytes() const { return quadOff() + (size_t)nQuads() * 8; }
 };
 
 // A piece of a row for one wave: granules [g0, g0 + n) of the row. Granule g holds the outputs
@@ -51,7 +62,7 @@ struct GranSeg {
 inline int64_t granules_for(int64_t N) { return N <= 0 ? 0 : (N + 31 + kGran - 1) / kGran; }
 
 struct GranLaunch {
-  int K, kind, dtype;           // kind: 0 complex transform, else real
+  int K, acc, kind, dtype;      // acc: kAccF32 or kAccMixed; kind: 0 complex transform, else real
   int adjoint;                  // x is the cotangent, out the float32 gradient
   const void* x;
   void* out;
@@ -60,6 +71,7 @@ struct GranLaunch {
   const GranSeg* segs;
   int64_t nseg;
   int32_t pieces, seg_n;
+  int two;                      // two granules at a time
   Row row0;                     // the only row when nrows == 1
   const Row* rows;              // device rows
   int nrows;

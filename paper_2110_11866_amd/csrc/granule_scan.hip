@@ -7,19 +7,28 @@
 // granule, 256 positions as 16 runs of 16:
 //   1. dy of run c as operand: lane 16 q + c holds dy[4 q .. 4 q + 3] of run c. The quads are loaded
 //      coalesced, lane l the l-th quad (16-byte loads at any sample alignment), and change lanes
-//      through 1 KB of LDS, swizzled so neither side conflicts;
-//   2. run sums B = P dy (2K x 16 by 16 x 16) in float64: lane 16 q + c receives the components of states
-//      q, q + 4, q + 8 of run c;
-//   3. float64 scan of the 16 runs along the 16 lanes of a DPP row (4 levels, constants a^{16 2^d}), the
-//      state at the granule's start entering run 0;
+//      through LDS, swizzled so neither side conflicts;
+//   2. run sums B = P dy (2K x 16 by 16 x 16): lane 16 q + c receives the components of states q, q + 4,
+//      q + 8 of run c. Float64 product for the mixed scan; from float32 to float32 for the float32 scan;
+//   3. float64 scan of the runs along the 16 lanes of a DPP row (4 levels, constants a^{16 2^d}), the
+//      state before the granule entering run 0;
 //   4. outputs of run c, position r: o = T dy + C S + Y y[j-2L], one product per component with the
 //      runs as rows and the positions as columns, so lane 16 q + r holds position r of runs
 //      4 q .. 4 q + 3 and a store instruction writes whole 128-byte lines.
 // The recurrence over the 16 positions and the K-term combination, 36 vector operations per position
-// at K = 5, become 40 matrix multiply-adds, which issue beside the vector work of other waves.
+// at K = 5, become 42 multiply-adds of matrix products.
 //
-// Zeros of T meet inputs of the same run at later positions: a run with an infinite or NaN input
-// takes the product masked position by position, so no output depends on a later input.
+// Float32 products run on the bfloat16 matrix cores as products of exact thirds (24 bits = 3 x 8): a
+// float32 or float64 matrix instruction has the vector units' rate and does not run beside them, the
+// bfloat16 one does 14 times the work. Six of the nine products of thirds keep float32 accuracy.
+//
+// Bound: issue of vector and matrix instructions (about 680 cycles of a SIMD per 256 outputs at K = 5,
+// 683 us of a 488e6-output scalogram without its stores), then the stores (3.9 GB at 5.3-5.8 TB/s, 740 us
+// without the products); together 1000 us, the tile scan 1390.
+//
+// Zeros of T meet inputs of the same run at later positions: where a run has an infinite or NaN input,
+// the product takes zero for it and its outputs from that position on are set to NaN, so no output
+// depends on a later input.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -34,6 +43,11 @@ namespace {
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v2f __attribute__((ext_vector_type(2)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v6i __attribute__((ext_vector_type(6)));
+typedef __bf16 v2b __attribute__((ext_vector_type(2)));
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
 typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));            // any sample alignment
 typedef unsigned short v4h_any __attribute__((ext_vector_type(4), aligned(2)));
 
@@ -62,11 +76,13 @@ struct Quad {
   using E = typename std::conditional<IN == 1 || IN == 2, unsigned short, typename std::conditional<IN == 3, v2f, float>::type>::type;
   using V = typename std::conditional<IN == 1 || IN == 2, v4h_any, v4f_any>::type;
   V v[IN == 3 ? 2 : 1];
+  // INNER: the whole granule lies inside [lo, hi)
+  template <bool INNER = false>
   __device__ __forceinline__ void load(const void* xs, int64_t p0, int64_t lo, int64_t hi, int64_t N, int lane) {
     const E* x = static_cast<const E*>(xs);
     const E* p = IN >= kInRev ? x + (N - 4 - p0) : x + p0;   // wave-uniform; the lane's quad starts at p -+ 4 lane
     const int o = IN >= kInRev ? -4 * lane : 4 * lane;
-    if (p0 >= lo && p0 + kGran <= hi) {
+    if (INNER || (p0 >= lo && p0 + kGran <= hi)) {
       v[0] = *reinterpret_cast<const V*>(p + o);
       if constexpr (IN == 3) v[1] = *reinterpret_cast<const V*>(p + o + 2);
     } else {
@@ -93,6 +109,61 @@ struct Quad {
   }
 };
 
+// Four float32 values as bfloat16 thirds, middle, high, low (two registers each): every value is the
+// exact sum of its thirds. The remainder after a third is one dot product with (-1, 0) or (0, -1).
+__device__ __forceinline__ int bf16_pair(float a, float b) {
+  return __builtin_bit_cast(int, __builtin_convertvector(v2f{a, b}, v2b));
+}
+__device__ __forceinline__ v6i thirds(const float (&x)[4]) {
+  int lo;   // (-1, 0): as a register, an inline constant would stand for another pair
+  asm("s_mov_b32 %0, 0xbf80" : "=s"(lo));
+  const v2b n0 = __builtin_bit_cast(v2b, lo), n1 = __builtin_bit_cast(v2b, (int)0xbf800000);
+  auto left = [&](int p, float a, float b, float& ra, float& rb) {
+    ra = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(v2b, p), n0, a, false);
+    rb = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(v2b, p), n1, b, false);
+  };
+  float r[4], t[4];
+  const int h0 = bf16_pair(x[0], x[1]), h1 = bf16_pair(x[2], x[3]);
+  left(h0, x[0], x[1], r[0], r[1]);
+  left(h1, x[2], x[3], r[2], r[3]);
+  const int m0 = bf16_pair(r[0], r[1]), m1 = bf16_pair(r[2], r[3]);
+  left(m0, r[0], r[1], t[0], t[1]);
+  left(m1, r[2], r[3], t[2], t[3]);
+  return v6i{m0, m1, h0, h1, bf16_pair(t[0], t[1]), bf16_pair(t[2], t[3])};
+}
+// Weights of four inputs per lane as thirds: middle, high, low.
+struct Weights {
+  v6i w;
+  __device__ __forceinline__ void load(const v2i* t, int h, int m, int l) {
+    const v2i vh = t[h], vm = t[m], vl = t[l];
+    w = v6i{vm[0], vm[1], vh[0], vh[1], vl[0], vl[1]};
+  }
+};
+// acc + x w to float32 accuracy: the products of thirds down to 2^-16 of the largest (middle x low and
+// low x low, below 2^-25, are left out), smallest first
+__device__ __forceinline__ v4f product(const v6i& x, const Weights& w, v4f acc) {
+  const v8b wmh = __builtin_bit_cast(v8b, __builtin_shufflevector(w.w, w.w, 0, 1, 2, 3));
+  const v8b whl = __builtin_bit_cast(v8b, __builtin_shufflevector(w.w, w.w, 2, 3, 4, 5));
+  const v8b lh = __builtin_bit_cast(v8b, __builtin_shufflevector(x, x, 4, 5, 2, 3));
+  const v8b mm = __builtin_bit_cast(v8b, __builtin_shufflevector(x, x, 0, 1, 0, 1));
+  const v8b hh = __builtin_bit_cast(v8b, __builtin_shufflevector(x, x, 2, 3, 2, 3));
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lh, whl, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mm, wmh, acc, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(hh, wmh, acc, 0, 0, 0);
+}
+
+// the same with the weights as rows
+__device__ __forceinline__ v4f product_t(const Weights& w, const v6i& x, v4f acc) {
+  const v8b wmh = __builtin_bit_cast(v8b, __builtin_shufflevector(w.w, w.w, 0, 1, 2, 3));
+  const v8b whl = __builtin_bit_cast(v8b, __builtin_shufflevector(w.w, w.w, 2, 3, 4, 5));
+  const v8b lh = __builtin_bit_cast(v8b, __builtin_shufflevector(x, x, 4, 5, 2, 3));
+  const v8b mm = __builtin_bit_cast(v8b, __builtin_shufflevector(x, x, 0, 1, 0, 1));
+  const v8b hh = __builtin_bit_cast(v8b, __builtin_shufflevector(x, x, 2, 3, 2, 3));
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(whl, lh, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wmh, mm, acc, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(wmh, hh, acc, 0, 0, 0);
+}
+
 // Granule slot of quad q of run c: 4 c + (q ^ swz(c)), so 8 lanes of consecutive runs reading one
 // quad index, and 16 of them, hit different 16-byte banks.
 __device__ __forceinline__ int swz(int c) { return (((c >> 1) ^ (c >> 3)) & 1) | (((c >> 2) & 1) << 1); }
@@ -100,13 +171,21 @@ __device__ __forceinline__ int swz(int c) { return (((c >> 1) ^ (c >> 3)) & 1) |
 // IN: the input (Quad). CPLX: the transform's outputs are complex (IN < 3: complex64 out; IN 3: their
 // cotangent comes in). An output component k is formed from stream k of the adjoint's two, or from
 // the only stream; the adjoint adds its components, Re sum conj(h) g = (h_re * g_re) + (h_im * g_im).
-template <int NS, bool CPLX, int IN>
+// NST: runs per lane column; a wave works on 16 columns of NST consecutive runs (256 NST positions) at a
+// time, so that the scan across lanes is done once for NST runs.
+// WIDE: run sums in float64 (the mixed scan), else from float32 inputs to float32 (the float32 scan);
+// everything that propagates from run to run is float64.
+template <int NS, bool CPLX, int IN, int NST, bool WIDE>
 __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
   constexpr bool REV = IN >= kInRev;
-  constexpr int ST = IN == 3 ? 2 : 1, NC = CPLX ? 2 : 1, MB = NS > 2 ? 2 : 1;
+  constexpr int ST = IN == 3 ? 2 : 1, NC = CPLX ? 2 : 1, MB = NS > 2 ? 2 : 1, SETS = NS > 2 ? 2 : 1;
+  constexpr int G = kGran * NST;        // positions at a time
+  constexpr int PS = NST == 1 ? kGran : kGran + 16;   // floats from one run of the columns to the next
+  constexpr int LV = NST == 1 ? 0 : NST == 2 ? 1 : 2;  // log2 NST
   static_assert(!REV || CPLX == (IN == 3), "the adjoint's input is the cotangent of the transform's output");
-  __shared__ __align__(16) float s_y[ST][kGran];   // y[j], by run and quad
-  __shared__ __align__(16) float s_b[ST][kGran];   // y[j - 2L]
+  __shared__ __align__(16) float s_y[ST][NST * PS];   // y[j], by run of the columns, column and quad
+  __shared__ __align__(16) float s_b[ST][NST * PS];   // y[j - 2L]
+  __shared__ double2 s_k[4 * NS * 4];                 // a^{16 NST 2^d} of slot s, row q, at (d NS + s) 4 + q
   const int lane = threadIdx.x, q = lane >> 4, c = lane & 15;
 
   Row row = P.row0;
@@ -134,66 +213,90 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
   // granules start on the output's 128-byte lines (the adjoint writes from the row's end)
   const int64_t m = REV ? (int64_t)((-reinterpret_cast<uintptr_t>(W + N * OB) & 127) / OB)
                         : (int64_t)((reinterpret_cast<uintptr_t>(W) & 127) / OB);
-  {
-    const int64_t left = (N + m + kGran - 1) / kGran - g0;   // granules from g0 to the row's end
-    gn = left < gn ? left : gn;
-  }
-  if (gn <= 0) return;
+  // outputs [n0, nend) of the piece
+  const int64_t first = kGran * g0 - m;
+  int64_t nend = first + kGran * gn;
+  nend = nend < N ? nend : N;
+  if (first >= nend) return;
 
   const GranLayout lay{4 * NS};   // layouts differ by the slot count only
-  const float* tf = reinterpret_cast<const float*>(P.tabs + (int64_t)row.scale * P.tab_stride);
+  const unsigned char* tb = P.tabs + (int64_t)row.scale * P.tab_stride;
+  const float* tf = reinterpret_cast<const float*>(tb);
   const double* td = reinterpret_cast<const double*>(tf + lay.nFloats());
-  float T[NC][4], C[NC][2 * NS], Y[NC];
-  double Pm[MB][4], scr[4][NS], sci[4][NS];
-  double gr[NS], gi[NS];
+  const v2i* tq = reinterpret_cast<const v2i*>(tb + lay.quadOff()) + lane;
+  Weights T[NC], C[NC][SETS];
+  float Y[NC];
+  double Pm[WIDE ? MB : 1][4], ar[NS], ai[NS];   // run sums; a^16
+  Weights Pw[WIDE ? 1 : MB];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    T[0][k] = tf[lay.fTre(k) + lane];
-    if constexpr (NC == 2) T[NC - 1][k] = tf[lay.fTim(k) + lane];
+  for (int k = 0; k < NC; ++k) {
+    T[k].load(tq, lay.bT(k, 0), lay.bT(k, 1), lay.bT(k, 2));
 #pragma unroll
-    for (int b = 0; b < MB; ++b) {
-      Pm[b][k] = td[lay.dP(b, k) + lane];
-    }
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      scr[k][s] = td[lay.dSC(k, s, 0) + q];
-      sci[k][s] = td[lay.dSC(k, s, 1) + q];
+    for (int e = 0; e < SETS; ++e) {
+      C[k][e].load(tq, lay.bC(k, e, 0), lay.bC(k, e, 1), lay.bC(k, e, 2));
     }
   }
 #pragma unroll
-  for (int k = 0; k < 2 * NS; ++k) {
-    C[0][k] = tf[lay.fCre(k) + lane];
-    if constexpr (NC == 2) C[NC - 1][k] = tf[lay.fCim(k) + lane];
+  for (int b = 0; b < MB; ++b) {
+    if constexpr (WIDE) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) Pm[b][k] = td[lay.dP(b, k) + lane];
+    } else {
+      Pw[b].load(tq, lay.bP(b, 0), lay.bP(b, 1), lay.bP(b, 2));
+    }
   }
 #pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    gr[s] = td[lay.dG(1, s, 0) + q]; gi[s] = td[lay.dG(1, s, 1) + q];
-  }
+  for (int s = 0; s < NS; ++s) { ar[s] = td[lay.dSC(0, s, 0) + q]; ai[s] = td[lay.dSC(0, s, 1) + q]; }
   Y[0] = tf[lay.fYre()];
   if constexpr (NC == 2) Y[NC - 1] = tf[lay.fYim()];
   const double Dd = td[lay.dD()];
+  const float Df = (float)Dd;
 
-  const int wslot = 4 * (4 * (lane >> 2) + ((lane & 3) ^ swz(lane >> 2)));
+  for (int i = lane; i < 4 * NS * 4; i += 64) {
+    const int d = i / (4 * NS), s = i / 4 % NS;
+    s_k[i] = make_double2(td[lay.dSC(LV + d, s, 0) + i % 4], td[lay.dSC(LV + d, s, 1) + i % 4]);
+  }
+
+  // quad of run i of column c: i PS + 4 (4 c + (q ^ swz(c))) floats. Written: lane l of load k holds
+  // positions 256 k + 4 l .., i.e. column 16 k / NST + l / (4 NST), run (l / 4) % NST, quad l % 4.
+  const int lc = lane / (4 * NST), li = (lane >> 2) % NST;
+  int wslot[NST];
+#pragma unroll
+  for (int k = 0; k < NST; ++k) {
+    const int cc = k * (16 / NST) + lc;
+    wslot[k] = li * PS + 4 * (4 * cc + ((lane & 3) ^ swz(cc)));
+  }
   const int rslot = 4 * (4 * c + (q ^ swz(c)));
-  // y[j - 2L] of position c of run 4 q + v: the swizzle of runs 4 q, 4 q + 1; its low bit flips for
-  // 4 q + 2, 4 q + 3
+  // y[j - 2L] of position c of column 4 q + v: the swizzle of columns 4 q, 4 q + 1; its low bit flips
+  // for 4 q + 2, 4 q + 3
   const int bs = (q >> 1) | ((q & 1) << 1);
   const int bslot0 = 64 * q + 4 * ((c >> 2) ^ bs) + (c & 3);
   const int bslot1 = 64 * q + 32 + 4 * ((c >> 2) ^ bs ^ 1) + (c & 3);
 
-  // run sums of a granule from the lane's operand quad d: Re, Im of state 4 s + q of run c in slot s
-  auto run_sums = [&](const double (&d)[4], double (&br)[NS], double (&bi)[NS]) {
+  // run sums from the lane's operand quad d (WIDE) or its thirds x: Re, Im of state 4 s + q of the lane's
+  // column in slot s
+  using sum_t = typename std::conditional<WIDE, double, float>::type;
+  auto run_sums = [&](const double (&d)[4], const v6i& x, sum_t (&br)[NS], sum_t (&bi)[NS]) {
 #pragma unroll
     for (int b = 0; b < MB; ++b) {
-      v4d acc = {0, 0, 0, 0};
+      typename std::conditional<WIDE, v4d, v4f>::type acc = {0, 0, 0, 0};
+      if constexpr (WIDE) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Pm[b][k], d[k], acc, 0, 0, 0);
+        for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Pm[b][k], d[k], acc, 0, 0, 0);
+      } else {
+        acc = product_t(Pw[b], x, acc);
+      }
       br[2 * b] = acc[0]; bi[2 * b] = acc[1];
       if (2 * b + 1 < NS) { br[2 * b + 1] = acc[2]; bi[2 * b + 1] = acc[3]; }
     }
   };
+  // (xr, xi) <- (cr, ci) (yr, yi) + (xr, xi)
+  auto mac = [](double cr, double ci, double yr, double yi, double& xr, double& xi) {
+    xr = fma(cr, yr, fma(-ci, yi, xr));
+    xi = fma(cr, yi, fma(ci, yr, xi));
+  };
 
-  const int64_t js = kGran * g0 - m + row.jout0;   // position of the piece's first output
+  const int64_t js = first + row.jout0;   // position of the piece's first output
   // the states before position js: every lane of row q holds state 4 s + q in slot s
   double zr[ST][NS], zi[ST][NS];
 #pragma unroll
@@ -203,13 +306,17 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
   {
     const int64_t lo = js - L2 > 0 ? js - L2 : 0;
     const int64_t nw = js > lo && lo < N ? (js - lo + kGran - 1) / kGran : 0;
-    if (nw > 0) {
+    if (nw > 0) {   // 256 positions at a time, run c of 16 per lane column
+      const int w1 = 4 * (4 * (lane >> 2) + ((lane & 3) ^ swz(lane >> 2)));
+      double gr[NS], gi[NS];
+#pragma unroll
+      for (int s = 0; s < NS; ++s) { gr[s] = td[lay.dG(1, s, 0) + q]; gi[s] = td[lay.dG(1, s, 1) + q]; }
       Quad<IN> y;
       int64_t p = js - kGran * nw;
       y.load(xs, p, lo, N, N, lane);
       for (int64_t i = 0; i < nw; ++i) {
 #pragma unroll
-        for (int t = 0; t < ST; ++t) *reinterpret_cast<v4f*>(s_y[t] + wslot) = y.f32(t);
+        for (int t = 0; t < ST; ++t) *reinterpret_cast<v4f*>(s_y[t] + w1) = y.f32(t);
         p += kGran;
         if (i + 1 < nw) y.load(xs, p, lo, N, N, lane);
         lds_order();
@@ -220,17 +327,22 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
 #pragma unroll
         for (int t = 0; t < ST; ++t) {
           const double d[4] = {(double)ya[t][0], (double)ya[t][1], (double)ya[t][2], (double)ya[t][3]};
-          double br[NS], bi[NS];
-          run_sums(d, br, bi);
+          v6i x = {};
+          if constexpr (!WIDE) {
+            const float f[4] = {ya[t][0], ya[t][1], ya[t][2], ya[t][3]};
+            x = thirds(f);
+          }
+          sum_t br[NS], bi[NS];
+          run_sums(d, x, br, bi);
 #pragma unroll
-          for (int s = 0; s < NS; ++s) {   // per run: acc <- a^256 acc + B
-            const double nr = fma(gr[s], zr[t][s], fma(-gi[s], zi[t][s], br[s]));
-            zi[t][s] = fma(gr[s], zi[t][s], fma(gi[s], zr[t][s], bi[s]));
-            zr[t][s] = nr;
+          for (int s = 0; s < NS; ++s) {   // per column: z <- a^256 z + B
+            double xr = br[s], xi = bi[s];
+            mac(gr[s], gi[s], zr[t][s], zi[t][s], xr, xi);
+            zr[t][s] = xr; zi[t][s] = xi;
           }
         }
       }
-      // sum over the runs, weighted a^{16 (15 - c)}
+      // sum over the columns, weighted a^{16 (15 - c)}
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         const double wr = td[lay.dLANE(s, 0) + (lane ^ 15)], wi = td[lay.dLANE(s, 1) + (lane ^ 15)];
@@ -245,126 +357,232 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
     }
   }
 
-  Quad<IN> ya, yb;
-  ya.load(xs, js, 0, N, N, lane);
-  yb.load(xs, js - L2, 0, N, N, lane);
-  for (int64_t g = 0; g < gn; ++g) {
-    const int64_t j = js + kGran * g;
+  Quad<IN> ya[NST], yb[NST];
 #pragma unroll
-    for (int t = 0; t < ST; ++t) {
-      *reinterpret_cast<v4f*>(s_y[t] + wslot) = ya.f32(t);
-      *reinterpret_cast<v4f*>(s_b[t] + wslot) = yb.f32(t);
-    }
-    if (g + 1 < gn) {   // the next granule's samples, in flight during this one
-      ya.load(xs, j + kGran, 0, N, N, lane);
-      yb.load(xs, j + kGran - L2, 0, N, N, lane);
-    }
-    lds_order();
-    float df[ST][4], b[ST][4];
-    double d[ST][4];
+  for (int k = 0; k < NST; ++k) {
+    ya[k].load(xs, js + kGran * k, 0, N, N, lane);
+    yb[k].load(xs, js + kGran * k - L2, 0, N, N, lane);
+  }
+  // one step from output n0. INNER: every output is the piece's, and the next step's samples lie inside the
+  // signal: the stores and loads are unconditional, so waiting for the loads does not wait for stores
+  // that follow them.
+  auto step = [&](auto inner, int64_t n0) {
+    constexpr bool INNER = decltype(inner)::value;
 #pragma unroll
-    for (int t = 0; t < ST; ++t) {
-      const v4f a = *reinterpret_cast<const v4f*>(s_y[t] + rslot), bb = *reinterpret_cast<const v4f*>(s_b[t] + rslot);
+    for (int t = 0; t < ST; ++t)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) { d[t][k] = fma(-Dd, (double)bb[k], (double)a[k]); df[t][k] = (float)d[t][k]; }
-      b[t][0] = s_b[t][bslot0]; b[t][1] = s_b[t][bslot0 + 16];
-      b[t][2] = s_b[t][bslot1]; b[t][3] = s_b[t][bslot1 + 16];
-    }
-    lds_order();
-
-    double br[ST][NS], bi[ST][NS];
-    bool odd = false;   // some input is infinite or NaN (or the run's sum overflows)
+      for (int k = 0; k < NST; ++k) {
+        *reinterpret_cast<v4f*>(s_y[t] + wslot[k]) = ya[k].f32(t);
+        *reinterpret_cast<v4f*>(s_b[t] + wslot[k]) = yb[k].f32(t);
+      }
+    if (INNER || n0 + G < nend) {   // the next samples, in flight during these
+      const int64_t j = n0 + G + row.jout0;
 #pragma unroll
-    for (int t = 0; t < ST; ++t) odd = odd || !__builtin_isfinite((df[t][0] + df[t][1]) + (df[t][2] + df[t][3]));
-
-    v4f o[NC];
-#pragma unroll
-    for (int k = 0; k < NC; ++k)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) o[k][v] = Y[k] * b[k % ST][v];
-    if (__ballot(odd) == 0) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int k = 0; k < NC; ++k) o[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(df[k % ST][i], T[k][i], o[k], 0, 0, 0);
-    } else {
-#pragma unroll 1
-      for (int r = 0; r < kRun; ++r) {   // column r from the inputs up to position r
-#pragma unroll
-        for (int k = 0; k < NC; ++k) {
-          v4f t = o[k];
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            t = __builtin_amdgcn_mfma_f32_16x16x4f32(4 * q + i <= r ? df[k % ST][i] : 0.0f, T[k][i], t, 0, 0, 0);
-#pragma unroll
-          for (int v = 0; v < 4; ++v) o[k][v] = c == r ? t[v] : o[k][v];
-        }
+      for (int k = 0; k < NST; ++k) {
+        ya[k].template load<INNER>(xs, j + kGran * k, 0, N, N, lane);
+        yb[k].template load<INNER>(xs, j + kGran * k - L2, 0, N, N, lane);
       }
     }
+    lds_order();
 
+    // float32 dy of run i, for the rare cases
+    auto differences = [&](int t, int i, float (&f)[4]) {
+      const v4f a = *reinterpret_cast<const v4f*>(s_y[t] + i * PS + rslot);
+      const v4f b = *reinterpret_cast<const v4f*>(s_b[t] + i * PS + rslot);
 #pragma unroll
-    for (int t = 0; t < ST; ++t) run_sums(d[t], br[t], bi[t]);
-
-    // states before the runs
-    float sf[ST][2 * NS];
+      for (int k = 0; k < 4; ++k) f[k] = WIDE ? (float)fma(-Dd, (double)b[k], (double)a[k]) : fmaf(-Df, b[k], a[k]);
+    };
+    // run sums of the columns' runs, then the state before each column
+    float df[WIDE ? ST : 1][NST][4];       // dy (WIDE), or its thirds
+    v6i dx[WIDE ? 1 : ST][NST];
+    sum_t br[ST][NST][NS], bi[ST][NST][NS];
+    double er[ST][NS], ei[ST][NS];
+    bool odd = false;   // some input is infinite or NaN (or a run's sum overflows)
+#pragma unroll
+    for (int t = 0; t < ST; ++t)
+#pragma unroll
+      for (int i = 0; i < NST; ++i) {
+        const v4f a = *reinterpret_cast<const v4f*>(s_y[t] + i * PS + rslot);
+        const v4f b = *reinterpret_cast<const v4f*>(s_b[t] + i * PS + rslot);
+        double d[4] = {0, 0, 0, 0};
+        float f[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if constexpr (WIDE) {
+            d[k] = fma(-Dd, (double)b[k], (double)a[k]);
+            f[k] = df[t][i][k] = (float)d[k];
+          } else {
+            f[k] = fmaf(-Df, b[k], a[k]);
+          }
+        }
+        odd = odd || !__builtin_isfinite((f[0] + f[1]) + (f[2] + f[3]));
+        if constexpr (!WIDE) dx[t][i] = thirds(f);
+        run_sums(d, dx[WIDE ? 0 : t][i], br[t][i], bi[t][i]);
+        __builtin_amdgcn_sched_barrier(0);   // a run at a time (registers)
+      }
+    const bool slow = __ballot(odd) != 0;
+    if (slow) {   // the run product sees zeros for those inputs (below), the run sums have seen them
+#pragma unroll
+      for (int t = 0; t < ST; ++t)
+#pragma unroll
+        for (int i = 0; i < NST; ++i) {
+          float f[4];
+          differences(t, i, f);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) f[k] = __builtin_isfinite(f[k]) ? f[k] : 0.0f;
+          if constexpr (WIDE) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) df[t][i][k] = f[k];
+          } else {
+            dx[t][i] = thirds(f);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+    }
 #pragma unroll
     for (int t = 0; t < ST; ++t) {
-      // the granule's carry enters run 0: B_0 += a^16 Z, then one scan gives the full states
+      double fr[NS], fi[NS];   // sum over the column's runs; the carry enters column 0
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        const double fr = c == 0 ? zr[t][s] : 0.0, fi = c == 0 ? zi[t][s] : 0.0;
-        br[t][s] = fma(scr[0][s], fr, fma(-sci[0][s], fi, br[t][s]));
-        bi[t][s] = fma(scr[0][s], fi, fma(sci[0][s], fr, bi[t][s]));
+        fr[s] = c == 0 ? zr[t][s] : 0.0;
+        fi[s] = c == 0 ? zi[t][s] : 0.0;
+#pragma unroll
+        for (int i = 0; i < NST; ++i) {
+          double xr = br[t][i][s], xi = bi[t][i][s];
+          mac(ar[s], ai[s], fr[s], fi[s], xr, xi);
+          fr[s] = xr; fi[s] = xi;
+        }
       }
-#define MK_LEVEL(D, SH)                                                              \
-  _Pragma("unroll") for (int s = 0; s < NS; ++s) {                                   \
-    const double ur = row_shr<SH>(br[t][s]), ui = row_shr<SH>(bi[t][s]);               \
-    br[t][s] = fma(scr[D][s], ur, fma(-sci[D][s], ui, br[t][s]));                    \
-    bi[t][s] = fma(scr[D][s], ui, fma(sci[D][s], ur, bi[t][s]));                     \
+      // inclusive scan over the columns, constants a^{16 NST 2^d}
+#define MK_LEVEL(D, SH)                                                                        \
+  _Pragma("unroll") for (int s = 0; s < NS; ++s) {                                             \
+    const double2 a = s_k[(D * NS + s) * 4 + q];                                               \
+    mac(a.x, a.y, row_shr<SH>(fr[s]), row_shr<SH>(fi[s]), fr[s], fi[s]);                       \
   }
       MK_LEVEL(0, 1) MK_LEVEL(1, 2) MK_LEVEL(2, 4) MK_LEVEL(3, 8)
 #undef MK_LEVEL
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        const double er = row_shr<1>(br[t][s]), ei = row_shr<1>(bi[t][s]);
-        sf[t][2 * s] = (float)(c == 0 ? zr[t][s] : er);
-        sf[t][2 * s + 1] = (float)(c == 0 ? zi[t][s] : ei);
-        zr[t][s] = row_last(br[t][s]);
-        zi[t][s] = row_last(bi[t][s]);
+        const double pr = row_shr<1>(fr[s]), pi = row_shr<1>(fi[s]);
+        er[t][s] = c == 0 ? zr[t][s] : pr;
+        ei[t][s] = c == 0 ? zi[t][s] : pi;
+        zr[t][s] = row_last(fr[s]);
+        zi[t][s] = row_last(fi[s]);
       }
     }
-#pragma unroll
-    for (int i = 0; i < 2 * NS; ++i)
-#pragma unroll
-      for (int k = 0; k < NC; ++k) o[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(sf[k % ST][i], C[k][i], o[k], 0, 0, 0);
 
-    // lane 16 q + r: position r of runs 4 q + v
-    const int64_t n0 = kGran * (g0 + g) - m;
     unsigned char* w = REV ? W + (N - 1 - n0) * OB : W + n0 * OB;   // wave-uniform
-    const bool whole = n0 >= 0 && n0 + kGran <= N;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int e = 64 * q + 16 * v + c;
-      if (whole || (n0 + e >= 0 && n0 + e < N)) {
-        if constexpr (REV) {
-          float* y = reinterpret_cast<float*>(w) - e;
-          __builtin_nontemporal_store(CPLX ? o[0][v] + o[NC - 1][v] : o[0][v], y);
-        } else if constexpr (CPLX) {
-          __builtin_nontemporal_store(v2f{o[0][v], o[NC - 1][v]}, reinterpret_cast<v2f*>(w) + e);
-        } else {
-          __builtin_nontemporal_store(o[0][v], reinterpret_cast<float*>(w) + e);
+    for (int i = 0; i < NST; ++i) {
+      v4f o[NC];
+      v6i sx[ST][SETS];
+#pragma unroll
+      for (int t = 0; t < ST; ++t) {
+#pragma unroll
+        for (int e = 0; e < SETS; ++e) {
+          float x[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int s = 2 * e + k / 2;
+            x[k] = s < NS ? (float)(k & 1 ? ei[t][s < NS ? s : 0] : er[t][s < NS ? s : 0]) : 0.0f;
+          }
+          sx[t][e] = thirds(x);
+        }
+        if (i + 1 < NST) {
+#pragma unroll
+          for (int s = 0; s < NS; ++s) {   // on to the next run of the column
+            double xr = br[t][i][s], xi = bi[t][i][s];
+            mac(ar[s], ai[s], er[t][s], ei[t][s], xr, xi);
+            er[t][s] = xr; ei[t][s] = xi;
+          }
         }
       }
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        const float* b = s_b[k % ST] + i * PS;
+        const float bv[4] = {b[bslot0], b[bslot0 + 16], b[bslot1], b[bslot1 + 16]};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[k][v] = Y[k] * bv[v];
+      }
+      [[maybe_unused]] v6i wx[ST];
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        if constexpr (WIDE) {
+          if (k < ST) wx[k] = thirds(df[k % ST][i]);
+          o[k] = product(wx[k % ST], T[k], o[k]);
+        } else {
+          o[k] = product(dx[k % ST][i], T[k], o[k]);
+        }
+      }
+      if (slow) {
+        // an infinite or NaN input reaches the outputs of its run from its own position on: bit 16 q' + c'
+        // of bad marks input 4 q' + e of column c'
+#pragma unroll 1
+        for (int e = 0; e < 4; ++e) {
+          bool mine = false;
+#pragma unroll
+          for (int t = 0; t < ST; ++t) {
+            float f[4];
+            differences(t, i, f);
+            const float fe = e == 0 ? f[0] : e == 1 ? f[1] : e == 2 ? f[2] : f[3];
+            mine = mine || !__builtin_isfinite(fe);
+          }
+          const unsigned long long bad = __ballot(mine);
+          // columns 4 q + v, positions 4 q' + e <= c
+          unsigned long long upto = 0;
+          for (int r = 0; r < 4; ++r)
+            if (4 * r + e <= c) upto |= bad >> (16 * r);
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if ((upto >> (4 * q + v)) & 1)
+#pragma unroll
+              for (int k = 0; k < NC; ++k) o[k][v] = __builtin_nanf("");
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < NC; ++k)
+#pragma unroll
+        for (int e = 0; e < SETS; ++e) o[k] = product(sx[k % ST][e], C[k][e], o[k]);
+
+      // lane 16 q + r: position r of run i of columns 4 q + v
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int e = kRun * (NST * (4 * q + v) + i) + c;
+        if (INNER || (n0 + e >= 0 && n0 + e < nend)) {
+          if constexpr (REV) {
+            __builtin_nontemporal_store(CPLX ? o[0][v] + o[NC - 1][v] : o[0][v], reinterpret_cast<float*>(w) - e);
+          } else if constexpr (CPLX) {
+            __builtin_nontemporal_store(v2f{o[0][v], o[NC - 1][v]}, reinterpret_cast<v2f*>(w) + e);
+          } else {
+            __builtin_nontemporal_store(o[0][v], reinterpret_cast<float*>(w) + e);
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
-  }
+    lds_order();   // the next samples overwrite these
+  };
+  // steps [inner0, inner1) from the first are INNER: outputs n0 >= 0 and n0 + G <= nend, and for the next
+  // step's samples j + G - 2L >= 0 and j + 2 G <= N
+  const int64_t steps = (nend - first + G - 1) / G;
+  auto up = [](int64_t v) { return v <= 0 ? (int64_t)0 : (v + G - 1) / G; };
+  const int64_t inner0 = up(-first) > up(L2 - js - G) ? up(-first) : up(L2 - js - G);
+  const int64_t fit = nend - first < N - js - G ? nend - first : N - js - G;   // inner while n0 - first + G <= fit
+  const int64_t inner1 = fit < G ? 0 : fit / G;
+  int64_t k = 0;
+  for (; k < steps && (k < inner0 || k >= inner1); ++k) step(std::false_type{}, first + G * k);
+  for (; k < inner1; ++k) step(std::true_type{}, first + G * k);
+  for (; k < steps; ++k) step(std::false_type{}, first + G * k);
 }
 
 using GranFn = void (*)(GranLaunch);
 
 template <int NS>
-GranFn pick(bool cplx, int in) {
+GranFn pick(bool cplx, int in, bool two, bool wide) {
 #define MK_PICK(C, D) \
-  if (cplx == (C) && in == (D)) return granule_kernel<NS, C, D>;
+  if (cplx == (C) && in == (D)) \
+    return wide ? (two ? granule_kernel<NS, C, D, 2, true> : granule_kernel<NS, C, D, 1, true>) \
+                : (two ? granule_kernel<NS, C, D, 2, false> : granule_kernel<NS, C, D, 1, false>);
   MK_PICK(false, 0) MK_PICK(false, 1) MK_PICK(false, 2) MK_PICK(false, 4)
   MK_PICK(true, 0) MK_PICK(true, 1) MK_PICK(true, 2) MK_PICK(true, 3)
 #undef MK_PICK
@@ -380,7 +598,10 @@ hipError_t launch_granules(const GranLaunch& a, hipStream_t s) {
   const bool cplx = a.kind == 0;
   const int ns = GranLayout{a.K}.NS();
   const int in = a.adjoint ? (cplx ? 3 : 4) : a.dtype;
-  const GranFn fn = ns == 1 ? pick<1>(cplx, in) : ns == 2 ? pick<2>(cplx, in) : pick<3>(cplx, in);
+  // two runs per lane column halve the scans across lanes in long pieces (ragged scalogram 1000 us a
+  // launch against 1090); four leave two waves per SIMD (1005)
+  const bool two = a.two != 0;
+  const GranFn fn = ns == 1 ? pick<1>(cplx, in, two, a.acc == kAccMixed) : ns == 2 ? pick<2>(cplx, in, two, a.acc == kAccMixed) : pick<3>(cplx, in, two, a.acc == kAccMixed);
   if (!fn) return hipErrorInvalidValue;
   hipLaunchKernelGGL(fn, dim3((unsigned)a.nseg), dim3(64), 0, s, a);
   return hipGetLastError();

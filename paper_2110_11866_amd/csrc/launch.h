@@ -47,6 +47,7 @@ struct ScanLaunch {
   const GranSeg* gran_segs;
   int64_t gran_nseg;
   int32_t gran_pieces, gran_n;
+  int gran_two;                 // two granules at a time (pieces of an even number of them)
   const unsigned char* gran_tabs;   // granule constants of scale 0 (stride tab_stride)
   // Column scan (granule.h), when col_cols > 0: row0 runs down the columns of a float32 matrix of row0.N
   // rows and col_cols columns, col_piece output rows per wave.

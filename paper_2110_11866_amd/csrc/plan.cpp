@@ -431,7 +431,7 @@ void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, dou
       td[lay.dLANE(slot, 0) + 16 * q + d] = re;
       td[lay.dLANE(slot, 1) + 16 * q + d] = im;
     }
-    for (int d = 0; d < 4; ++d) {
+    for (int d = 0; d < 6; ++d) {
       apow(p, (int64_t)kRun << d, L, alpha, re, im);
       td[lay.dSC(d, slot, 0) + q] = re;
       td[lay.dSC(d, slot, 1) + q] = im;
@@ -447,6 +447,42 @@ void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, dou
       tf[lay.fTre(rp % 4) + 16 * (rp / 4) + r] = (float)T[0][r - rp];
       tf[lay.fTim(rp % 4) + 16 * (rp / 4) + r] = (float)T[1][r - rp];
     }
+  // thirds: the nearest bfloat16 of the value, of what is left, and the rest
+  auto thirds = [](float v, uint16_t* h, uint16_t* m, uint16_t* l) {
+    auto near = [](float x) {   // round to nearest even
+      uint32_t u;
+      std::memcpy(&u, &x, 4);
+      return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1)) >> 16);
+    };
+    auto value = [](uint16_t b) {
+      const uint32_t u = (uint32_t)b << 16;
+      float x;
+      std::memcpy(&x, &u, 4);
+      return x;
+    };
+    *h = near(v);
+    const float r = v - value(*h);
+    *m = near(r);
+    *l = near(r - value(*m));
+  };
+  uint16_t* bq = reinterpret_cast<uint16_t*>(dst + lay.quadOff());
+  for (int b = 0; b < lay.MB(); ++b)
+    for (int lane = 0; lane < 64; ++lane)
+      for (int e = 0; e < 4; ++e) {
+        const int u = lane / 4 % 4, v = lane % 4;   // the float64 table has row u + 4 v
+        thirds((float)td[lay.dP(b, e) + 16 * (lane / 16) + u + 4 * v], bq + 4 * (lay.bP(b, 0) + lane) + e,
+               bq + 4 * (lay.bP(b, 1) + lane) + e, bq + 4 * (lay.bP(b, 2) + lane) + e);
+      }
+  for (int c = 0; c < 2; ++c)
+    for (int lane = 0; lane < 64; ++lane)
+      for (int e = 0; e < 4; ++e) {
+        thirds(tf[(c ? lay.fTim(e) : lay.fTre(e)) + lane], bq + 4 * (lay.bT(c, 0) + lane) + e,
+               bq + 4 * (lay.bT(c, 1) + lane) + e, bq + 4 * (lay.bT(c, 2) + lane) + e);
+        for (int set = 0; set < lay.SETS(); ++set)
+          if (4 * set + e < 2 * lay.NS())
+            thirds(tf[(c ? lay.fCim(4 * set + e) : lay.fCre(4 * set + e)) + lane], bq + 4 * (lay.bC(c, set, 0) + lane) + e,
+                   bq + 4 * (lay.bC(c, set, 1) + lane) + e, bq + 4 * (lay.bC(c, set, 2) + lane) + e);
+      }
   tf[lay.fYre()] = (float)(gre * cx);
   tf[lay.fYim()] = (float)(gim * cx);
   td[lay.dD()] = std::exp(-2.0 * alpha * (double)L);
@@ -454,7 +490,8 @@ void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, dou
 
 int64_t GranSplit::piece(int64_t nw) const {
   const int64_t n = (int64_t)std::ceil(per_warm * (double)nw);
-  return std::min<int64_t>(std::max(base, n), (int64_t)1 << 30);
+  const int64_t p = std::min<int64_t>(std::max(base, n), (int64_t)1 << 30);
+  return two() ? (p + 1) / 2 * 2 : p;
 }
 
 GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus, double kWarm) {

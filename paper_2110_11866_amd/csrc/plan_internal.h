@@ -58,6 +58,7 @@ struct morlet_plan_s {
   int32_t qstart[mk::kQueues + 1] = {0};   // queue q is row_order[qstart[q] .. qstart[q + 1])
   int64_t max_row_tiles = 0;
   int64_t ntiles = 0, ntiles_max = 0;
+  bool gran_two = false;                   // granule scan: every piece starts on an even granule
   std::vector<mk::GranSeg> gran_segs;      // granule scan: pieces of the rows in launch order
   void* d_rows = nullptr;                  // device rows, then tile_row, row_order, gran_segs
   size_t rows_bytes = 0;
@@ -122,7 +123,10 @@ struct GranSplit {
   int64_t base = 1;      // granules per piece, at least
   double per_warm = 0;   // and at least this many per granule of the window
   double cost = 0;       // estimated time of the launch, in granule times of a wave on a full device
-  int64_t piece(int64_t nw) const;
+  int64_t piece(int64_t nw) const;   // even with two()
+  // two granules at a time: halves the scans across lanes, but starts and ends cost more; from pieces of
+  // eight granules on (4096^2 image, pieces of four: 98 us with two, 93 with one)
+  bool two() const { return base >= 8; }
 };
 struct GranRow {
   int64_t ng, nw, count;   // granules, window granules, rows of this shape

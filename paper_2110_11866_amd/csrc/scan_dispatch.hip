@@ -311,11 +311,11 @@ hipError_t launch_scan(const ScanLaunch& a, int variant, int mom, hipStream_t s)
   if (a.gran_nseg > 0) {
     if ((variant != kVarForward && variant != kVarAdjoint) || a.nrows < 1) return hipErrorInvalidValue;
     GranLaunch g{};
-    g.K = a.K; g.kind = a.kind; g.dtype = a.dtype;
+    g.K = a.K; g.acc = a.acc; g.kind = a.kind; g.dtype = a.dtype;
     g.adjoint = variant == kVarAdjoint;
     g.x = a.x; g.out = a.out;
     g.row0 = a.row0; g.rows = a.rows; g.nrows = a.nrows; g.segs = a.gran_segs;
-    g.nseg = a.gran_nseg; g.pieces = a.gran_pieces; g.seg_n = a.gran_n;
+    g.nseg = a.gran_nseg; g.pieces = a.gran_pieces; g.seg_n = a.gran_n; g.two = a.gran_two;
     g.tabs = a.gran_tabs; g.tab_stride = a.tab_stride;
     return launch_granules(g, s);
   }

@@ -36,7 +36,8 @@ def torch_dtype_code(dt: torch.dtype) -> int:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the current device's current stream, without building a Stream object
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 class _PlanBase:
@@ -90,7 +91,8 @@ class _PlanBase:
         """Refit the coefficients at new sigma (and xi, Morlet plans) with the window, lowest
         order, ASFT shift and tile shape kept, into the plan's own device table on the
         current stream (morlet_plan_refit; single-signal Morlet and Gaussian plans)."""
-        _abi.morlet_plan_refit(self.handle, float(sigma), float(xi), _stream() if torch.cuda.is_available() else 0)
+        _abi.morlet_plan_refit(self.handle, float(sigma), float(xi),
+                               torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else 0)
         self.sigma = float(sigma)
         if self.kind == "morlet":
             self.xi = float(xi)
@@ -136,9 +138,10 @@ class _PlanBase:
         """A zero-filled workspace owned by the plan (allocated on first use); the backward
         size also serves the forward."""
         need = self.backward_workspace_bytes() if backward else self.workspace_bytes()
-        if self._ws is None or self._ws.numel() < need or self._ws.device != torch.device(device):
-            self._ws = torch.zeros(max(need, 64), dtype=torch.uint8, device=device)
-        return self._ws
+        w = self._ws
+        if w is None or w.numel() < need or w.device != torch.device(device):
+            w = self._ws = torch.zeros(max(need, 64), dtype=torch.uint8, device=device)
+        return w
 
     def _check_x(self, x: torch.Tensor) -> None:
         if not x.is_cuda:
@@ -186,7 +189,7 @@ class MorletPlan(_PlanBase):
         self._check_x(x)
         if out is None:
             out = torch.empty(self.N, dtype=torch.complex64, device=x.device)
-        if out.dtype != torch.complex64 or out.numel() != self.N or not out.is_contiguous():
+        elif out.dtype != torch.complex64 or out.numel() != self.N or not out.is_contiguous():
             raise ValueError("out must be a contiguous complex64 tensor of N elements")
         w = self.workspace(x.device) if ws is None else ws
         _abi.morlet_forward(self.handle, x.data_ptr(), torch_dtype_code(x.dtype), out.data_ptr(), w.data_ptr(),
@@ -258,7 +261,7 @@ class GaussPlan(_PlanBase):
         self._check_x(x)
         if out is None:
             out = torch.empty(self.N, dtype=torch.float32, device=x.device)
-        if out.dtype != torch.float32 or out.numel() != self.N or not out.is_contiguous():
+        elif out.dtype != torch.float32 or out.numel() != self.N or not out.is_contiguous():
             raise ValueError("out must be a contiguous float32 tensor of N elements")
         w = self.workspace(x.device) if ws is None else ws
         _abi.gauss_smooth(self.handle, x.data_ptr(), torch_dtype_code(x.dtype), out.data_ptr(), w.data_ptr(),
@@ -329,7 +332,7 @@ class Gauss2DPlan(_PlanBase):
         self._check_x(x)
         if out is None:
             out = torch.empty((self.H, self.W), dtype=torch.float32, device=x.device)
-        if out.dtype != torch.float32 or out.numel() != self.N or not out.is_contiguous():
+        elif out.dtype != torch.float32 or out.numel() != self.N or not out.is_contiguous():
             raise ValueError("out must be a contiguous float32 tensor of H x W elements")
         w = self.workspace(x.device) if ws is None else ws
         _abi.gauss_smooth2d(self.handle, x.data_ptr(), torch_dtype_code(x.dtype), out.data_ptr(), w.data_ptr(),
@@ -395,7 +398,7 @@ class Gabor2DPlan(_PlanBase):
             raise ValueError(f"x must be a contiguous tensor of {self.H} x {self.W} pixels")
         if out is None:
             out = torch.empty((self.H, self.W), dtype=torch.complex64, device=x.device)
-        if out.dtype != torch.complex64 or out.numel() != self.N or not out.is_contiguous():
+        elif out.dtype != torch.complex64 or out.numel() != self.N or not out.is_contiguous():
             raise ValueError("out must be a contiguous complex64 tensor of H x W elements")
         w = self.workspace(x.device) if ws is None else ws
         _abi.gabor2d(self.handle, x.data_ptr(), torch_dtype_code(x.dtype), out.data_ptr(), w.data_ptr(), w.numel(),
@@ -460,7 +463,7 @@ class ScalogramPlan(_PlanBase):
         total = self.S * self.N
         if out is None:
             out = torch.empty(total, dtype=torch.complex64, device=x.device)
-        if out.dtype != torch.complex64 or out.numel() != total or not out.is_contiguous():
+        elif out.dtype != torch.complex64 or out.numel() != total or not out.is_contiguous():
             raise ValueError("out must be a contiguous complex64 tensor of S * sum(lengths) elements")
         w = self.workspace(x.device) if ws is None else ws
         _abi.morlet_scalogram_forward(self.handle, x.data_ptr(), torch_dtype_code(x.dtype), out.data_ptr(),
@@ -488,6 +491,7 @@ class _MorletFn(torch.autograd.Function):
         # the parameter gradients come back in the parameters' own dtypes (float64 for the
         # layer's parameters), never rounded through float32 on the way
         ctx.param_dtypes = tuple(v.dtype if torch.is_tensor(v) else torch.float64 for v in (sigma, xi))
+        ctx.host_params = all(torch.is_tensor(v) and v.device.type == "cpu" for v in (sigma, xi))
         ctx.save_for_backward(x)
         return plan.forward(x.contiguous())
 
@@ -498,6 +502,8 @@ class _MorletFn(torch.autograd.Function):
         gx, gp = ctx.plan.backward(x.contiguous(), gW.contiguous().to(torch.complex64), want_params=want_p)
         gs = gxi = None
         if want_p:
+            if ctx.host_params:   # one copy (and wait) for both, where autograd would make one for each
+                gp = gp.cpu()
             gs = gp[0].to(ctx.param_dtypes[0]) if ctx.needs_input_grad[1] else None
             gxi = gp[1].to(ctx.param_dtypes[1]) if ctx.needs_input_grad[2] else None
         return (gx.to(x.dtype) if ctx.needs_input_grad[0] else None), gs, gxi, None

@@ -198,7 +198,10 @@ bool equal_rows(const morlet_plan_s* p) {
 // interleaved.
 void build_gran_segs(morlet_plan_s* p) {
   p->gran_segs.clear();
-  if (equal_rows(p)) return;   // their pieces follow from the index
+  if (equal_rows(p)) {   // their pieces follow from the index
+    mk::set_split(p, p->rows.empty() ? 0 : p->rows[0].N, p->rows.empty() ? 0 : p->rows[0].L, (int64_t)p->rows.size());
+    return;
+  }
   const int S = p->S > 0 ? p->S : 1;
   if ((int64_t)p->rows.size() != (int64_t)p->B * S) return;
   auto window = [](const mk::Row& r) { return (2 * r.L + mk::kGran - 1) / mk::kGran; };
@@ -442,7 +445,9 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant) {
   const mk::Row& row = plan->batched ? plan->rows[0] : a.row0;
   const int64_t ng = mk::granules_for(row.N), nw = (2 * row.L + mk::kGran - 1) / mk::kGran;
   if (ng == 0) return false;
-  const mk::GranSplit split = mk::split_granules({{ng, nw, nrows}}, plan->num_cus);
+  // found when the plan was built; a row padded by its boundary has its own
+  const mk::GranSplit split = ng == plan->gran_ng && nw == plan->gran_nw ? plan->gran_split
+                                                                        : mk::split_granules({{ng, nw, nrows}}, plan->num_cus);
   const int64_t n = split.piece(nw), ns = (ng + n - 1) / n;
   if (ns * nrows > INT32_MAX) return false;
   // A window much longer than a piece is summed by every piece: the tiles schedule, whose tiles hand

@@ -524,7 +524,14 @@ GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus, double k
   return best;
 }
 
+void set_split(morlet_plan_s* p, int64_t N, int64_t L, int64_t count) {
+  p->gran_ng = granules_for(N);
+  p->gran_nw = (2 * L + kGran - 1) / kGran;
+  p->gran_split = split_granules({{p->gran_ng, p->gran_nw, count}}, p->num_cus);
+}
+
 bool build_table(morlet_plan_s* p, std::string* err) {
+  if (p->gran_ng < 0) set_split(p, p->N, p->L, 1);
   p->h_tab.assign(scale_bytes(p->K, p->R), 0);
   fill_granules(p->h_tab.data() + TabLayout{p->K, p->R}.bytes(), out_kind(p), p->K, p->L, p->P_S, p->sigma, p->xi,
                 p->mode, p->n0, p->cc, p->sc);

@@ -7,6 +7,20 @@
 #include "granule.h"
 #include "layout.h"
 
+namespace mk {
+// Pieces of rows for the granule scan: granules per piece of a row of ng granules whose window spans
+// nw granules (2L positions), from the load of the whole launch.
+struct GranSplit {
+  int64_t base = 1;      // granules per piece, at least
+  double per_warm = 0;   // and at least this many per granule of the window
+  double cost = 0;       // estimated time of the launch, in granule times of a wave on a full device
+  int64_t piece(int64_t nw) const;   // even with two()
+  // two granules at a time: halves the scans across lanes, but starts and ends cost more; from pieces of
+  // eight granules on (4096^2 image, pieces of four: 98 us with two, 93 with one)
+  bool two() const { return base >= 8; }
+};
+}  // namespace mk
+
 // One scale of a batched plan.
 struct ScaleParams {
   double sigma = 0, xi = 0;
@@ -58,6 +72,8 @@ struct morlet_plan_s {
   int32_t qstart[mk::kQueues + 1] = {0};   // queue q is row_order[qstart[q] .. qstart[q + 1])
   int64_t max_row_tiles = 0;
   int64_t ntiles = 0, ntiles_max = 0;
+  int64_t gran_ng = -1, gran_nw = -1;      // rows of one length: the granules, window granules and split
+  mk::GranSplit gran_split;
   bool gran_two = false;                   // granule scan: every piece starts on an even granule
   std::vector<mk::GranSeg> gran_segs;      // granule scan: pieces of the rows in launch order
   void* d_rows = nullptr;                  // device rows, then tile_row, row_order, gran_segs
@@ -117,21 +133,12 @@ size_t scale_bytes(int K, int R);
 // Output kind of a plan's forward scan.
 int out_kind(const morlet_plan_s* p);
 
-// Pieces of rows for the granule scan: granules per piece of a row of ng granules whose window spans
-// nw granules (2L positions), from the load of the whole launch.
-struct GranSplit {
-  int64_t base = 1;      // granules per piece, at least
-  double per_warm = 0;   // and at least this many per granule of the window
-  double cost = 0;       // estimated time of the launch, in granule times of a wave on a full device
-  int64_t piece(int64_t nw) const;   // even with two()
-  // two granules at a time: halves the scans across lanes, but starts and ends cost more; from pieces of
-  // eight granules on (4096^2 image, pieces of four: 98 us with two, 93 with one)
-  bool two() const { return base >= 8; }
-};
 struct GranRow {
   int64_t ng, nw, count;   // granules, window granules, rows of this shape
 };
 // warm: cost of a window granule relative to one with outputs.
 GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus, double warm = 0.3);
+// The split of `count` rows of N samples with half width L, kept in the plan.
+void set_split(morlet_plan_s* p, int64_t N, int64_t L, int64_t count);
 
 }  // namespace mk

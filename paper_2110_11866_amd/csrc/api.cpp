@@ -421,10 +421,12 @@ morlet_status init_morlet_rows(morlet_plan_s* p, int B, int64_t len, double sigm
   return upload_batched(p);
 }
 
-// Granule scan: a forward or adjoint launch under the automatic schedule and tile shape, float32 or mixed
-// accumulation. Returns whether the launch takes it (a.row0 set for a single row).
+// Granule scan, or carried scan (a.gran_sums set): a forward or adjoint launch under the automatic schedule
+// and tile shape, float32 or mixed accumulation. Returns whether the launch takes one (a.row0 set for a
+// single row, a.ws and a.ntiles set).
 bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant) {
   a.gran_nseg = 0;
+  a.gran_sums = nullptr;
   // not for the adjoint of an edge-extended row: its fold adds up 2L outputs whose sum is smaller by
   // orders of magnitude, and the rounding of the run weights does not average out in it
   if (variant == mk::kVarParamGrad || (variant == mk::kVarAdjoint && plan->boundary == 1) ||
@@ -450,11 +452,28 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant) {
                                                                         : mk::split_granules({{ng, nw, nrows}}, plan->num_cus);
   const int64_t n = split.piece(nw), ns = (ng + n - 1) / n;
   if (ns * nrows > INT32_MAX) return false;
-  // A window much longer than a piece is summed by every piece: the tiles schedule, whose tiles hand
-  // their states on, takes about 16 us for one round of tiles and 0.03 us per tile, the granule scan
-  // 2.6 us per unit of the split's cost (N = 102400, 2L = 65536: 16 against 91 us; N = 2^22,
-  // 2L = 8192: 60 against 37).
-  if (2.6 * split.cost > 16.0 + 0.03 * (double)a.ntiles) return false;
+  // A window much longer than a piece is summed by every piece. The carried scan sums no windows but reads
+  // the row twice, in two launches: about 8 us and 2.7 us per chunk of a block, a block per CU; the granule
+  // scan about 3 us and 1.8 us per unit of the split's cost. K = 5, us, granule | carried: N = 102400, 2L =
+  // 2664: 7 | 10.5, 10650: 15 | 10.2, 42600: 47 | 10.6; N = 2^22, 2L = 10650: 32 | 35, 42600: 72 | 35; N =
+  // 2^24, 2L = 10650: 66 | 96, 42600: 119 | 101. (The tiles schedule, whose tiles wait for the states of the
+  // tiles before them, takes 17, 60 and 111 us there.) The pieces' sums lie in the workspace after its
+  // header, within what the tiles schedule needs.
+  const int64_t all = mk::chunks_for(row.N, row.jout0), most = std::min<int64_t>(all, std::max<int64_t>(1, plan->num_cus / nrows));
+  const int64_t len = (all + most - 1) / most, np = (all + len - 1) / len;
+  const int64_t rounds = (np * nrows + plan->num_cus - 1) / plan->num_cus;
+  if (3.0 + 1.8 * split.cost > 8.0 + 2.7 * (double)(len * rounds)) {
+    const int states = plan->K * (variant == mk::kVarAdjoint && a.kind == 0 ? 2 : 1);
+    if (nrows > 65535 || len > INT32_MAX ||
+        (size_t)((np - 1) * nrows) * states * 16 > mk::tile_state_bytes(states) * (size_t)a.ntiles)
+      return false;
+    a.gran_sums = reinterpret_cast<double*>(static_cast<unsigned char*>(a.ws) + sizeof(mk::WsHeader));
+    a.gran_segs = nullptr;
+    a.gran_pieces = (int32_t)np;
+    a.gran_n = (int32_t)len;
+    a.gran_nseg = np * nrows;
+    return true;
+  }
   a.gran_segs = nullptr;
   a.gran_pieces = (int32_t)ns;
   a.gran_two = split.two();
@@ -581,7 +600,7 @@ morlet_status make_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int v
 morlet_status column_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int variant, int64_t cols, bool& taken) {
   taken = false;
   const morlet_status st = make_launch(plan, a, ws, variant, 0, 0);
-  if (st != MORLET_OK || a.gran_nseg == 0) return st;
+  if (st != MORLET_OK || a.gran_nseg == 0 || a.gran_sums) return st;
   const int64_t nw = (2 * plan->rows[0].L + mk::kRun - 1) / mk::kRun, ng = (plan->rows[0].N + mk::kRun - 1) / mk::kRun;
   const int64_t blocks = (cols + mk::kColWave - 1) / mk::kColWave;
   const mk::GranSplit split = mk::split_granules({{ng, nw, blocks}}, plan->num_cus / 2, 0.5);

@@ -77,8 +77,19 @@ struct GranLaunch {
   int nrows;
   const unsigned char* tabs;    // granule constants of scale 0
   int64_t tab_stride;
+  double* sums;                 // carried scan: [nrows][pieces - 1][streams][K] complex float64
 };
 hipError_t launch_granules(const GranLaunch& a, hipStream_t s);
+
+// Carried scan (carry_scan.hip): rows of one length in `pieces` pieces of seg_n chunks, a block each; the
+// states pass from piece to piece through sums. A row's pieces start at or before position
+// jout0 - 31 - kChunk; together they reach its last output.
+constexpr int kCarryWaves = 8;
+constexpr int64_t kChunk = kCarryWaves * kGran;
+inline int64_t chunks_for(int64_t N, int64_t jout0) {   // chunks of a row of N outputs at any alignment
+  return (jout0 > 0 ? (jout0 + kChunk - 1) / kChunk : 0) + (N + 31 + kChunk - 1) / kChunk;
+}
+hipError_t launch_carried(const GranLaunch& a, hipStream_t s);
 
 // Column scan (column_scan.hip): a real filter along the columns of a rows x cols float32 matrix.
 constexpr int kColWave = 32;    // columns per wave

@@ -31,142 +31,13 @@
 // depends on a later input.
 #include <hip/hip_runtime.h>
 
-#include <type_traits>
-
 #include "granule.h"
+#include "granule_ops.h"
 #include "launch.h"
 #include "scan_common.h"
 
 namespace mk {
 namespace {
-
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef double v4d __attribute__((ext_vector_type(4)));
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef int v2i __attribute__((ext_vector_type(2)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v6i __attribute__((ext_vector_type(6)));
-typedef __bf16 v2b __attribute__((ext_vector_type(2)));
-typedef __bf16 v8b __attribute__((ext_vector_type(8)));
-typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));            // any sample alignment
-typedef unsigned short v4h_any __attribute__((ext_vector_type(4), aligned(2)));
-
-template <int SH, typename T>
-__device__ __forceinline__ T row_shr(T v) {   // lane c of each 16-lane row reads lane c - SH, else 0
-  return __builtin_amdgcn_update_dpp((T)0, v, 0x110 + SH, 0xF, 0xF, true);
-}
-template <typename T>
-__device__ __forceinline__ T row_last(T v) {  // every lane of a row reads its lane 15
-  return __builtin_amdgcn_update_dpp((T)0, v, 0x15F, 0xF, 0xF, true);
-}
-
-// order of a wave's own LDS accesses (the hardware keeps it; this keeps the compiler's)
-__device__ __forceinline__ void lds_order() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-// The wave's quads of samples p0 + 4 lane .. + 3 of ST real streams, zero outside [lo, hi), in the
-// type they are stored in. IN 0, 1, 2: one stream of float32, float16, bfloat16 samples at index p.
-// IN 3, 4: the cotangent of the adjoint, read backwards, sample p at index N - 1 - p: complex64 (its
-// real and imaginary parts two streams) or float32.
-enum { kInRev = 3 };
-template <int IN>
-struct Quad {
-  using E = typename std::conditional<IN == 1 || IN == 2, unsigned short, typename std::conditional<IN == 3, v2f, float>::type>::type;
-  using V = typename std::conditional<IN == 1 || IN == 2, v4h_any, v4f_any>::type;
-  V v[IN == 3 ? 2 : 1];
-  // INNER: the whole granule lies inside [lo, hi)
-  template <bool INNER = false>
-  __device__ __forceinline__ void load(const void* xs, int64_t p0, int64_t lo, int64_t hi, int64_t N, int lane) {
-    const E* x = static_cast<const E*>(xs);
-    const E* p = IN >= kInRev ? x + (N - 4 - p0) : x + p0;   // wave-uniform; the lane's quad starts at p -+ 4 lane
-    const int o = IN >= kInRev ? -4 * lane : 4 * lane;
-    if (INNER || (p0 >= lo && p0 + kGran <= hi)) {
-      v[0] = *reinterpret_cast<const V*>(p + o);
-      if constexpr (IN == 3) v[1] = *reinterpret_cast<const V*>(p + o + 2);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int64_t j = p0 + 4 * lane + (IN >= kInRev ? 3 - e : e);
-        const bool in = j >= lo && j < hi;
-        if constexpr (IN == 3) {
-          const v2f t = in ? p[o + e] : v2f{0.0f, 0.0f};
-          v[e / 2][2 * (e % 2)] = t[0];
-          v[e / 2][2 * (e % 2) + 1] = t[1];
-        } else {
-          v[0][e] = in ? p[o + e] : (E)0;
-        }
-      }
-    }
-  }
-  __device__ __forceinline__ v4f f32(int st) const {   // stream st in scan order
-    if constexpr (IN == 0) return v[0];
-    else if constexpr (IN == 1) return v4f{cvt_f16(v[0][0]), cvt_f16(v[0][1]), cvt_f16(v[0][2]), cvt_f16(v[0][3])};
-    else if constexpr (IN == 2) return v4f{cvt_bf16(v[0][0]), cvt_bf16(v[0][1]), cvt_bf16(v[0][2]), cvt_bf16(v[0][3])};
-    else if constexpr (IN == 3) return v4f{v[1][2 + st], v[1][st], v[0][2 + st], v[0][st]};
-    else return v4f{v[0][3], v[0][2], v[0][1], v[0][0]};
-  }
-};
-
-// Four float32 values as bfloat16 thirds, middle, high, low (two registers each): every value is the
-// exact sum of its thirds. The remainder after a third is one dot product with (-1, 0) or (0, -1).
-__device__ __forceinline__ int bf16_pair(float a, float b) {
-  return __builtin_bit_cast(int, __builtin_convertvector(v2f{a, b}, v2b));
-}
-__device__ __forceinline__ v6i thirds(const float (&x)[4]) {
-  int lo;   // (-1, 0): as a register, an inline constant would stand for another pair
-  asm("s_mov_b32 %0, 0xbf80" : "=s"(lo));
-  const v2b n0 = __builtin_bit_cast(v2b, lo), n1 = __builtin_bit_cast(v2b, (int)0xbf800000);
-  auto left = [&](int p, float a, float b, float& ra, float& rb) {
-    ra = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(v2b, p), n0, a, false);
-    rb = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(v2b, p), n1, b, false);
-  };
-  float r[4], t[4];
-  const int h0 = bf16_pair(x[0], x[1]), h1 = bf16_pair(x[2], x[3]);
-  left(h0, x[0], x[1], r[0], r[1]);
-  left(h1, x[2], x[3], r[2], r[3]);
-  const int m0 = bf16_pair(r[0], r[1]), m1 = bf16_pair(r[2], r[3]);
-  left(m0, r[0], r[1], t[0], t[1]);
-  left(m1, r[2], r[3], t[2], t[3]);
-  return v6i{m0, m1, h0, h1, bf16_pair(t[0], t[1]), bf16_pair(t[2], t[3])};
-}
-// Weights of four inputs per lane as thirds: middle, high, low.
-struct Weights {
-  v6i w;
-  __device__ __forceinline__ void load(const v2i* t, int h, int m, int l) {
-    const v2i vh = t[h], vm = t[m], vl = t[l];
-    w = v6i{vm[0], vm[1], vh[0], vh[1], vl[0], vl[1]};
-  }
-};
-// acc + x w to float32 accuracy: the products of thirds down to 2^-16 of the largest (middle x low and
-// low x low, below 2^-25, are left out), smallest first
-__device__ __forceinline__ v4f product(const v6i& x, const Weights& w, v4f acc) {
-  const v8b wmh = __builtin_bit_cast(v8b, __builtin_shufflevector(w.w, w.w, 0, 1, 2, 3));
-  const v8b whl = __builtin_bit_cast(v8b, __builtin_shufflevector(w.w, w.w, 2, 3, 4, 5));
-  const v8b lh = __builtin_bit_cast(v8b, __builtin_shufflevector(x, x, 4, 5, 2, 3));
-  const v8b mm = __builtin_bit_cast(v8b, __builtin_shufflevector(x, x, 0, 1, 0, 1));
-  const v8b hh = __builtin_bit_cast(v8b, __builtin_shufflevector(x, x, 2, 3, 2, 3));
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lh, whl, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mm, wmh, acc, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(hh, wmh, acc, 0, 0, 0);
-}
-
-// the same with the weights as rows
-__device__ __forceinline__ v4f product_t(const Weights& w, const v6i& x, v4f acc) {
-  const v8b wmh = __builtin_bit_cast(v8b, __builtin_shufflevector(w.w, w.w, 0, 1, 2, 3));
-  const v8b whl = __builtin_bit_cast(v8b, __builtin_shufflevector(w.w, w.w, 2, 3, 4, 5));
-  const v8b lh = __builtin_bit_cast(v8b, __builtin_shufflevector(x, x, 4, 5, 2, 3));
-  const v8b mm = __builtin_bit_cast(v8b, __builtin_shufflevector(x, x, 0, 1, 0, 1));
-  const v8b hh = __builtin_bit_cast(v8b, __builtin_shufflevector(x, x, 2, 3, 2, 3));
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(whl, lh, acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wmh, mm, acc, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(wmh, hh, acc, 0, 0, 0);
-}
-
-// Granule slot of quad q of run c: 4 c + (q ^ swz(c)), so 8 lanes of consecutive runs reading one
-// quad index, and 16 of them, hit different 16-byte banks.
-__device__ __forceinline__ int swz(int c) { return (((c >> 1) ^ (c >> 3)) & 1) | (((c >> 2) & 1) << 1); }
 
 // IN: the input (Quad). CPLX: the transform's outputs are complex (IN < 3: complex64 out; IN 3: their
 // cotangent comes in). An output component k is formed from stream k of the adjoint's two, or from
@@ -178,7 +49,7 @@ __device__ __forceinline__ int swz(int c) { return (((c >> 1) ^ (c >> 3)) & 1) |
 template <int NS, bool CPLX, int IN, int NST, bool WIDE>
 __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
   constexpr bool REV = IN >= kInRev;
-  constexpr int ST = IN == 3 ? 2 : 1, NC = CPLX ? 2 : 1, MB = NS > 2 ? 2 : 1, SETS = NS > 2 ? 2 : 1;
+  constexpr int ST = IN == 3 ? 2 : 1, NC = CPLX ? 2 : 1, SETS = NS > 2 ? 2 : 1;
   constexpr int G = kGran * NST;        // positions at a time
   constexpr int PS = NST == 1 ? kGran : kGran + 16;   // floats from one run of the columns to the next
   constexpr int LV = NST == 1 ? 0 : NST == 2 ? 1 : 2;  // log2 NST
@@ -226,8 +97,8 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
   const v2i* tq = reinterpret_cast<const v2i*>(tb + lay.quadOff()) + lane;
   Weights T[NC], C[NC][SETS];
   float Y[NC];
-  double Pm[WIDE ? MB : 1][4], ar[NS], ai[NS];   // run sums; a^16
-  Weights Pw[WIDE ? 1 : MB];
+  double ar[NS], ai[NS];   // a^16
+  RunSums<NS, WIDE> run_sums;
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
     T[k].load(tq, lay.bT(k, 0), lay.bT(k, 1), lay.bT(k, 2));
@@ -236,15 +107,7 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
       C[k][e].load(tq, lay.bC(k, e, 0), lay.bC(k, e, 1), lay.bC(k, e, 2));
     }
   }
-#pragma unroll
-  for (int b = 0; b < MB; ++b) {
-    if constexpr (WIDE) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) Pm[b][k] = td[lay.dP(b, k) + lane];
-    } else {
-      Pw[b].load(tq, lay.bP(b, 0), lay.bP(b, 1), lay.bP(b, 2));
-    }
-  }
+  run_sums.load(lay, td, tq, lane);
 #pragma unroll
   for (int s = 0; s < NS; ++s) { ar[s] = td[lay.dSC(0, s, 0) + q]; ai[s] = td[lay.dSC(0, s, 1) + q]; }
   Y[0] = tf[lay.fYre()];
@@ -273,29 +136,7 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
   const int bslot0 = 64 * q + 4 * ((c >> 2) ^ bs) + (c & 3);
   const int bslot1 = 64 * q + 32 + 4 * ((c >> 2) ^ bs ^ 1) + (c & 3);
 
-  // run sums from the lane's operand quad d (WIDE) or its thirds x: Re, Im of state 4 s + q of the lane's
-  // column in slot s
-  using sum_t = typename std::conditional<WIDE, double, float>::type;
-  auto run_sums = [&](const double (&d)[4], const v6i& x, sum_t (&br)[NS], sum_t (&bi)[NS]) {
-#pragma unroll
-    for (int b = 0; b < MB; ++b) {
-      typename std::conditional<WIDE, v4d, v4f>::type acc = {0, 0, 0, 0};
-      if constexpr (WIDE) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Pm[b][k], d[k], acc, 0, 0, 0);
-      } else {
-        acc = product_t(Pw[b], x, acc);
-      }
-      br[2 * b] = acc[0]; bi[2 * b] = acc[1];
-      if (2 * b + 1 < NS) { br[2 * b + 1] = acc[2]; bi[2 * b + 1] = acc[3]; }
-    }
-  };
-  // (xr, xi) <- (cr, ci) (yr, yi) + (xr, xi)
-  auto mac = [](double cr, double ci, double yr, double yi, double& xr, double& xi) {
-    xr = fma(cr, yr, fma(-ci, yi, xr));
-    xi = fma(cr, yi, fma(ci, yr, xi));
-  };
-
+  using sum_t = typename RunSums<NS, WIDE>::sum_t;
   const int64_t js = first + row.jout0;   // position of the piece's first output
   // the states before position js: every lane of row q holds state 4 s + q in slot s
   double zr[ST][NS], zi[ST][NS];

@@ -49,6 +49,7 @@ struct ScanLaunch {
   int32_t gran_pieces, gran_n;
   int gran_two;                 // two granules at a time (pieces of an even number of them)
   const unsigned char* gran_tabs;   // granule constants of scale 0 (stride tab_stride)
+  double* gran_sums;            // not null: the carried scan, gran_pieces pieces of gran_n chunks per row
   // Column scan (granule.h), when col_cols > 0: row0 runs down the columns of a float32 matrix of row0.N
   // rows and col_cols columns, col_piece output rows per wave.
   int64_t col_cols, col_piece;

@@ -317,7 +317,8 @@ hipError_t launch_scan(const ScanLaunch& a, int variant, int mom, hipStream_t s)
     g.row0 = a.row0; g.rows = a.rows; g.nrows = a.nrows; g.segs = a.gran_segs;
     g.nseg = a.gran_nseg; g.pieces = a.gran_pieces; g.seg_n = a.gran_n; g.two = a.gran_two;
     g.tabs = a.gran_tabs; g.tab_stride = a.tab_stride;
-    return launch_granules(g, s);
+    g.sums = a.gran_sums;
+    return a.gran_sums ? launch_carried(g, s) : launch_granules(g, s);
   }
   KernelFn fn = select_kernel(a.K, a.R, variant, a.acc, a.kind, mom, variant == kVarAdjoint ? 0 : a.dtype);
   if (!fn) return hipErrorInvalidValue;

@@ -1,0 +1,157 @@
+"""The carried scan (rows whose window is much longer than a wave's piece, automatic schedule) against the
+float64 oracle and the tiles schedule, where it can go wrong: windows past one and many chunks (2048
+positions), rows that end inside a chunk, one and several chunks per piece, more pieces than one pass of
+the lanes over their sums (128), every slot count, both directions, every input type and view, a
+workspace of exactly the stated size, edge extension, rows of one length, and non-finite inputs."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import morlet_oracle as O
+
+pytestmark = pytest.mark.gpu
+# as for the granule scan: float32 terms exceed the results by less than 100 over these windows
+TOL = 1e-5
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2110_11866_amd  # noqa: F401
+    yield
+
+
+def _rel(a, b):
+    return float(np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-300))
+
+
+def _say(*a):
+    print("[case]", *a, flush=True)
+    sys.stdout.flush()
+
+
+def _plans(kind, N, sigma, K, L, mode, accum="auto"):
+    import paper_2110_11866_amd as M
+    if kind == "morlet":
+        plan = M.MorletPlan(N, sigma, 6 / sigma, K, L, mode=mode, accum=accum)
+        i = plan.info()
+        return plan, O.plan_morlet(sigma, 6 / sigma, K, L, mode=mode, n0=i["n0"] if mode == "asft" else None, P_S=i["P_S"])
+    plan = M.GaussPlan(N, sigma, K, L, mode=mode, accum=accum)
+    return plan, O.plan_gauss(sigma, K, L, mode=mode, n0=plan.info()["n0"] if mode == "asft" else None)
+
+
+@pytest.mark.parametrize("K", [1, 4, 5, 8, 9, 12])
+@pytest.mark.parametrize("N", [16385, 34815, 70001])
+def test_both_directions(N, K):
+    sigma, L = 6000.0, 20000
+    x = np.random.default_rng(N + K).standard_normal(N).astype(np.float32)
+    xt = torch.from_numpy(x).cuda()
+    g = np.random.default_rng(N).standard_normal((N, 2)).astype(np.float32).view(np.complex64)[:, 0]
+    for kind in ("morlet", "gauss"):
+        for mode in ("sft", "asft"):
+            _say("directions", kind, N, K, mode)
+            plan, p = _plans(kind, N, sigma, K, L, mode)
+            gk = g if kind == "morlet" else g.real.copy()
+            got, gx = plan.forward(xt), plan.backward(None, torch.from_numpy(gk).cuda(), want_params=False)[0]
+            assert _rel(got.cpu().numpy(), O.forward(x.astype(np.float64), p)) <= TOL
+            assert _rel(gx.cpu().numpy(), O.adjoint(gk.astype(np.complex128), p)) <= TOL
+            plan.set_schedule("tiles")
+            assert _rel(got.cpu().numpy(), plan.forward(xt).cpu().numpy()) <= 2 * TOL
+
+
+@pytest.mark.parametrize("off", [0, 1, 15, 16, 31])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
+def test_views_and_workspace(off, dtype):
+    N, sigma, K, L = 30001, 6000.0, 5, 20000
+    buf = torch.from_numpy(np.random.default_rng(off).standard_normal(N + 64).astype(np.float32)).cuda().to(dtype)
+    x = buf[off:off + N]
+    for kind in ("morlet", "gauss"):
+        _say("views", off, dtype, kind)
+        plan, p = _plans(kind, N, sigma, K, L, "asft")
+        full = torch.full((N + 64,), 7.0, dtype=torch.complex64 if kind == "morlet" else torch.float32, device="cuda")
+        need = plan.workspace_bytes()
+        room = torch.zeros(need + 4096, dtype=torch.uint8, device="cuda")
+        room[need:] = 201
+        plan.forward(x, out=full[off:off + N], ws=room[:need])
+        torch.cuda.synchronize()
+        got = full.cpu().numpy()
+        assert _rel(got[off:off + N], O.forward(x.double().cpu().numpy(), p)) <= TOL
+        assert (got[:off] == 7).all() and (got[off + N:] == 7).all()
+        assert bool((room[need:] == 201).all())
+
+
+@pytest.mark.parametrize("mode", ["sft", "asft"])
+def test_many_pieces_of_several_chunks(mode):
+    # 517 chunks in pieces of three; the window spans 21 chunks. The float64 scan is the reference.
+    N, sigma, L = (1 << 20) + 17, 8192.0, 21300
+    x = torch.from_numpy(np.random.default_rng(1).standard_normal(N).astype(np.float32)).cuda()
+    g = torch.from_numpy(np.random.default_rng(2).standard_normal((N, 2)).astype(np.float32)).cuda().view(torch.complex64)[:, 0].contiguous()
+    _say("pieces", mode)
+    plan, wide = _plans("morlet", N, sigma, 5, L, mode)[0], _plans("morlet", N, sigma, 5, L, mode, "f64")[0]
+    for _ in range(2):   # the same workspace again, after another launch has used it
+        got, gx = plan.forward(x), plan.backward(None, g, want_params=False)[0]
+        assert _rel(got.cpu().numpy(), wide.forward(x).cpu().numpy()) <= TOL
+        assert _rel(gx.cpu().numpy(), wide.backward(None, g, want_params=False)[0].cpu().numpy()) <= TOL
+        plan.set_schedule("tiles").forward(x)
+        plan.set_schedule("auto")
+
+
+def test_edge_and_rows_of_one_length():
+    import paper_2110_11866_amd as M
+    N, sigma, K, L = 20003, 3000.0, 6, 9001
+    x = np.random.default_rng(5).standard_normal(3 * N).astype(np.float32)
+    xt = torch.from_numpy(x).cuda()
+    for mode in ("sft", "asft"):
+        _say("edge", mode)
+        plan, p = _plans("morlet", N, sigma, K, L, mode)
+        plan.set_boundary("edge")
+        pad = np.concatenate([np.full(2 * L, x[0]), x[:N], np.full(2 * L, x[N - 1])]).astype(np.float64)
+        assert _rel(plan.forward(xt[:N]).cpu().numpy(), O.forward(pad, p)[2 * L:2 * L + N]) <= TOL
+        _say("rows", mode)
+        rows = M.ScalogramPlan([N] * 3, [sigma], [6 / sigma], K, L / sigma, mode=mode)
+        assert rows.scale_info(0)["L"] == L
+        W = rows.forward(xt).cpu().numpy().reshape(3, N)
+        want = np.stack([O.forward(x[N * b:N * (b + 1)].astype(np.float64), p) for b in range(3)])
+        assert _rel(W, want) <= TOL
+        g = torch.from_numpy(W.reshape(-1)).cuda()
+        gx = rows.backward(xt, g)[0].cpu().numpy().reshape(3, N)
+        assert _rel(gx, np.stack([O.adjoint(W[b].astype(np.complex128), p) for b in range(3)])) <= TOL
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_non_finite_input_reaches_no_earlier_output(bad):
+    N, sigma, K, L = 40000, 3000.0, 5, 9001
+    x = np.random.default_rng(8).standard_normal(N).astype(np.float32)
+    for kind in ("morlet", "gauss"):
+        plan, _ = _plans(kind, N, sigma, K, L, "asft")
+        clean = plan.forward(torch.from_numpy(x).cuda()).cpu().numpy()
+        for at in (12000, 20479, 20480, 33333):
+            _say("non-finite", bad, kind, at)
+            y = x.copy()
+            y[at] = bad
+            got = plan.forward(torch.from_numpy(y).cuda()).cpu().numpy()
+            first = at + plan.info()["n0"] - L
+            assert np.isfinite(got[:first]).all()
+            assert _rel(got[:first], clean[:first]) <= TOL
+            assert not np.isfinite(got[first:first + 2 * L + 1]).any()
+
+
+def test_graph_replays():
+    N, sigma, K, L = 40000, 3000.0, 5, 9001
+    plan, p = _plans("morlet", N, sigma, K, L, "asft")
+    x = torch.randn(N, device="cuda")
+    out, ws = torch.empty(N, dtype=torch.complex64, device="cuda"), plan.workspace("cuda")
+    plan.forward(x, out=out, ws=ws)
+    torch.cuda.synchronize()
+    _say("graph")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        plan.forward(x, out=out, ws=ws)
+    for i in range(3):
+        x.copy_(torch.from_numpy(np.random.default_rng(i).standard_normal(N).astype(np.float32)))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, plan.forward(x))

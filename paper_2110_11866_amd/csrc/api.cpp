@@ -628,8 +628,10 @@ morlet_status run_columns(morlet_plan_t axis, int variant, const void* in, void*
 }
 
 // Workspace bytes a forward launch reads and writes: the header; the tiles schedule adds a tile
-// state per tile, the segments schedule a float64 state vector per segment.
+// state per tile, the segments schedule a float64 state vector per segment, the carried scan one per
+// piece but the last of each row. The granule scan uses none.
 size_t launch_ws_bytes(const mk::ScanLaunch& a, int K, int64_t ntiles) {
+  if (a.gran_sums) return sizeof(mk::WsHeader) + (size_t)(a.gran_nseg - a.nrows) * 2 * (size_t)K * sizeof(double);
   if (a.gran_nseg > 0) return 0;
   if (a.nseg > 0) return sizeof(mk::WsHeader) + (size_t)a.nseg * 2 * (size_t)K * sizeof(double);
   return a.serial ? sizeof(mk::WsHeader) : mk::workspace_bytes(K, ntiles);
@@ -2232,7 +2234,8 @@ morlet_status morlet_forward_noalloc(morlet_plan_t plan, const void* x, morlet_d
   hipStream_t s = static_cast<hipStream_t>(stream);
   // every call clears what the launch reads as its start state (header and tile flags): the
   // array keeps the previous call's contents, which may come from a plan of another shape
-  hipError_t e = mk::launch_zero_fill(ws, need, s);
+  // (the granule and carried scans read nothing that they have not written)
+  hipError_t e = a.gran_nseg > 0 ? hipSuccess : mk::launch_zero_fill(ws, need, s);
   if (e == hipSuccess) e = mk::launch_scan(a, mk::kVarForward, 0, s);
   if (e != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(e));
   return MORLET_OK;

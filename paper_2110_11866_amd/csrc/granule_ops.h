@@ -19,8 +19,6 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v6i __attribute__((ext_vector_type(6)));
 typedef __bf16 v2b __attribute__((ext_vector_type(2)));
 typedef __bf16 v8b __attribute__((ext_vector_type(8)));
-typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));            // any sample alignment
-typedef unsigned short v4h_any __attribute__((ext_vector_type(4), aligned(2)));
 
 template <int SH, typename T>
 __device__ __forceinline__ T row_shr(T v) {   // lane c of each 16-lane row reads lane c - SH, else 0

@@ -25,8 +25,6 @@ constexpr int kMmThreads = 256;
 // an odd length are not aligned) and one sincos: the phases of the other three are float64 rotations
 // by constants. With a sincos and 4-byte accesses per sample the kernels were bound by its 100 float64
 // instructions (N = 2^22: demodulation 16 us, remodulation 24; now 11.5 and 16.6, 5.8 and 5.0 TB/s).
-typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
-
 struct Turns {   // e^{i xi k}, k = 1, 2, 3
   double c[3], s[3];
 };

@@ -49,7 +49,8 @@ __global__ void zero_fill_kernel(uint4* p, size_t n16, unsigned char* tail, size
 //   dL/dm_p = sgn_p (e^{aL} S1_p + e^{-aL} Sx),  dL/dl_p = sgn_p e^{aL} S2_p   (chain rule
 //   through the fitted coefficients, Jacobian rows from the plan), plus for ASFT the output
 //   scale (n0^2/sigma^3 Re Q), the carrier phase (-n0 Im Q) and the decay
-//   dL/dalpha = sum_p sgn_p [m_p (e^{aL} (L S1_p + S3_p) - L e^{-aL} Sx) + l_p e^{aL} (L S2_p + S4_p)],
+//   dL/dalpha = S_w + L sum_p sgn_p [m_p (e^{aL} S1_p - e^{-aL} Sx) + l_p e^{aL} S2_p],
+//   Re Q = cx Sx + sum_p sgn_p e^{aL} (m_p S1_p + l_p S2_p),
 //   dalpha/dsigma = -2 n0 / sigma^3.
 // Per-row sums of the tile partials (block r = row r): a row's tiles are consecutive, so its
 // partials are one contiguous [ntiles][NRED] block; thread (g, q) = (tid / NRED, tid % NRED)
@@ -57,7 +58,7 @@ __global__ void zero_fill_kernel(uint4* p, size_t n16, unsigned char* tail, size
 // group sums are added in order.
 __global__ __launch_bounds__(256) void pg_rows_kernel(ScanLaunch P, int K, double* rowpart) {
   const int r = blockIdx.x, tid = threadIdx.x;
-  const int NRED = 4 * K + 3, G = 256 / NRED, g = tid / NRED, q = tid % NRED;
+  const int NRED = 2 * K + 3, G = 256 / NRED, g = tid / NRED, q = tid % NRED;
   __shared__ double red[256];
   const Row row = P.nrows == 1 ? P.row0 : P.rows[r];
   double acc = 0.0;
@@ -75,8 +76,8 @@ __global__ __launch_bounds__(256) void pg_rows_kernel(ScanLaunch P, int K, doubl
 __global__ __launch_bounds__(256) void pg_finalize_kernel(ScanLaunch P, int K, const double* rowpart,
                                                           double* gparams) {
   const int s = blockIdx.x, tid = threadIdx.x;
-  const int NRED = 4 * K + 3;
-  __shared__ double tot[4 * kMaxTerms + 3];
+  const int NRED = 2 * K + 3;
+  __shared__ double tot[2 * kMaxTerms + 3];
   // the scale's rows: b S + s for every signal b of a batched launch (rows are signal-major,
   // one block per scale), or the only row; summed in signal order
   const int S = gridDim.x;
@@ -92,17 +93,18 @@ __global__ __launch_bounds__(256) void pg_finalize_kernel(ScanLaunch P, int K, c
     const double* td = reinterpret_cast<const double*>(P.tabs + (int64_t)s * P.tab_stride + P.f32_bytes);
     const double up = td[lay.sUP()], dn = td[lay.sDN()], LL = td[lay.sLL()];
     const double* S = tot;
-    const double Sx = S[4 * K], Qr = S[4 * K + 1], Qi = S[4 * K + 2];
-    double ds = td[lay.sDSIG()] * Qr, dx = -td[lay.sDXI()] * Qi, dal = 0.0;
+    const double Sx = S[2 * K], Qi = S[2 * K + 1];
+    double Qr = td[lay.sCX()] * Sx, dx = -td[lay.sDXI()] * Qi, ds = 0.0, dal = S[2 * K + 2];
     for (int t = 0; t < K; ++t) {
       const double sg = td[lay.rSGN() * K + t];
       const double gm = sg * (up * S[t] + dn * Sx), gl = sg * up * S[K + t];
       ds += td[lay.rJ(0) * K + t] * gm + td[lay.rJ(2) * K + t] * gl;
       dx += td[lay.rJ(1) * K + t] * gm + td[lay.rJ(3) * K + t] * gl;
       const double cc = td[lay.rCC() * K + t], sc = td[lay.rSC() * K + t];
-      dal += sg * (cc * (up * (LL * S[t] + S[2 * K + t]) - LL * dn * Sx) + sc * up * (LL * S[K + t] + S[3 * K + t]));
+      dal += sg * LL * (cc * (up * S[t] - dn * Sx) + sc * up * S[K + t]);
+      Qr += td[lay.rMW() * K + t] * S[t] + td[lay.rLW() * K + t] * S[K + t];
     }
-    ds += td[lay.sDALPHA()] * dal;
+    ds += td[lay.sDSIG()] * Qr + td[lay.sDALPHA()] * dal;
     gparams[2 * s] = ds;
     gparams[2 * s + 1] = dx;
   }

@@ -25,7 +25,7 @@
 //          reversed. So the adjoint is again a causal, decaying scan.
 //   kPg  : forward scan of x whose per-position components are reduced against g instead
 //          of stored: per tile, sum_n Re u Re v_p, sum_n Im u Im v_p, sum_n Re u y[j-2L]
-//          and sum_n u (A - iB) with u = conj(g) G; with MOM (ASFT) it also carries
+//          and Im sum_n u (A - iB) with u = conj(g) G; with MOM (ASFT) it also carries
 //          w_p = d v_p / d alpha (w = a w - a v + 2L a^{2L} y[j-2L]) for the sigma gradient.
 //
 // How (one block = one tile of T = 256 R scan positions, persistent grid, ticketed tiles):
@@ -58,13 +58,6 @@ namespace mk {
 namespace {
 
 enum { kFwd = 0, kAdj = 1, kPg = 2, kSegSum = 3 };
-
-// The matrix-core evaluation of the per-thread run (below) computes the same outputs as the
-// vector-ALU recurrence with a third fewer vector instructions, but on the ragged scalogram it
-// measured 1.70 ms per launch against 1.58 ms: the kernel is bound by the latency of its per-tile
-// dependency chain, not by vector issue, and the run's operand loads lengthen that chain. Off
-// until the chain is shortened.
-constexpr bool kMatrixRun = false;
 
 // four floats as a clang vector (what the nontemporal-store builtin takes); outputs are
 // written once and never re-read by the kernel, so they bypass the cache hierarchy's reuse
@@ -127,7 +120,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
   static_assert(!(SINE || MIXED) || VAR == kFwd, "sine-component output only in the forward scan");
   constexpr int NS = (VAR == kAdj && !GAUSS) ? 2 : 1;   // real input streams
   constexpr int KS = (NS == 2 || MOM) ? 2 * K : K;      // complex states per position
-  constexpr int NRED = 4 * K + 3;                        // kPg partial sums per tile
+  constexpr int NRED = 2 * K + 3;                        // kPg partial sums per tile
   static_assert(!(MOM && VAR != kPg), "moment states only in the gradient pass");
 
   __shared__ uint32_t s_tile;
@@ -156,15 +149,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
   constexpr int kSub = R < 16 ? R : 16;                     // positions per thread per store round
   static_assert(R % kSub == 0, "R must be a multiple of the store sub-run");
   constexpr int kStride = (kStash ? 2 * NS * R : kSub * (kCplxOut ? 2 : 1)) + 4;   // floats per thread
-  // Morlet forward, R = 16, float32 recurrence: each thread's run of 16 positions is evaluated as
-  // one linear map on the matrix cores (v_mfma_f32_16x16x4_f32), outputs = Tc dy + Cc S + Y y
-  // per component (the run matrices of the table's fourth section), instead of 16 steps of the
-  // K-term recurrence and combination on the vector ALUs. The stash then holds the run's input
-  // differences dy (16 floats) and the thread's state S before the run (2K floats, zero-padded
-  // to a multiple of 4); y[j - 2L] is read again from the input (a cache hit).
-  constexpr int NKB_C = (2 * K + 3) / 4;   // k-blocks of four state components
-  constexpr bool MFMA = kMatrixRun && VAR == kFwd && KIND == 0 && R == 16 && (F32T || ACC == kAccMixed) && NS == 1 &&
-                        16 + 4 * NKB_C <= kStride;
   __shared__ __align__(16) float s_out[kWaves][(VAR == kPg && !kStash) ? 4 : 64 * kStride];
 
   WsHeader* hdr = static_cast<WsHeader*>(P.ws);
@@ -309,21 +293,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
     // Positions past jend in a wave that also holds earlier positions are scanned like the
     // others: they produce no output and their state is never carried further, so their inputs
     // need no masking (in the gradient pass the cotangent is zero there).
-    bool fast_in = (j0 - 2 * row.L >= 0) && (j0 + R <= row.N);
-    {
-      if constexpr (VAR == kAdj) {
-        const char* g = static_cast<const char*>(P.x) + row.w_off * (GAUSS ? 4 : 8);
-        const int64_t e = GAUSS ? 4 : 8;
-        fast_in = fast_in && ((reinterpret_cast<uintptr_t>(g + (row.N - j0 - R) * e) & 15) == 0) &&
-                  ((reinterpret_cast<uintptr_t>(g + (row.N - j0 + 2 * row.L - R) * e) & 15) == 0);
-      } else {
-        const char* xs = static_cast<const char*>(P.x) + row.x_off * (DT == 0 ? 4 : 2);
-        const uintptr_t m = DT == 0 ? 15 : 7;
-        const int64_t e = DT == 0 ? 4 : 2;
-        fast_in = fast_in && ((reinterpret_cast<uintptr_t>(xs + j0 * e) & m) == 0) &&
-                  ((reinterpret_cast<uintptr_t>(xs + (j0 - 2 * row.L) * e) & m) == 0);
-      }
-    }
+    const bool fast_in = (j0 - 2 * row.L >= 0) && (j0 + R <= row.N);
     const acc_t Dw = tab.scalar(lay.sD());
 
     // 2. chunk sums: the recurrence run from a zero state over the thread's R positions,
@@ -334,7 +304,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
     //    float64 FMA issues at the rate of an unpacked float32 FMA; the float32 mode saves the
     //    conversions and half the DPP moves of the wave scan.
     //    State i = s K + t: stream s, term t; with MOM, state K + t is the alpha-derivative of
-    //    state t: w <- a (w - v) + ddy, ddy = d dy / d alpha = 2L a^{2L} y[j-2L].
+    //    state t: w <- a (w - v) + ddy, ddy = d dy / d alpha = 2L a^{2L} y[j-2L], summed as w + r v
+    //    with r the position in the chunk, whose input is r dy + ddy.
     sc_t br[KS], bi[KS];
 #pragma unroll
     for (int i = 0; i < KS; ++i) { br[i] = 0; bi[i] = 0; }
@@ -344,6 +315,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const sc_t ddy = MOM ? (sc_t)(2 * row.L) * Dd * (sc_t)yb[0][r] : (sc_t)0;
+          const sc_t pos = (sc_t)(4 * q + r);
 #pragma unroll
           for (int s = 0; s < NS; ++s) {
             const sc_t dyd = (sc_t)ya[s][r] - Dd * (sc_t)yb[s][r];
@@ -354,9 +326,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
               const sc_t pr = br[i], pi = bi[i];
               br[i] = fma(ar, pr, fma(-ai, pi, dyd));
               bi[i] = fma(ar, pi, ai * pr);
-              if (MOM && s == 0) {
-                const sc_t wr = br[K + t] - pr, wi = bi[K + t] - pi;
-                br[K + t] = fma(ar, wr, fma(-ai, wi, ddy));
+              if (MOM && s == 0) {   // w + r v, r from the chunk's start
+                const sc_t wr = br[K + t], wi = bi[K + t];
+                br[K + t] = fma(ar, wr, fma(-ai, wi, fma(pos, dyd, ddy)));
                 bi[K + t] = fma(ar, wi, ai * wr);
               }
             }
@@ -365,12 +337,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
       };
       float* stash = &s_out[wid][0] + lane * kStride;
       auto keep = [&](int q, const float (&ya)[NS][4], const float (&yb)[NS][4]) {
-        if constexpr (MFMA) {
-          float d[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) d[r] = (float)((sc_t)ya[0][r] - Dd * (sc_t)yb[0][r]);
-          *reinterpret_cast<float4*>(stash + 4 * q) = make_float4(d[0], d[1], d[2], d[3]);
-        } else if constexpr (kStash && NS == 1) {
+        if constexpr (kStash && NS == 1) {
           *reinterpret_cast<float4*>(stash + 8 * q) = make_float4(ya[0][0], yb[0][0], ya[0][1], yb[0][1]);
           *reinterpret_cast<float4*>(stash + 8 * q + 4) = make_float4(ya[0][2], yb[0][2], ya[0][3], yb[0][3]);
         } else if constexpr (kStash) {
@@ -381,30 +348,26 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
       };
       if (wave_dead) {
         // nothing to load or sum
-      } else if (fast_in && NS == 1 && !MOM) {
+      } else if (fast_in && NS == 1 && (!MOM || kStash)) {
         // every position of the run is in range: form all R differences first, then per term
-        // a Horner pass four positions at a time, B <- a^4 B + (a^3 dy_0 + a^2 dy_1 + a dy_2 + dy_3)
+        // a Horner pass four positions at a time, B <- a^4 B + (a^3 dy_0 + a^2 dy_1 + a dy_2 + dy_3),
+        // and with MOM the same of r dy_r + ddy_r
         sc_t dyd[R];
 #pragma unroll
         for (int q = 0; q < R / 4; ++q) {
           float ya[NS][4], yb[NS][4];
           load_quad_fast(j0 + 4 * q, ya, yb);
-          if constexpr (!MFMA) keep(q, ya, yb);
+          keep(q, ya, yb);
 #pragma unroll
           for (int r = 0; r < 4; ++r) dyd[4 * q + r] = (sc_t)ya[0][r] - Dd * (sc_t)yb[0][r];
-          if constexpr (MFMA)
-            *reinterpret_cast<float4*>(stash + 4 * q) = make_float4((float)dyd[4 * q], (float)dyd[4 * q + 1],
-                                                                    (float)dyd[4 * q + 2], (float)dyd[4 * q + 3]);
         }
-#pragma unroll
-        for (int t = 0; t < K; ++t) {
+        auto horner = [&](int t, sc_t& Br, sc_t& Bi) {
           // the term's own contiguous block (one scalar load): a^1 .. a^4
           const int hc = lay.vHC(t);
           const sc_t a1r = tabs.scalar(hc), a1i = tabs.scalar(hc + 1);
           const sc_t a2r = tabs.scalar(hc + 2), a2i = tabs.scalar(hc + 3);
           const sc_t a3r = tabs.scalar(hc + 4), a3i = tabs.scalar(hc + 5);
           const sc_t a4r = tabs.scalar(hc + 6), a4i = tabs.scalar(hc + 7);
-          sc_t Br = 0, Bi = 0;
 #pragma unroll
           for (int q = 0; q < R / 4; ++q) {
             const sc_t d0 = dyd[4 * q], d1 = dyd[4 * q + 1], d2 = dyd[4 * q + 2], d3 = dyd[4 * q + 3];
@@ -419,9 +382,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
               Br = nr;
             }
           }
-          br[t] = Br;
-          bi[t] = Bi;
           __builtin_amdgcn_sched_barrier(0);   // one term's constants live at a time (SGPR budget)
+        };
+#pragma unroll
+        for (int t = 0; t < K; ++t) horner(t, br[t], bi[t]);
+        if constexpr (MOM) {
+#pragma unroll
+          for (int q = 0; q < R / 4; ++q) {   // y[j - 2L] back from the stash
+            const float4 v0 = *reinterpret_cast<const float4*>(stash + 8 * q), v1 = *reinterpret_cast<const float4*>(stash + 8 * q + 4);
+            const float yb[4] = {v0.y, v0.w, v1.y, v1.w};
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              dyd[4 * q + r] = fma((sc_t)(4 * q + r), dyd[4 * q + r], (sc_t)(2 * row.L) * Dd * (sc_t)yb[r]);
+          }
+#pragma unroll
+          for (int t = 0; t < K; ++t) horner(t, br[K + t], bi[K + t]);
         }
       } else if (fast_in) {
 #pragma unroll
@@ -438,6 +413,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
           load_quad(j0 + 4 * q, ya, yb);
           keep(q, ya, yb);
           step1(q, ya, yb);
+        }
+      }
+      if constexpr (MOM) {
+#pragma unroll
+        for (int t = 0; t < K; ++t) {   // w at the chunk's last position
+          br[K + t] = fma(-(sc_t)(R - 1), br[t], br[K + t]);
+          bi[K + t] = fma(-(sc_t)(R - 1), bi[t], bi[K + t]);
         }
       }
     }
@@ -835,14 +817,57 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
 
       if constexpr (VAR == kPg) {
         // reductions against the cotangent at the output positions n = j - jout0:
-        // S1_t = sum Re u Re v_t, S2_t = sum Im u Im v_t (S3, S4 the same for the alpha
-        // derivative states), Sx = sum Re u y[j-2L], Q = sum u (A - iB), u = conj(g) G
-        acc_t sv_re[K], sv_im[K], sw_re[K], sw_im[K], s_xb = 0, q_re = 0, q_im = 0;
+        // S1_t = sum Re u Re v_t, S2_t = sum Im u Im v_t, Sx = sum Re u y[j-2L], Im Q, Q = sum u
+        // (A - iB), u = conj(g) G (Re Q follows from the others), and with MOM the alpha-derivative
+        // states' S_w = sum_t (m_t sum Re u Re w_t + l_t sum Im u Im w_t), m_t and l_t the weights of
+        // A and B. The states w are carried as w + r v, r the position in the chunk: their
+        // recurrence is then that of v with r dy + ddy as input, and r times what A and B hold is
+        // taken off the weighted sums (float64 operations per position at K = 5: 125, with w itself and the
+        // sums of each term apart 163; 442 us at 64 x 32768 x 16 scales,
+        // with the inputs loaded whole at any alignment and the cotangent a quad ahead 388; plain SFT 332 and 247).
+        acc_t sv_re[K], sv_im[K], s_w = 0, s_xb = 0, q_im = 0;
 #pragma unroll
-        for (int t = 0; t < K; ++t) { sv_re[t] = 0; sv_im[t] = 0; sw_re[t] = 0; sw_im[t] = 0; }
+        for (int t = 0; t < K; ++t) { sv_re[t] = 0; sv_im[t] = 0; }
+        if constexpr (MOM) {   // w + r v, r from the chunk's start, before its first position
+#pragma unroll
+          for (int t = 0; t < K; ++t) { vr[K + t] -= vr[t]; vi[K + t] -= vi[t]; }
+        }
+        // One branch for the wave and clamped addresses at the row's ends: lanes that branch apart here,
+        // where the state fills the registers, let the compiler move live values aside under part of the
+        // lanes (seen in the assembly of the K = 12, R = 8 Gaussian pass: a stale address, a fault).
+        auto load_g = [&](int q, float (&gr)[4], float (&gi)[4]) {
+          const int64_t n = nb + 4 * q;
+          if (__all(n >= 0 && n + 4 <= row.N)) {
+            if constexpr (GAUSS) {
+              const v4f_any a = *reinterpret_cast<const v4f_any*>(static_cast<const float*>(P.g) + row.w_off + n);
+#pragma unroll
+              for (int r = 0; r < 4; ++r) { gr[r] = a[r]; gi[r] = 0.f; }
+            } else {
+              const float* p = reinterpret_cast<const float*>(static_cast<const float2*>(P.g) + row.w_off + n);
+              const v4f_any a = *reinterpret_cast<const v4f_any*>(p), b = *reinterpret_cast<const v4f_any*>(p + 4);
+#pragma unroll
+              for (int r = 0; r < 4; ++r) { gr[r] = r < 2 ? a[2 * r] : b[2 * r - 4]; gi[r] = r < 2 ? a[2 * r + 1] : b[2 * r - 3]; }
+            }
+          } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int64_t m = n + r, c = m < 0 ? 0 : m < row.N ? m : row.N - 1;
+              float2 z = make_float2(0.f, 0.f);
+              if constexpr (GAUSS) z.x = static_cast<const float*>(P.g)[row.w_off + c];
+              else z = (static_cast<const float2*>(P.g) + row.w_off)[c];
+              gr[r] = m == c ? z.x : 0.f;
+              gi[r] = m == c ? z.y : 0.f;
+            }
+          }
+        };
+        float fr[4] = {0, 0, 0, 0}, fi[4] = {0, 0, 0, 0};   // the next four, in flight during these
+        if (!wave_dead) load_g(0, fr, fi);
 #pragma unroll 1
         for (int q = 0; q < (wave_dead ? 0 : R / 4); ++q) {
           float ya[NS][4], yb[NS][4], gr[4], gi[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) { gr[r] = fr[r]; gi[r] = fi[r]; }
+          if (q + 1 < R / 4) load_g(q + 1, fr, fi);
           if constexpr (kStash) {
             const float* stg = &s_out[wid][0] + lane * kStride;
             const float4 v0 = *reinterpret_cast<const float4*>(stg + 8 * q);
@@ -852,21 +877,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
           } else {
             load_quad(j0 + 4 * q, ya, yb);
           }
-          if constexpr (GAUSS) {
-            load4_f32(static_cast<const float*>(P.g) + row.w_off, nb + 4 * q, row.N, gr);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) gi[r] = 0.f;
-          } else {
-            load4_c(static_cast<const float2*>(P.g) + row.w_off, nb + 4 * q, row.N, gr, gi);
-          }
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const acc_t dyr = (acc_t)ya[0][r] - Dw * (acc_t)yb[0][r];
             const acc_t ybr = (acc_t)yb[0][r];
             const acc_t ur = (acc_t)gr[r] * gre + (acc_t)gi[r] * gim;
             const acc_t ui = (acc_t)gr[r] * gim - (acc_t)gi[r] * gre;
-            const acc_t ddy = MOM ? (acc_t)(2 * row.L) * Dw * ybr : (acc_t)0;
-            acc_t A = cx * ybr, B = 0;
+            const acc_t pos = (acc_t)(4 * q + r);
+            const acc_t dwy = MOM ? fma(pos, dyr, (acc_t)(2 * row.L) * Dw * ybr) : (acc_t)0;
+            acc_t A = 0, B = 0, Aw = 0, Bw = 0;
 #pragma unroll
             for (int t = 0; t < K; ++t) {
               const acc_t ar = tab.re(lay.eA(), t), ai = tab.im(lay.eA(), t);
@@ -875,31 +894,28 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
               const acc_t ni = fma(ar, pi, ai * pr);
               vr[t] = nr;
               vi[t] = ni;
-              if constexpr (MOM) {   // w = a (w - v_prev) + ddy
-                const acc_t wr = vr[K + t] - pr, wi = vi[K + t] - pi;
-                vr[K + t] = fma(ar, wr, fma(-ai, wi, ddy));
+              if constexpr (MOM) {
+                const acc_t wr = vr[K + t], wi = vi[K + t];
+                vr[K + t] = fma(ar, wr, fma(-ai, wi, dwy));
                 vi[K + t] = fma(ar, wi, ai * wr);
-                sw_re[t] = fma(ur, vr[K + t], sw_re[t]);
-                sw_im[t] = fma(ui, vi[K + t], sw_im[t]);
+                Aw = fma(tab.row(lay.rMW(), t), vr[K + t], Aw);
+                if (!GAUSS) Bw = fma(tab.row(lay.rLW(), t), vi[K + t], Bw);
               }
               sv_re[t] = fma(ur, nr, sv_re[t]);
               sv_im[t] = fma(ui, ni, sv_im[t]);
               A = fma(tab.row(lay.rMW(), t), nr, A);
               if (!GAUSS) B = fma(tab.row(lay.rLW(), t), ni, B);
             }
+            if constexpr (MOM) s_w = fma(ur, fma(-pos, A, Aw), fma(ui, fma(-pos, B, Bw), s_w));
             s_xb = fma(ur, ybr, s_xb);
-            q_re = fma(ur, A, fma(ui, B, q_re));
-            q_im = fma(ui, A, fma(-ur, B, q_im));
+            q_im = fma(ui, fma(cx, ybr, A), fma(-ur, B, q_im));
           }
         }
-        // block reduction of the 4K + 3 partial sums in float64, fixed order
+        // block reduction of the 2K + 3 partial sums in float64, fixed order
         double red[NRED];
 #pragma unroll
-        for (int t = 0; t < K; ++t) {
-          red[t] = (double)sv_re[t]; red[K + t] = (double)sv_im[t];
-          red[2 * K + t] = (double)sw_re[t]; red[3 * K + t] = (double)sw_im[t];
-        }
-        red[4 * K] = (double)s_xb; red[4 * K + 1] = (double)q_re; red[4 * K + 2] = (double)q_im;
+        for (int t = 0; t < K; ++t) { red[t] = (double)sv_re[t]; red[K + t] = (double)sv_im[t]; }
+        red[2 * K] = (double)s_xb; red[2 * K + 1] = (double)q_im; red[2 * K + 2] = (double)s_w;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1)
 #pragma unroll
@@ -913,97 +929,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
           for (int w = 0; w < kWaves; ++w) sacc += s_red[w * NRED + tid];
           P.partials[(size_t)tile * NRED + tid] = sacc;
-        }
-      } else if constexpr (MFMA) {
-        // The run of thread c (positions j0(c) + r, r < 16) as a 16 x 16 x 4 product per group of
-        // 16 threads: D[r][c'] = sum_k A[r][k] B[k][c'] with c = 16 g + c'. Lane l supplies
-        // A[l % 16][l / 16] and B[l / 16][l % 16] of each k-block and receives D[4 (l / 16) + v][l % 16],
-        // v < 4. The k-blocks' K index is permuted so that lane l supplies, for the Toeplitz part,
-        // the input differences dy[4 (l / 16) + kb] of its chunk (kb = 0..3: one 16-byte LDS read)
-        // and, for the state part, components NKB_C (l / 16) + kb; its results are the outputs
-        // r = 4 (l / 16) + v of chunk c, i.e. four consecutive positions.
-        if (!wave_dead) {
-          float* slot = &s_out[wid][0] + lane * kStride;
-          {
-            float st[4 * NKB_C];
-#pragma unroll
-            for (int k = 0; k < 4 * NKB_C; ++k) st[k] = k < 2 * K ? (float)((k & 1) ? vi[k >> 1] : vr[k >> 1]) : 0.0f;
-#pragma unroll
-            for (int k = 0; k < NKB_C; ++k)
-              *reinterpret_cast<float4*>(slot + 16 + 4 * k) = make_float4(st[4 * k], st[4 * k + 1], st[4 * k + 2], st[4 * k + 3]);
-          }
-          // the lane's operands from memory: its run-matrix entries and y[j - 2L] of the four
-          // chunks it computes (one request each, all in flight together)
-          const int i16 = lane & 15, q = lane >> 4;
-          const float* tm = reinterpret_cast<const float*>(tb + lay.mfmaOff());
-          const float4 m_tre = *reinterpret_cast<const float4*>(tm + lay.mTre() + 16 * i16 + 4 * q);
-          const float4 m_tim = *reinterpret_cast<const float4*>(tm + lay.mTim() + 16 * i16 + 4 * q);
-          float m_cre[NKB_C], m_cim[NKB_C], m_y[4][4];
-#pragma unroll
-          for (int kb = 0; kb < NKB_C; ++kb) {
-            m_cre[kb] = tm[lay.mCre() + lay.mCW() * i16 + NKB_C * q + kb];
-            m_cim[kb] = tm[lay.mCim() + lay.mCW() * i16 + NKB_C * q + kb];
-          }
-          {
-            const void* xs = static_cast<const char*>(P.x) + row.x_off * (DT == 0 ? 4 : 2);
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-              load4(xs, DT, jt + (int64_t)(wid * 64 + 16 * g + i16) * R + 4 * q - 2 * row.L, row.N, m_y[g]);
-          }
-          wave_lds_sync();
-          const float yre = (float)(gre * cx), yim = (float)(gim * cx);
-          // two groups at a time: four independent accumulation chains keep the matrix core busy
-#pragma unroll
-          for (int gp = 0; gp < 4; gp += 2) {
-            float* sl[2];
-            float4 d4[2];
-            float sc[2][NKB_C];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              sl[h] = &s_out[wid][0] + (16 * (gp + h) + i16) * kStride;
-              d4[h] = *reinterpret_cast<const float4*>(sl[h] + 4 * q);
-#pragma unroll
-              for (int kb = 0; kb < NKB_C; ++kb) sc[h][kb] = sl[h][16 + NKB_C * q + kb];
-            }
-            v4f dre[2], dim[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              dre[h] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-              dim[h] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-            }
-            const float tr[4] = {m_tre.x, m_tre.y, m_tre.z, m_tre.w}, ti[4] = {m_tim.x, m_tim.y, m_tim.z, m_tim.w};
-#pragma unroll
-            for (int kb = 0; kb < 4; ++kb) {
-              const float dv[2] = {kb == 0 ? d4[0].x : kb == 1 ? d4[0].y : kb == 2 ? d4[0].z : d4[0].w,
-                                   kb == 0 ? d4[1].x : kb == 1 ? d4[1].y : kb == 2 ? d4[1].z : d4[1].w};
-#pragma unroll
-              for (int h = 0; h < 2; ++h) {
-                dre[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(tr[kb], dv[h], dre[h], 0, 0, 0);
-                dim[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(ti[kb], dv[h], dim[h], 0, 0, 0);
-              }
-            }
-#pragma unroll
-            for (int kb = 0; kb < NKB_C; ++kb) {
-#pragma unroll
-              for (int h = 0; h < 2; ++h) {
-                dre[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(m_cre[kb], sc[h][kb], dre[h], 0, 0, 0);
-                dim[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(m_cim[kb], sc[h][kb], dim[h], 0, 0, 0);
-              }
-            }
-            // outputs r = 4 q + v of each chunk go to floats 2 r, 2 r + 1 of its slot (read above by
-            // this group only, before these writes)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const float* y = m_y[gp + h];
-              *reinterpret_cast<float4*>(sl[h] + 8 * q) =
-                  make_float4(fmaf(yre, y[0], dre[h][0]), fmaf(yim, y[0], dim[h][0]), fmaf(yre, y[1], dre[h][1]),
-                              fmaf(yim, y[1], dim[h][1]));
-              *reinterpret_cast<float4*>(sl[h] + 8 * q + 4) =
-                  make_float4(fmaf(yre, y[2], dre[h][2]), fmaf(yim, y[2], dim[h][2]), fmaf(yre, y[3], dre[h][3]),
-                              fmaf(yim, y[3], dim[h][3]));
-            }
-          }
-          flush(0);
         }
       } else {
         // outputs n = j - jout0, in sub-runs of kSub positions per thread: each thread writes
@@ -1161,10 +1086,7 @@ __global__ __launch_bounds__(kThreads) void seg_sum_kernel(ScanLaunch P) {
   for (int64_t ti = t0; ti < t1; ++ti) {
     const int64_t j0 = ti * T + (int64_t)tid * R;
     double dy[R];
-    const bool fast = (j0 - 2 * row.L >= 0) && (j0 + R <= row.N) &&
-                      ((reinterpret_cast<uintptr_t>(static_cast<const char*>(xs) + (j0 - 2 * row.L) * (DT == 0 ? 4 : 2)) |
-                        reinterpret_cast<uintptr_t>(static_cast<const char*>(xs) + j0 * (DT == 0 ? 4 : 2))) &
-                       (DT == 0 ? 15 : 7)) == 0;
+    const bool fast = (j0 - 2 * row.L >= 0) && (j0 + R <= row.N);
 #pragma unroll
     for (int q = 0; q < R / 4; ++q) {
       float ya[4], yb[4];

@@ -60,9 +60,9 @@ def _parse():
     return ap.parse_args()
 
 
-# the sources that make the scan kernel and its dispatch: counters taken on it stay valid while
-# these are unchanged
-SCAN_SOURCES = ("layout.h", "launch.h", "scan_common.h", "scan_dispatch.hip", "scan_inst.hip", "scan_kernel.h")
+# the sources that make the granule scan (the kernel of the default workload) and its dispatch: counters
+# taken on it stay valid while these are unchanged
+SCAN_SOURCES = ("granule.h", "granule_ops.h", "granule_scan.hip", "launch.h", "layout.h", "scan_common.h", "scan_dispatch.hip")
 
 
 def _csrc_sha256() -> str:

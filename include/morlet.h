@@ -79,8 +79,9 @@ typedef enum { MORLET_SCAN_SFT = 0, MORLET_SCAN_ASFT = 1 } morlet_scan;
  *   MORLET_ACC_F32 : float32 for everything a thread computes - the chunk sums of its positions,
  *                    the 16-lane wave scan, the recurrence and the K-term combination; float64
  *                    only for the carries between the 16-lane rows of a wave, between waves and
- *                    between tiles (the decoupled look-back). Backward calls run the mixed scan
- *                    in this mode.
+ *                    between tiles (the decoupled look-back); the granule and carried scans sum
+ *                    float32 differences to float32 accuracy over 16 positions, everything beyond in
+ *                    float64. The adjoint of the plain SFT runs the mixed scan in this mode.
  *   MORLET_ACC_F64 : float64 scan state, carries and K-term combination (a reference mode).
  *   MORLET_ACC_MIXED: float64 chunk sums and wave scan, float32 recurrence and combination.
  *   MORLET_ACC_KAHAN: the float32 tile scan compensated: every sum and product a thread forms
@@ -176,8 +177,9 @@ morlet_status morlet_plan_multiply(morlet_plan_t* out, int64_t N, double sigma, 
  *   y = G_y *_columns (G_x *_rows img),
  * each axis by eq. aproGauss with orders 0..K-1 on its own window [-L_x, L_x], [-L_y, L_y]
  * (0: the error-optimal window of the fit), zero outside the image. Evaluated as one scan
- * launch over the H rows, a transpose, one scan launch over the W rows of the transposed
- * image and a transpose back. morlet_plan_set (SFT/ASFT with one n0 for both axes, 0 = each
+ * launch over the H rows and one down the W columns (with accumulations, tile shapes or schedules
+ * that the granule scan does not take: a transpose, one scan launch over the W rows of the
+ * transposed image and a transpose back). morlet_plan_set (SFT/ASFT with one n0 for both axes, 0 = each
  * axis's default; accumulation), _set_tile and _set_schedule apply to both axes; autotune
  * and the 1-D backward calls return MORLET_ERR_UNSUPPORTED (gauss_smooth2d_backward is the
  * image's backward); morlet_plan_info returns
@@ -197,8 +199,8 @@ morlet_status gauss_smooth2d(morlet_plan_t plan, const void* x, morlet_dtype dty
 
 /* Backward of the 2-D smoothing for a real loss: gy = dLoss/dy (device float32, H x W) ->
  * gx = dLoss/dx (device float32, H x W, overwritten). The smoothing is linear, so gx is its
- * transpose applied to gy: a transpose, the adjoint scan over the W column lines, a transpose,
- * the adjoint scan over the H row lines. Workspace: morlet_backward_workspace_size (zero-filled
+ * transpose applied to gy: the adjoint scan over the W column lines (between transposes where the
+ * forward has them), then over the H row lines. Workspace: morlet_backward_workspace_size (zero-filled
  * once; it is not the forward's). Errors as gauss_smooth2d. */
 morlet_status gauss_smooth2d_backward(morlet_plan_t plan, const float* gy, float* gx, void* ws, size_t ws_bytes,
                                       void* stream);
@@ -227,9 +229,10 @@ morlet_status morlet_plan_gabor2d(morlet_plan_t* out, int64_t H, int64_t W, doub
                                   int64_t L_x, double sigma_y, int32_t K_y, int64_t L_y);
 
 /* 2-D Gabor filter: x (device, H x W elements of dtype, row-major) -> y (device complex64
- * [re, im] pairs, H x W, row-major). Four launches on the stream: the batched Morlet scan of
- * the H rows into the workspace, a transpose into the real and imaginary planes, one Gaussian
- * scan over their 2W column lines, a transpose back into y. Workspace: morlet_workspace_size
+ * [re, im] pairs, H x W, row-major). Two launches on the stream: the batched Morlet scan of
+ * the H rows into the workspace and one Gaussian scan down its 2W real columns into y (where the
+ * granule scan does not apply four: a transpose into the real and imaginary planes, the scan over
+ * their 2W lines, a transpose back). Workspace: morlet_workspace_size
  * (zero-filled once): the tile states and two H W complex64 buffers. Errors: a non-Gabor plan
  * is MORLET_ERR_INVALID_ARG; otherwise as gauss_smooth2d. */
 morlet_status gabor2d(morlet_plan_t plan, const void* x, morlet_dtype dtype, void* y, void* ws, size_t ws_bytes,
@@ -237,8 +240,8 @@ morlet_status gabor2d(morlet_plan_t plan, const void* x, morlet_dtype dtype, voi
 
 /* Backward of the 2-D Gabor filter for a real loss: gW = dLoss/dRe y + i dLoss/dIm y (device
  * complex64, H x W) -> gx = dLoss/dx (device float32, H x W, overwritten). The transposes of
- * the two passes in reverse order: gW into its real and imaginary planes, the Gaussian adjoint
- * over the 2W column lines, back to complex64, the batched Morlet adjoint over the H rows
+ * the two passes in reverse order: the Gaussian adjoint over the 2W real columns (lines of its two
+ * planes where the forward transposes), the batched Morlet adjoint over the H rows
  * (per-line adjoints as morlet_backward); gabor2d_grad adds the parameter gradients. Workspace:
  * morlet_backward_workspace_size (zero-filled once; not the forward's). Errors: a non-Gabor
  * plan is MORLET_ERR_INVALID_ARG; a short workspace MORLET_ERR_WORKSPACE. */
@@ -306,11 +309,13 @@ morlet_status morlet_plan_set_boundary(morlet_plan_t plan, morlet_boundary bound
  * For more rows it acts as AUTO. MORLET_SCHED_AUTO (default): at tile shape R = 16 and float32, mixed
  * or default accumulation the granule scan (rows cut into pieces of 256-position granules, each piece
  * summing the window before it, so no wave waits on another and the workspace is not used; float64
- * states), except single signals whose window is much longer than a piece; else rows when the longest row has no
- * more tiles than one block's share of all tiles; else segments for at most eight rows with at
+ * states), or, for rows of one length whose window is much longer than a piece, the carried scan (two
+ * launches, the first for the pieces' sums, 16 K bytes each in the workspace), for the forward and the adjoint
+ * (not of an edge-extended signal); else rows when the longest row has no
+ * more tiles than one block's share of all tiles; else segments (forward) for at most eight rows with at
  * least two tiles per resident block; else tiles. The schedules are deterministic; they differ
- * only in the float64 rounding of the carried states. The adjoint and gradient passes use tiles
- * or rows. Host-only, no device work. */
+ * in the float64 rounding of the carried states and in how float32 rounding enters the outputs. The gradient
+ * pass uses tiles or rows. Host-only, no device work. */
 typedef enum {
   MORLET_SCHED_AUTO = 0,
   MORLET_SCHED_TILES = 1,
@@ -385,10 +390,10 @@ morlet_status morlet_plan_info(morlet_plan_t plan, int64_t* L, int32_t* P_S, int
  * only, not the multiplication method. Errors: as morlet_forward / morlet_scalogram_forward
  * (MORLET_ERR_INVALID_ARG for a plan that is not a Morlet plan, MORLET_ERR_UNSUPPORTED for edge
  * extension, multiplication-method and image plans); MORLET_ERR_WORKSPACE, with nothing
- * launched, when the launch needs more than the array: the row-serial schedule of a scalogram
- * needs 64 bytes, the tiles schedule 64 bytes plus one tile state per tile of 256 R positions
+ * launched, when the launch needs more than the array: the granule scan needs none, the carried
+ * scan 64 bytes plus 16 K per piece (at most 512), the row-serial schedule of a scalogram 64 bytes, the tiles schedule 64 bytes plus one tile state per tile of 256 R positions
  * (256 bytes at K <= 5, 640 at K = 12), so a single signal of up to about 2^27 samples at K = 5,
- * R = 16; the segments schedule (the automatic choice for long single signals) 64 bytes plus
+ * R = 16; the segments schedule 64 bytes plus
  * 16 K bytes per segment (about two segments per resident block); MORLET_ERR_HIP if the
  * array's address cannot be resolved or a launch fails. */
 #define MORLET_NOALLOC_SCRATCH_BYTES (8u << 20)

@@ -391,7 +391,7 @@ morlet_status morlet_plan_info(morlet_plan_t plan, int64_t* L, int32_t* P_S, int
  * (MORLET_ERR_INVALID_ARG for a plan that is not a Morlet plan, MORLET_ERR_UNSUPPORTED for edge
  * extension, multiplication-method and image plans); MORLET_ERR_WORKSPACE, with nothing
  * launched, when the launch needs more than the array: the granule scan needs none, the carried
- * scan 64 bytes plus 16 K per piece (at most 512), the row-serial schedule of a scalogram 64 bytes, the tiles schedule 64 bytes plus one tile state per tile of 256 R positions
+ * scan 64 bytes plus 16 K per piece (at most one per compute unit), the row-serial schedule of a scalogram 64 bytes, the tiles schedule 64 bytes plus one tile state per tile of 256 R positions
  * (256 bytes at K <= 5, 640 at K = 12), so a single signal of up to about 2^27 samples at K = 5,
  * R = 16; the segments schedule 64 bytes plus
  * 16 K bytes per segment (about two segments per resident block); MORLET_ERR_HIP if the

@@ -155,3 +155,38 @@ def test_graph_replays():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, plan.forward(x))
+
+
+@pytest.mark.parametrize("mode", ["sft", "asft"])
+def test_other_callers_with_long_windows(mode):
+    # images of few long lines, the multiplication method's three rows and the differentials, both
+    # directions, against the same plans under the tiles schedule
+    import paper_2110_11866_amd as M
+    rng = np.random.default_rng(6)
+    H, W = 12, 30011
+    img = torch.from_numpy(rng.standard_normal((H, W)).astype(np.float32)).cuda()
+    gc = torch.from_numpy(rng.standard_normal((H, W, 2)).astype(np.float32)).cuda().view(torch.complex64)[..., 0].contiguous()
+    x, gx = img.reshape(-1)[:70001].contiguous(), gc.reshape(-1)[:70001].contiguous()
+
+    def both(name, plan, runs):
+        _say(name, mode)
+        got = [r() for r in runs]
+        plan.set_schedule("tiles")
+        for a, r in zip(got, runs):
+            assert _rel(a.cpu().numpy(), r().cpu().numpy()) <= 2 * TOL
+
+    p = M.Gauss2DPlan(H, W, 2.0, 3000.0, 4, 6, 9001, mode=mode)
+    both("gauss2d", p, [lambda: p.forward(img), lambda: p.backward(img)])
+    q = M.Gabor2DPlan(H, W, 3000.0, 0.002, 5, 2.0, 4, 9001, 6, mode=mode)
+    both("gabor2d", q, [lambda: q.forward(img), lambda: q.backward(gc)])
+    tall = img.t().contiguous()   # long columns: the second axis
+    gt = gc.t().contiguous()
+    v = M.Gauss2DPlan(W, H, 3000.0, 2.0, 4, 9001, 6, mode=mode)
+    both("gauss2d columns", v, [lambda: v.forward(tall), lambda: v.backward(tall)])
+    u = M.Gabor2DPlan(W, H, 2.0, 1.5, 5, 3000.0, 4, 6, 9001, mode=mode)
+    both("gabor2d columns", u, [lambda: u.forward(tall), lambda: u.backward(gt)])
+    m = M.MultiplyPlan(70001, 3000.0, 0.002, 2, 9001, mode=mode)
+    both("multiply", m, [lambda: m.forward(x), lambda: m.backward(None, gx)[0]])
+    for order in (1, 2):
+        d = M.GaussDerivPlan(70001, 3000.0, 6, 12001, order, mode=mode)
+        both("deriv", d, [lambda: d.forward(x), lambda: d.backward(None, x)[0]])

@@ -36,7 +36,10 @@ struct GranLayout {
   MK_HD int dSC(int d, int s, int part) const { return 64 * (4 * MB() + 2 * NS()) + 4 * ((d * NS() + s) * 2 + part); }
   MK_HD int dG(int k, int s, int part) const { return dSC(6, 0, 0) + 4 * ((k * NS() + s) * 2 + part); }
   MK_HD int dD() const { return dG(17, 0, 0); }
-  MK_HD int nDoubles() const { return (dD() + 32) / 32 * 32; }
+  // run sums of the complex adjoint, from stream c (real, imaginary part of the cotangent): dP times the
+  // term's output weight of component c
+  MK_HD int dPA(int c, int mb, int kb) const { return (dD() + 64) / 64 * 64 + 64 * (4 * (c * MB() + mb) + kb); }
+  MK_HD int nDoubles() const { return dPA(2, 0, 0); }
   // bfloat16 thirds of the float32 weights (value = high + middle + low, exactly), four per lane:
   // T[4 q + e -> r] of component c, and the weights of state components 4 set + e (0 past the last)
   MK_HD int SETS() const { return NS() > 2 ? 2 : 1; }
@@ -45,7 +48,10 @@ struct GranLayout {
   // run sums: lane 16 q + 4 u + v holds the weights of inputs 4 q + e for component v of the states u, u + 4
   // (block 0: real and imaginary parts of slots 0, 1) or u + 8 (block 1)
   MK_HD int bP(int mb, int third) const { return 64 * (6 + 6 * SETS() + 3 * mb + third); }
-  MK_HD int nQuads() const { return 64 * (6 + 6 * SETS() + 3 * MB()); }
+  // the same for the complex adjoint (dPA), and its output from the state before the run, Re a^{r + 1} V
+  MK_HD int bPA(int c, int mb, int third) const { return 64 * (6 + 6 * SETS() + 3 * (MB() + c * MB() + mb) + third); }
+  MK_HD int bCA(int set, int third) const { return 64 * (6 + 6 * SETS() + 9 * MB() + 3 * set + third); }
+  MK_HD int nQuads() const { return bCA(SETS(), 0); }
   MK_HD size_t quadOff() const { return (size_t)nFloats() * 4 + (size_t)nDoubles() * 8; }
   MK_HD size_t bytes() const { return quadOff() + (size_t)nQuads() * 8; }
 };

@@ -149,32 +149,45 @@ template <int NS, bool WIDE>
 struct RunSums {
   static constexpr int MB = NS > 2 ? 2 : 1;
   using sum_t = typename std::conditional<WIDE, double, float>::type;
+  using acc_t = typename std::conditional<WIDE, v4d, v4f>::type;
   double p[WIDE ? MB : 1][4];
   Weights w[WIDE ? 1 : MB];
-  __device__ __forceinline__ void load(const GranLayout& lay, const double* td, const v2i* tq, int lane) {
+  // c: -1, or the stream of the complex adjoint
+  __device__ __forceinline__ void load(const GranLayout& lay, const double* td, const v2i* tq, int lane, int c = -1) {
 #pragma unroll
     for (int b = 0; b < MB; ++b) {
       if constexpr (WIDE) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) p[b][k] = td[lay.dP(b, k) + lane];
-      } else {
+        for (int k = 0; k < 4; ++k) p[b][k] = td[(c < 0 ? lay.dP(b, k) : lay.dPA(c, b, k)) + lane];
+      } else if (c < 0) {
         w[b].load(tq, lay.bP(b, 0), lay.bP(b, 1), lay.bP(b, 2));
+      } else {
+        w[b].load(tq, lay.bPA(c, b, 0), lay.bPA(c, b, 1), lay.bPA(c, b, 2));
       }
     }
   }
-  __device__ __forceinline__ void operator()(const double (&d)[4], const v6i& x, sum_t (&br)[NS], sum_t (&bi)[NS]) const {
+  __device__ __forceinline__ void add(const double (&d)[4], const v6i& x, acc_t (&acc)[MB]) const {
 #pragma unroll
     for (int b = 0; b < MB; ++b) {
-      typename std::conditional<WIDE, v4d, v4f>::type acc = {0, 0, 0, 0};
       if constexpr (WIDE) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(p[b][k], d[k], acc, 0, 0, 0);
+        for (int k = 0; k < 4; ++k) acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(p[b][k], d[k], acc[b], 0, 0, 0);
       } else {
-        acc = product_t(w[b], x, acc);
+        acc[b] = product_t(w[b], x, acc[b]);
       }
-      br[2 * b] = acc[0]; bi[2 * b] = acc[1];
-      if (2 * b + 1 < NS) { br[2 * b + 1] = acc[2]; bi[2 * b + 1] = acc[3]; }
     }
+  }
+  static __device__ __forceinline__ void states(const acc_t (&acc)[MB], sum_t (&br)[NS], sum_t (&bi)[NS]) {
+#pragma unroll
+    for (int b = 0; b < MB; ++b) {
+      br[2 * b] = acc[b][0]; bi[2 * b] = acc[b][1];
+      if (2 * b + 1 < NS) { br[2 * b + 1] = acc[b][2]; bi[2 * b + 1] = acc[b][3]; }
+    }
+  }
+  __device__ __forceinline__ void operator()(const double (&d)[4], const v6i& x, sum_t (&br)[NS], sum_t (&bi)[NS]) const {
+    acc_t acc[MB] = {};
+    add(d, x, acc);
+    states(acc, br, bi);
   }
 };
 

@@ -41,7 +41,10 @@ namespace {
 
 // IN: the input (Quad). CPLX: the transform's outputs are complex (IN < 3: complex64 out; IN 3: their
 // cotangent comes in). An output component k is formed from stream k of the adjoint's two, or from
-// the only stream; the adjoint adds its components, Re sum conj(h) g = (h_re * g_re) + (h_im * g_im).
+// the only stream; the adjoint adds its components, Re sum conj(h) g = (h_re * g_re) + (h_im * g_im). Term
+// p's part of the sum is Re a^d w_p with w_p = q_re g_re + q_im g_im (q: the term's complex output weights), so
+// the complex adjoint runs one state per term on w_p (with a state for each stream 188 us a launch at
+// 64 x 32768 x 16 scales, K = 5, now 166).
 // NST: runs per lane column; a wave works on 16 columns of NST consecutive runs (256 NST positions) at a
 // time, so that the scan across lanes is done once for NST runs.
 // WIDE: run sums in float64 (the mixed scan), else from float32 inputs to float32 (the float32 scan);
@@ -50,6 +53,8 @@ template <int NS, bool CPLX, int IN, int NST, bool WIDE>
 __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
   constexpr bool REV = IN >= kInRev;
   constexpr int ST = IN == 3 ? 2 : 1, NC = CPLX ? 2 : 1, SETS = NS > 2 ? 2 : 1;
+  constexpr int NO = CPLX && !REV ? 2 : 1;   // outputs of a state: the complex adjoint has one state for its two streams
+  using Sums = RunSums<NS, WIDE>;
   constexpr int G = kGran * NST;        // positions at a time
   constexpr int PS = NST == 1 ? kGran : kGran + 16;   // floats from one run of the columns to the next
   constexpr int LV = NST == 1 ? 0 : NST == 2 ? 1 : 2;  // log2 NST
@@ -95,19 +100,23 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
   const float* tf = reinterpret_cast<const float*>(tb);
   const double* td = reinterpret_cast<const double*>(tf + lay.nFloats());
   const v2i* tq = reinterpret_cast<const v2i*>(tb + lay.quadOff()) + lane;
-  Weights T[NC], C[NC][SETS];
+  Weights T[NC], C[NO][SETS];
   float Y[NC];
   double ar[NS], ai[NS];   // a^16
-  RunSums<NS, WIDE> run_sums;
+  Sums run_sums[ST];
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
     T[k].load(tq, lay.bT(k, 0), lay.bT(k, 1), lay.bT(k, 2));
+  }
+#pragma unroll
+  for (int k = 0; k < NO; ++k)
 #pragma unroll
     for (int e = 0; e < SETS; ++e) {
-      C[k][e].load(tq, lay.bC(k, e, 0), lay.bC(k, e, 1), lay.bC(k, e, 2));
+      if constexpr (IN == 3) C[k][e].load(tq, lay.bCA(e, 0), lay.bCA(e, 1), lay.bCA(e, 2));
+      else C[k][e].load(tq, lay.bC(k, e, 0), lay.bC(k, e, 1), lay.bC(k, e, 2));
     }
-  }
-  run_sums.load(lay, td, tq, lane);
+#pragma unroll
+  for (int t = 0; t < ST; ++t) run_sums[t].load(lay, td, tq, lane, IN == 3 ? t : -1);
 #pragma unroll
   for (int s = 0; s < NS; ++s) { ar[s] = td[lay.dSC(0, s, 0) + q]; ai[s] = td[lay.dSC(0, s, 1) + q]; }
   Y[0] = tf[lay.fYre()];
@@ -136,14 +145,12 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
   const int bslot0 = 64 * q + 4 * ((c >> 2) ^ bs) + (c & 3);
   const int bslot1 = 64 * q + 32 + 4 * ((c >> 2) ^ bs ^ 1) + (c & 3);
 
-  using sum_t = typename RunSums<NS, WIDE>::sum_t;
+  using sum_t = typename Sums::sum_t;
   const int64_t js = first + row.jout0;   // position of the piece's first output
   // the states before position js: every lane of row q holds state 4 s + q in slot s
-  double zr[ST][NS], zi[ST][NS];
+  double zr[NS], zi[NS];
 #pragma unroll
-  for (int t = 0; t < ST; ++t)
-#pragma unroll
-    for (int s = 0; s < NS; ++s) { zr[t][s] = 0; zi[t][s] = 0; }
+  for (int s = 0; s < NS; ++s) { zr[s] = 0; zi[s] = 0; }
   {
     const int64_t lo = js - L2 > 0 ? js - L2 : 0;
     const int64_t nw = js > lo && lo < N ? (js - lo + kGran - 1) / kGran : 0;
@@ -165,6 +172,7 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
 #pragma unroll
         for (int t = 0; t < ST; ++t) ya[t] = *reinterpret_cast<const v4f*>(s_y[t] + rslot);
         lds_order();
+        typename Sums::acc_t acc[Sums::MB] = {};
 #pragma unroll
         for (int t = 0; t < ST; ++t) {
           const double d[4] = {(double)ya[t][0], (double)ya[t][1], (double)ya[t][2], (double)ya[t][3]};
@@ -173,27 +181,25 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
             const float f[4] = {ya[t][0], ya[t][1], ya[t][2], ya[t][3]};
             x = thirds(f);
           }
-          sum_t br[NS], bi[NS];
-          run_sums(d, x, br, bi);
+          run_sums[t].add(d, x, acc);
+        }
+        sum_t br[NS], bi[NS];
+        Sums::states(acc, br, bi);
 #pragma unroll
-          for (int s = 0; s < NS; ++s) {   // per column: z <- a^256 z + B
-            double xr = br[s], xi = bi[s];
-            mac(gr[s], gi[s], zr[t][s], zi[t][s], xr, xi);
-            zr[t][s] = xr; zi[t][s] = xi;
-          }
+        for (int s = 0; s < NS; ++s) {   // per column: z <- a^256 z + B
+          double xr = br[s], xi = bi[s];
+          mac(gr[s], gi[s], zr[s], zi[s], xr, xi);
+          zr[s] = xr; zi[s] = xi;
         }
       }
       // sum over the columns, weighted a^{16 (15 - c)}
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         const double wr = td[lay.dLANE(s, 0) + (lane ^ 15)], wi = td[lay.dLANE(s, 1) + (lane ^ 15)];
+        double vr = wr * zr[s] - wi * zi[s], vi = wr * zi[s] + wi * zr[s];
 #pragma unroll
-        for (int t = 0; t < ST; ++t) {
-          double vr = wr * zr[t][s] - wi * zi[t][s], vi = wr * zi[t][s] + wi * zr[t][s];
-#pragma unroll
-          for (int off = 8; off >= 1; off >>= 1) { vr += __shfl_xor(vr, off, 64); vi += __shfl_xor(vi, off, 64); }
-          zr[t][s] = vr; zi[t][s] = vi;
-        }
+        for (int off = 8; off >= 1; off >>= 1) { vr += __shfl_xor(vr, off, 64); vi += __shfl_xor(vi, off, 64); }
+        zr[s] = vr; zi[s] = vi;
       }
     }
   }
@@ -236,13 +242,14 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
     // run sums of the columns' runs, then the state before each column
     float df[WIDE ? ST : 1][NST][4];       // dy (WIDE), or its thirds
     v6i dx[WIDE ? 1 : ST][NST];
-    sum_t br[ST][NST][NS], bi[ST][NST][NS];
-    double er[ST][NS], ei[ST][NS];
+    sum_t br[NST][NS], bi[NST][NS];
+    double er[NS], ei[NS];
     bool odd = false;   // some input is infinite or NaN (or a run's sum overflows)
 #pragma unroll
-    for (int t = 0; t < ST; ++t)
+    for (int i = 0; i < NST; ++i) {
+      typename Sums::acc_t acc[Sums::MB] = {};
 #pragma unroll
-      for (int i = 0; i < NST; ++i) {
+      for (int t = 0; t < ST; ++t) {
         const v4f a = *reinterpret_cast<const v4f*>(s_y[t] + i * PS + rslot);
         const v4f b = *reinterpret_cast<const v4f*>(s_b[t] + i * PS + rslot);
         double d[4] = {0, 0, 0, 0};
@@ -258,9 +265,11 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
         }
         odd = odd || !__builtin_isfinite((f[0] + f[1]) + (f[2] + f[3]));
         if constexpr (!WIDE) dx[t][i] = thirds(f);
-        run_sums(d, dx[WIDE ? 0 : t][i], br[t][i], bi[t][i]);
+        run_sums[t].add(d, dx[WIDE ? 0 : t][i], acc);
         __builtin_amdgcn_sched_barrier(0);   // a run at a time (registers)
       }
+      Sums::states(acc, br[i], bi[i]);
+    }
     const bool slow = __ballot(odd) != 0;
     if (slow) {   // the run product sees zeros for those inputs (below), the run sums have seen them
 #pragma unroll
@@ -280,16 +289,15 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
           __builtin_amdgcn_sched_barrier(0);
         }
     }
-#pragma unroll
-    for (int t = 0; t < ST; ++t) {
+    {
       double fr[NS], fi[NS];   // sum over the column's runs; the carry enters column 0
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        fr[s] = c == 0 ? zr[t][s] : 0.0;
-        fi[s] = c == 0 ? zi[t][s] : 0.0;
+        fr[s] = c == 0 ? zr[s] : 0.0;
+        fi[s] = c == 0 ? zi[s] : 0.0;
 #pragma unroll
         for (int i = 0; i < NST; ++i) {
-          double xr = br[t][i][s], xi = bi[t][i][s];
+          double xr = br[i][s], xi = bi[i][s];
           mac(ar[s], ai[s], fr[s], fi[s], xr, xi);
           fr[s] = xr; fi[s] = xi;
         }
@@ -305,10 +313,10 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         const double pr = row_shr<1>(fr[s]), pi = row_shr<1>(fi[s]);
-        er[t][s] = c == 0 ? zr[t][s] : pr;
-        ei[t][s] = c == 0 ? zi[t][s] : pi;
-        zr[t][s] = row_last(fr[s]);
-        zi[t][s] = row_last(fi[s]);
+        er[s] = c == 0 ? zr[s] : pr;
+        ei[s] = c == 0 ? zi[s] : pi;
+        zr[s] = row_last(fr[s]);
+        zi[s] = row_last(fi[s]);
       }
     }
 
@@ -316,26 +324,23 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
 #pragma unroll
     for (int i = 0; i < NST; ++i) {
       v4f o[NC];
-      v6i sx[ST][SETS];
+      v6i sx[SETS];
 #pragma unroll
-      for (int t = 0; t < ST; ++t) {
+      for (int e = 0; e < SETS; ++e) {
+        float x[4];
 #pragma unroll
-        for (int e = 0; e < SETS; ++e) {
-          float x[4];
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const int s = 2 * e + k / 2;
-            x[k] = s < NS ? (float)(k & 1 ? ei[t][s < NS ? s : 0] : er[t][s < NS ? s : 0]) : 0.0f;
-          }
-          sx[t][e] = thirds(x);
+        for (int k = 0; k < 4; ++k) {
+          const int s = 2 * e + k / 2;
+          x[k] = s < NS ? (float)(k & 1 ? ei[s < NS ? s : 0] : er[s < NS ? s : 0]) : 0.0f;
         }
-        if (i + 1 < NST) {
+        sx[e] = thirds(x);
+      }
+      if (i + 1 < NST) {
 #pragma unroll
-          for (int s = 0; s < NS; ++s) {   // on to the next run of the column
-            double xr = br[t][i][s], xi = bi[t][i][s];
-            mac(ar[s], ai[s], er[t][s], ei[t][s], xr, xi);
-            er[t][s] = xr; ei[t][s] = xi;
-          }
+        for (int s = 0; s < NS; ++s) {   // on to the next run of the column
+          double xr = br[i][s], xi = bi[i][s];
+          mac(ar[s], ai[s], er[s], ei[s], xr, xi);
+          er[s] = xr; ei[s] = xi;
         }
       }
 #pragma unroll
@@ -381,9 +386,9 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
         }
       }
 #pragma unroll
-      for (int k = 0; k < NC; ++k)
+      for (int k = 0; k < NO; ++k)
 #pragma unroll
-        for (int e = 0; e < SETS; ++e) o[k] = product(sx[k % ST][e], C[k][e], o[k]);
+        for (int e = 0; e < SETS; ++e) o[k] = product(sx[e], C[k][e], o[k]);
 
       // lane 16 q + r: position r of run i of columns 4 q + v
 #pragma unroll

@@ -404,6 +404,7 @@ void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, dou
   // output: (gre + i gim)(A - iB) for the wavelet, gre (A - B) for real output, with
   // A = cx y + sum_t mw_t Re v_t, B = sum_t lw_t Im v_t; weights of Re v, Im v per component
   double T[2][kRun] = {}, cx = 0;
+  float ca[8][64] = {};   // outputs of the complex adjoint from its state: component 2 slot + part
   for (int i = 0; i < K; ++i) {
     const int64_t p = P_S + i;
     const int slot = i / 4, q = i % 4;
@@ -421,8 +422,14 @@ void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, dou
       const int v = 2 * (slot % 2);   // result registers v, v + 1 of lane row q: rows q + 4 v, q + 4 (v + 1)
       td[lay.dP(b, kb) + lq + q + 4 * v] = re;
       td[lay.dP(b, kb) + lq + q + 4 * (v + 1)] = im;
+      for (int c = 0; c < 2; ++c) {
+        td[lay.dPA(c, b, kb) + lq + q + 4 * v] = wr[c] * re + wi[c] * im;
+        td[lay.dPA(c, b, kb) + lq + q + 4 * (v + 1)] = wr[c] * im - wi[c] * re;
+      }
       // outputs at position d from the state before the run
       apow(p, d + 1, L, alpha, re, im);
+      ca[2 * slot][16 * q + d] = (float)re;
+      ca[2 * slot + 1][16 * q + d] = (float)-im;
       tf[lay.fCre(2 * slot) + 16 * q + d] = (float)(wr[0] * re + wi[0] * im);
       tf[lay.fCre(2 * slot + 1) + 16 * q + d] = (float)(-wr[0] * im + wi[0] * re);
       tf[lay.fCim(2 * slot) + 16 * q + d] = (float)(wr[1] * re + wi[1] * im);
@@ -472,7 +479,15 @@ void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, dou
         const int u = lane / 4 % 4, v = lane % 4;   // the float64 table has row u + 4 v
         thirds((float)td[lay.dP(b, e) + 16 * (lane / 16) + u + 4 * v], bq + 4 * (lay.bP(b, 0) + lane) + e,
                bq + 4 * (lay.bP(b, 1) + lane) + e, bq + 4 * (lay.bP(b, 2) + lane) + e);
+        for (int c = 0; c < 2; ++c)
+          thirds((float)td[lay.dPA(c, b, e) + 16 * (lane / 16) + u + 4 * v], bq + 4 * (lay.bPA(c, b, 0) + lane) + e,
+                 bq + 4 * (lay.bPA(c, b, 1) + lane) + e, bq + 4 * (lay.bPA(c, b, 2) + lane) + e);
       }
+  for (int set = 0; set < lay.SETS(); ++set)
+    for (int lane = 0; lane < 64; ++lane)
+      for (int e = 0; e < 4; ++e)
+        thirds(ca[4 * set + e][lane], bq + 4 * (lay.bCA(set, 0) + lane) + e, bq + 4 * (lay.bCA(set, 1) + lane) + e,
+               bq + 4 * (lay.bCA(set, 2) + lane) + e);
   for (int c = 0; c < 2; ++c)
     for (int lane = 0; lane < 64; ++lane)
       for (int e = 0; e < 4; ++e) {

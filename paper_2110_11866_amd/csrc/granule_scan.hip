@@ -44,7 +44,7 @@ namespace {
 // the only stream; the adjoint adds its components, Re sum conj(h) g = (h_re * g_re) + (h_im * g_im). Term
 // p's part of the sum is Re a^d w_p with w_p = q_re g_re + q_im g_im (q: the term's complex output weights), so
 // the complex adjoint runs one state per term on w_p (with a state for each stream 188 us a launch at
-// 64 x 32768 x 16 scales, K = 5, now 166).
+// 64 x 32768 x 16 scales, K = 5, now 142).
 // NST: runs per lane column; a wave works on 16 columns of NST consecutive runs (256 NST positions) at a
 // time, so that the scan across lanes is done once for NST runs.
 // WIDE: run sums in float64 (the mixed scan), else from float32 inputs to float32 (the float32 scan);
@@ -427,8 +427,8 @@ template <int NS>
 GranFn pick(bool cplx, int in, bool two, bool wide) {
 #define MK_PICK(C, D) \
   if (cplx == (C) && in == (D)) \
-    return wide ? (two ? granule_kernel<NS, C, D, 2, true> : granule_kernel<NS, C, D, 1, true>) \
-                : (two ? granule_kernel<NS, C, D, 2, false> : granule_kernel<NS, C, D, 1, false>);
+    return wide ? (two ? granule_kernel<NS, C, D, (D) == 3 ? 1 : 2, true> : granule_kernel<NS, C, D, 1, true>) \
+                : (two ? granule_kernel<NS, C, D, (D) == 3 ? 1 : 2, false> : granule_kernel<NS, C, D, 1, false>);
   MK_PICK(false, 0) MK_PICK(false, 1) MK_PICK(false, 2) MK_PICK(false, 4)
   MK_PICK(true, 0) MK_PICK(true, 1) MK_PICK(true, 2) MK_PICK(true, 3)
 #undef MK_PICK
@@ -445,7 +445,8 @@ hipError_t launch_granules(const GranLaunch& a, hipStream_t s) {
   const int ns = GranLayout{a.K}.NS();
   const int in = a.adjoint ? (cplx ? 3 : 4) : a.dtype;
   // two runs per lane column halve the scans across lanes in long pieces (ragged scalogram 1000 us a
-  // launch against 1090); four leave two waves per SIMD (1005)
+  // launch against 1090); four leave two waves per SIMD (1005). In the complex adjoint two already do
+  // (202 registers, 166 us at 64 x 32768 x 16 scales): one, three waves (142)
   const bool two = a.two != 0;
   const GranFn fn = ns == 1 ? pick<1>(cplx, in, two, a.acc == kAccMixed) : ns == 2 ? pick<2>(cplx, in, two, a.acc == kAccMixed) : pick<3>(cplx, in, two, a.acc == kAccMixed);
   if (!fn) return hipErrorInvalidValue;

@@ -111,35 +111,57 @@ __global__ __launch_bounds__(64 * kCW) void carry_sums_kernel(GranLaunch P) {
   const float Df = (float)Dd;
   const int w1 = 4 * (4 * (lane >> 2) + ((lane & 3) ^ swz(lane >> 2)));
   const int rslot = 4 * (4 * c + (q ^ swz(c)));
-  for (int i = 0; i < P.seg_n; ++i) {
+  using Sums = RunSums<NS, WIDE>;
+  auto sum = [&](auto split) {   // the piece's chunks, the first loaded; returns whether some input had no thirds
+    uint32_t top = 0;
+    for (int i = 0; i < P.seg_n; ++i) {
 #pragma unroll
-    for (int t = 0; t < ST; ++t) {
-      *reinterpret_cast<v4f*>(s_y[w][t] + w1) = ya.f32(t);
-      *reinterpret_cast<v4f*>(s_b[w][t] + w1) = yb.f32(t);
-    }
-    p += kChunk;
-    if (i + 1 < P.seg_n) {
-      ya.load(a.xs, p, 0, N, N, lane);
-      yb.load(a.xs, p - L2, 0, N, N, lane);
-    }
-    lds_order();
-#pragma unroll
-    for (int t = 0; t < ST; ++t) {
-      double d[4];
-      float f[4];
-      differences(s_y[w][t] + rslot, s_b[w][t] + rslot, Dd, Df, WIDE, d, f);
-      v6i x = {};
-      if constexpr (!WIDE) x = thirds(f);
-      typename RunSums<NS, WIDE>::sum_t br[NS], bi[NS];
-      run_sums(d, x, br, bi);
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        double xr = br[s], xi = bi[s];
-        mac(gr[s], gi[s], zr[t][s], zi[t][s], xr, xi);
-        zr[t][s] = xr; zi[t][s] = xi;
+      for (int t = 0; t < ST; ++t) {
+        *reinterpret_cast<v4f*>(s_y[w][t] + w1) = ya.f32(t);
+        *reinterpret_cast<v4f*>(s_b[w][t] + w1) = yb.f32(t);
       }
+      p += kChunk;
+      if (i + 1 < P.seg_n) {
+        ya.load(a.xs, p, 0, N, N, lane);
+        yb.load(a.xs, p - L2, 0, N, N, lane);
+      }
+      lds_order();
+#pragma unroll
+      for (int t = 0; t < ST; ++t) {
+        double d[4];
+        float f[4];
+        differences(s_y[w][t] + rslot, s_b[w][t] + rslot, Dd, Df, WIDE, d, f);
+        typename Sums::acc_t acc[Sums::MB] = {};
+        if constexpr (WIDE) {
+          run_sums.add(d, v6i{}, acc);
+        } else if constexpr (decltype(split)::value) {
+          keep_top(top, f);
+          run_sums.add(d, thirds(f), acc);
+        } else {
+          run_sums.add_unsplit(f, acc);
+        }
+        typename Sums::sum_t br[NS], bi[NS];
+        Sums::states(acc, br, bi);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          double xr = br[s], xi = bi[s];
+          mac(gr[s], gi[s], zr[t][s], zi[t][s], xr, xi);
+          zr[t][s] = xr; zi[t][s] = xi;
+        }
+      }
+      lds_order();
     }
-    lds_order();
+    return no_thirds(top);
+  };
+  if (sum(std::true_type{})) {
+    p -= kChunk * (int64_t)P.seg_n;
+    ya.load(a.xs, p, 0, N, N, lane);
+    yb.load(a.xs, p - L2, 0, N, N, lane);
+#pragma unroll
+    for (int t = 0; t < ST; ++t)
+#pragma unroll
+      for (int s = 0; s < NS; ++s) { zr[t][s] = 0; zi[t][s] = 0; }
+    sum(std::false_type{});
   }
   // over the columns, weighted a^{16 (15 - c)}, and the waves, a^{256 (7 - w)}
 #pragma unroll
@@ -295,6 +317,7 @@ __global__ __launch_bounds__(64 * kCW) void carry_kernel(GranLaunch P) {
   const int bslot0 = 64 * q + 4 * ((c >> 2) ^ bs) + (c & 3);
   const int bslot1 = 64 * q + 32 + 4 * ((c >> 2) ^ bs ^ 1) + (c & 3);
   const int from = c < w ? c : kCW;
+  using Sums = RunSums<NS, WIDE>;
   for (int64_t i = 0; i < chunks; ++i, j += kChunk) {
     const int par = (int)(i & 1);
 #pragma unroll
@@ -309,33 +332,39 @@ __global__ __launch_bounds__(64 * kCW) void carry_kernel(GranLaunch P) {
     lds_order();
     v6i dx[ST];
     double er[ST][NS], ei[ST][NS], fr[ST][NS], fi[ST][NS];
-    bool odd = false;
+    uint32_t top = 0;
     unsigned nan = 0;   // the lane's inputs that are infinite or NaN
 #pragma unroll
     for (int t = 0; t < ST; ++t) {
       double d[4];
       float f[4];
       differences(s_y[w][t] + rslot, s_b[w][t] + rslot, Dd, Df, WIDE, d, f);
-      odd = odd || !__builtin_isfinite((f[0] + f[1]) + (f[2] + f[3]));
+      keep_top(top, f);
       dx[t] = thirds(f);
-      typename RunSums<NS, WIDE>::sum_t br[NS], bi[NS];
-      run_sums(d, dx[t], br, bi);
+      typename Sums::acc_t acc[Sums::MB] = {};
+      run_sums.add(d, dx[t], acc);
+      typename Sums::sum_t br[NS], bi[NS];
+      Sums::states(acc, br, bi);
 #pragma unroll
       for (int s = 0; s < NS; ++s) { fr[t][s] = br[s]; fi[t][s] = bi[s]; }
     }
-    const bool slow = __ballot(odd) != 0;
-    if (slow) {   // the run product sees zeros for those inputs, the run sums have seen them
+    const bool slow = no_thirds(top);
+    if (slow) {   // the run sums of the inputs as they are
 #pragma unroll
       for (int t = 0; t < ST; ++t) {
         double d[4];
         float f[4];
         differences(s_y[w][t] + rslot, s_b[w][t] + rslot, Dd, Df, WIDE, d, f);
+        if constexpr (!WIDE) {
+          typename Sums::acc_t acc[Sums::MB] = {};
+          run_sums.add_unsplit(f, acc);
+          typename Sums::sum_t br[NS], bi[NS];
+          Sums::states(acc, br, bi);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          nan |= __builtin_isfinite(f[k]) ? 0u : 1u << k;
-          f[k] = __builtin_isfinite(f[k]) ? f[k] : 0.0f;
+          for (int s = 0; s < NS; ++s) { fr[t][s] = br[s]; fi[t][s] = bi[s]; }
         }
-        dx[t] = thirds(f);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) nan |= __builtin_isfinite(f[k]) ? 0u : 1u << k;
       }
     }
 #pragma unroll
@@ -373,6 +402,13 @@ __global__ __launch_bounds__(64 * kCW) void carry_kernel(GranLaunch P) {
         mac(l.x, l.y, xr, xi, er[t][s], ei[t][s]);
       }
 
+    auto components = [&](int e, int t, float (&x)[4]) {   // states 2 e, 2 e + 1 of stream t in float32
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int s = 2 * e + k / 2;
+        x[k] = s < NS ? (float)(k & 1 ? ei[t][s < NS ? s : 0] : er[t][s < NS ? s : 0]) : 0.0f;
+      }
+    };
     v4f o[NC];
 #pragma unroll
     for (int k = 0; k < NC; ++k) {
@@ -382,7 +418,27 @@ __global__ __launch_bounds__(64 * kCW) void carry_kernel(GranLaunch P) {
       for (int v = 0; v < 4; ++v) o[k][v] = Y[k] * bv[v];
       o[k] = product(dx[k % ST], T[k], o[k]);
     }
-    if (slow) {
+    if (slow) {   // from the inputs and states as they are; infinite and NaN inputs count as zeros
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        double d[4];
+        float f[4];
+        differences(s_y[w][k % ST] + rslot, s_b[w][k % ST] + rslot, Dd, Df, WIDE, d, f);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) f[v] = __builtin_isfinite(f[v]) ? f[v] : 0.0f;
+        const float* b = s_b[w][k % ST];
+        o[k] = product_unsplit(f, T[k], v4f{Y[k] * b[bslot0], Y[k] * b[bslot0 + 16], Y[k] * b[bslot1], Y[k] * b[bslot1 + 16]});
+#pragma unroll
+        for (int e = 0; e < SETS; ++e) {
+          float x[4];
+          components(e, k % ST, x);
+          o[k] = product_unsplit(x, C[k][e], o[k]);
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < ST; ++t)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) { er[t][s] = 0; ei[t][s] = 0; }
       // an infinite or NaN input reaches the outputs of its run from its own position on: bit 16 q' + c'
       // of bad marks input 4 q' + e of column c'
 #pragma unroll 1
@@ -404,11 +460,7 @@ __global__ __launch_bounds__(64 * kCW) void carry_kernel(GranLaunch P) {
 #pragma unroll
       for (int t = 0; t < ST; ++t) {
         float x[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int s = 2 * e + k / 2;
-          x[k] = s < NS ? (float)(k & 1 ? ei[t][s < NS ? s : 0] : er[t][s < NS ? s : 0]) : 0.0f;
-        }
+        components(e, t, x);
         sx[t] = thirds(x);
       }
 #pragma unroll

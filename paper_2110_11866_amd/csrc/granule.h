@@ -27,7 +27,8 @@ struct GranLayout {
   MK_HD int fYre() const { return 64 * (8 + 4 * NS()); }
   MK_HD int fYim() const { return fYre() + 1; }
   MK_HD int nFloats() const { return (fYre() + 4 + 31) / 32 * 32; }
-  // float64: run sums B = sum_r a^{15 - r} dy[r], lane 16 q + m holding the weight of input 4 q + kb for
+  // float64: run sums B / 2, B = sum_r a^{15 - r} dy[r] (states are held at half their size, the weights fC*,
+  // bC and bCA are for such states), lane 16 q + m holding the weight of input 4 q + kb for
   // row m of the product; a^{16 c} per lane (64); a^{16 2^d}, d < 6, one value per q; a^{256 k},
   // k in [0, 16];
   // e^{-2 alpha L}. Parts of slot s: 0 real, 1 imaginary

@@ -79,7 +79,8 @@ struct Quad {
 };
 
 // Four float32 values as bfloat16 thirds, middle, high, low (two registers each): every value is the
-// exact sum of its thirds. The remainder after a third is one dot product with (-1, 0) or (0, -1).
+// exact sum of its thirds, if its nearest bfloat16 is finite (no_thirds). The remainder after a third is one
+// dot product with (-1, 0) or (0, -1).
 __device__ __forceinline__ int bf16_pair(float a, float b) {
   return __builtin_bit_cast(int, __builtin_convertvector(v2f{a, b}, v2b));
 }
@@ -100,9 +101,24 @@ __device__ __forceinline__ v6i thirds(const float (&x)[4]) {
   left(m1, r[2], r[3], t[2], t[3]);
   return v6i{m0, m1, h0, h1, bf16_pair(t[0], t[1]), bf16_pair(t[2], t[3])};
 }
+// The largest sum of four magnitudes that a lane has seen, as bits (an infinite or NaN one is above all others).
+__device__ __forceinline__ void keep_top(uint32_t& top, const float (&x)[4]) {
+  const uint32_t m = __float_as_uint((fabsf(x[0]) + fabsf(x[1])) + (fabsf(x[2]) + fabsf(x[3])));
+  top = m > top ? m : top;
+}
+// Whether some value of the wave's is infinite, NaN or so near the end of the range that its high third may be
+// infinite.
+__device__ __forceinline__ bool no_thirds(uint32_t top) { return __ballot(top >= __float_as_uint(0x1p126f)) != 0; }
 // Weights of four inputs per lane as thirds: middle, high, low.
 struct Weights {
   v6i w;
+  __device__ __forceinline__ float at(int e) const {   // the weight of input e
+    auto part = [&](int i) {
+      asm volatile("" : "+v"(i));   // formed where it is used, not kept in registers through the loop
+      return __int_as_float(e % 2 ? i & (int)0xffff0000 : i << 16);
+    };
+    return (part(w[4 + e / 2]) + part(w[e / 2])) + part(w[2 + e / 2]);
+  }
   __device__ __forceinline__ void load(const v2i* t, int h, int m, int l) {
     const v2i vh = t[h], vm = t[m], vl = t[l];
     w = v6i{vm[0], vm[1], vh[0], vh[1], vl[0], vl[1]};
@@ -121,7 +137,19 @@ __device__ __forceinline__ v4f product(const v6i& x, const Weights& w, v4f acc) 
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(hh, wmh, acc, 0, 0, 0);
 }
 
-// the same with the weights as rows
+// the same in float32, for any x (an infinite or NaN value must not meet a zero weight)
+__device__ __forceinline__ v4f product_unsplit(const float (&x)[4], const Weights& w, v4f acc) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], w.at(e), acc, 0, 0, 0);
+  return acc;
+}
+
+// product() and product_unsplit() with the weights as rows
+__device__ __forceinline__ v4f product_t_unsplit(const Weights& w, const float (&x)[4], v4f acc) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.at(e), x[e], acc, 0, 0, 0);
+  return acc;
+}
 __device__ __forceinline__ v4f product_t(const Weights& w, const v6i& x, v4f acc) {
   const v8b wmh = __builtin_bit_cast(v8b, __builtin_shufflevector(w.w, w.w, 0, 1, 2, 3));
   const v8b whl = __builtin_bit_cast(v8b, __builtin_shufflevector(w.w, w.w, 2, 3, 4, 5));
@@ -177,17 +205,17 @@ struct RunSums {
       }
     }
   }
+  __device__ __forceinline__ void add_unsplit(const float (&x)[4], acc_t (&acc)[MB]) const {
+    if constexpr (!WIDE)
+#pragma unroll
+      for (int b = 0; b < MB; ++b) acc[b] = product_t_unsplit(w[b], x, acc[b]);
+  }
   static __device__ __forceinline__ void states(const acc_t (&acc)[MB], sum_t (&br)[NS], sum_t (&bi)[NS]) {
 #pragma unroll
     for (int b = 0; b < MB; ++b) {
       br[2 * b] = acc[b][0]; bi[2 * b] = acc[b][1];
       if (2 * b + 1 < NS) { br[2 * b + 1] = acc[b][2]; bi[2 * b + 1] = acc[b][3]; }
     }
-  }
-  __device__ __forceinline__ void operator()(const double (&d)[4], const v6i& x, sum_t (&br)[NS], sum_t (&bi)[NS]) const {
-    acc_t acc[MB] = {};
-    add(d, x, acc);
-    states(acc, br, bi);
   }
 };
 

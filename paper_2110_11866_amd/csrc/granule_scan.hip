@@ -28,7 +28,9 @@
 //
 // Zeros of T meet inputs of the same run at later positions: where a run has an infinite or NaN input,
 // the product takes zero for it and its outputs from that position on are set to NaN, so no output
-// depends on a later input.
+// depends on a later input. A wave with such inputs, or finite ones so large that their nearest bfloat16 is
+// infinite, repeats its products in float32. The states are held at half their size (the weights P at half, C
+// at twice theirs): one that is finite in float32 always has thirds.
 #include <hip/hip_runtime.h>
 
 #include "granule.h"
@@ -159,38 +161,50 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
       double gr[NS], gi[NS];
 #pragma unroll
       for (int s = 0; s < NS; ++s) { gr[s] = td[lay.dG(1, s, 0) + q]; gi[s] = td[lay.dG(1, s, 1) + q]; }
-      Quad<IN> y;
-      int64_t p = js - kGran * nw;
-      y.load(xs, p, lo, N, N, lane);
-      for (int64_t i = 0; i < nw; ++i) {
+      auto window = [&](auto split) {   // returns whether some input had no thirds
+        Quad<IN> y;
+        int64_t p = js - kGran * nw;
+        uint32_t top = 0;
+        y.load(xs, p, lo, N, N, lane);
+        for (int64_t i = 0; i < nw; ++i) {
 #pragma unroll
-        for (int t = 0; t < ST; ++t) *reinterpret_cast<v4f*>(s_y[t] + w1) = y.f32(t);
-        p += kGran;
-        if (i + 1 < nw) y.load(xs, p, lo, N, N, lane);
-        lds_order();
-        v4f ya[ST];
+          for (int t = 0; t < ST; ++t) *reinterpret_cast<v4f*>(s_y[t] + w1) = y.f32(t);
+          p += kGran;
+          if (i + 1 < nw) y.load(xs, p, lo, N, N, lane);
+          lds_order();
+          v4f ya[ST];
 #pragma unroll
-        for (int t = 0; t < ST; ++t) ya[t] = *reinterpret_cast<const v4f*>(s_y[t] + rslot);
-        lds_order();
-        typename Sums::acc_t acc[Sums::MB] = {};
+          for (int t = 0; t < ST; ++t) ya[t] = *reinterpret_cast<const v4f*>(s_y[t] + rslot);
+          lds_order();
+          typename Sums::acc_t acc[Sums::MB] = {};
 #pragma unroll
-        for (int t = 0; t < ST; ++t) {
-          const double d[4] = {(double)ya[t][0], (double)ya[t][1], (double)ya[t][2], (double)ya[t][3]};
-          v6i x = {};
-          if constexpr (!WIDE) {
+          for (int t = 0; t < ST; ++t) {
+            const double d[4] = {(double)ya[t][0], (double)ya[t][1], (double)ya[t][2], (double)ya[t][3]};
             const float f[4] = {ya[t][0], ya[t][1], ya[t][2], ya[t][3]};
-            x = thirds(f);
+            if constexpr (WIDE) {
+              run_sums[t].add(d, v6i{}, acc);
+            } else if constexpr (decltype(split)::value) {
+              keep_top(top, f);
+              run_sums[t].add(d, thirds(f), acc);
+            } else {
+              run_sums[t].add_unsplit(f, acc);
+            }
           }
-          run_sums[t].add(d, x, acc);
-        }
-        sum_t br[NS], bi[NS];
-        Sums::states(acc, br, bi);
+          sum_t br[NS], bi[NS];
+          Sums::states(acc, br, bi);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {   // per column: z <- a^256 z + B
-          double xr = br[s], xi = bi[s];
-          mac(gr[s], gi[s], zr[s], zi[s], xr, xi);
-          zr[s] = xr; zi[s] = xi;
+          for (int s = 0; s < NS; ++s) {   // per column: z <- a^256 z + B
+            double xr = br[s], xi = bi[s];
+            mac(gr[s], gi[s], zr[s], zi[s], xr, xi);
+            zr[s] = xr; zi[s] = xi;
+          }
         }
+        return no_thirds(top);
+      };
+      if (window(std::true_type{})) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) { zr[s] = 0; zi[s] = 0; }
+        window(std::false_type{});
       }
       // sum over the columns, weighted a^{16 (15 - c)}
 #pragma unroll
@@ -244,7 +258,7 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
     v6i dx[WIDE ? 1 : ST][NST];
     sum_t br[NST][NS], bi[NST][NS];
     double er[NS], ei[NS];
-    bool odd = false;   // some input is infinite or NaN (or a run's sum overflows)
+    uint32_t top = 0;
 #pragma unroll
     for (int i = 0; i < NST; ++i) {
       typename Sums::acc_t acc[Sums::MB] = {};
@@ -263,31 +277,27 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
             f[k] = fmaf(-Df, b[k], a[k]);
           }
         }
-        odd = odd || !__builtin_isfinite((f[0] + f[1]) + (f[2] + f[3]));
+        keep_top(top, f);
         if constexpr (!WIDE) dx[t][i] = thirds(f);
         run_sums[t].add(d, dx[WIDE ? 0 : t][i], acc);
         __builtin_amdgcn_sched_barrier(0);   // a run at a time (registers)
       }
       Sums::states(acc, br[i], bi[i]);
     }
-    const bool slow = __ballot(odd) != 0;
-    if (slow) {   // the run product sees zeros for those inputs (below), the run sums have seen them
+    const bool slow = no_thirds(top);
+    if (!WIDE && slow) {   // the run sums of the inputs as they are
 #pragma unroll
-      for (int t = 0; t < ST; ++t)
+      for (int i = 0; i < NST; ++i) {
+        typename Sums::acc_t acc[Sums::MB] = {};
 #pragma unroll
-        for (int i = 0; i < NST; ++i) {
+        for (int t = 0; t < ST; ++t) {
           float f[4];
           differences(t, i, f);
-#pragma unroll
-          for (int k = 0; k < 4; ++k) f[k] = __builtin_isfinite(f[k]) ? f[k] : 0.0f;
-          if constexpr (WIDE) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) df[t][i][k] = f[k];
-          } else {
-            dx[t][i] = thirds(f);
-          }
+          run_sums[t].add_unsplit(f, acc);
           __builtin_amdgcn_sched_barrier(0);
         }
+        Sums::states(acc, br[i], bi[i]);
+      }
     }
     {
       double fr[NS], fi[NS];   // sum over the column's runs; the carry enters column 0
@@ -325,23 +335,18 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
     for (int i = 0; i < NST; ++i) {
       v4f o[NC];
       v6i sx[SETS];
-#pragma unroll
-      for (int e = 0; e < SETS; ++e) {
-        float x[4];
+      auto components = [&](int e, float (&x)[4]) {   // states 2 e, 2 e + 1 in float32
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const int s = 2 * e + k / 2;
           x[k] = s < NS ? (float)(k & 1 ? ei[s < NS ? s : 0] : er[s < NS ? s : 0]) : 0.0f;
         }
-        sx[e] = thirds(x);
-      }
-      if (i + 1 < NST) {
+      };
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {   // on to the next run of the column
-          double xr = br[i][s], xi = bi[i][s];
-          mac(ar[s], ai[s], er[s], ei[s], xr, xi);
-          er[s] = xr; ei[s] = xi;
-        }
+      for (int e = 0; e < SETS; ++e) {
+        float x[4];
+        components(e, x);
+        sx[e] = thirds(x);
       }
 #pragma unroll
       for (int k = 0; k < NC; ++k) {
@@ -360,7 +365,26 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
           o[k] = product(dx[k % ST][i], T[k], o[k]);
         }
       }
-      if (slow) {
+      if (slow) {   // from the inputs and states as they are; infinite and NaN inputs count as zeros
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+          float f[4];
+          differences(k % ST, i, f);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) f[v] = __builtin_isfinite(f[v]) ? f[v] : 0.0f;
+          const float* b = s_b[k % ST] + i * PS;
+          __builtin_amdgcn_sched_barrier(0);
+          o[k] = product_unsplit(f, T[k], v4f{Y[k] * b[bslot0], Y[k] * b[bslot0 + 16], Y[k] * b[bslot1], Y[k] * b[bslot1 + 16]});
+        }
+#pragma unroll
+        for (int e = 0; e < SETS; ++e) {
+          float x[4];
+          __builtin_amdgcn_sched_barrier(0);
+          components(e, x);
+          sx[e] = v6i{};
+#pragma unroll
+          for (int k = 0; k < NO; ++k) o[k] = product_unsplit(x, C[k][e], o[k]);
+        }
         // an infinite or NaN input reaches the outputs of its run from its own position on: bit 16 q' + c'
         // of bad marks input 4 q' + e of column c'
 #pragma unroll 1
@@ -383,6 +407,14 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
             if ((upto >> (4 * q + v)) & 1)
 #pragma unroll
               for (int k = 0; k < NC; ++k) o[k][v] = __builtin_nanf("");
+        }
+      }
+      if (i + 1 < NST) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {   // on to the next run of the column
+          double xr = br[i][s], xi = bi[i][s];
+          mac(ar[s], ai[s], er[s], ei[s], xr, xi);
+          er[s] = xr; ei[s] = xi;
         }
       }
 #pragma unroll

@@ -401,6 +401,9 @@ void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, dou
   const double s = mode == 1 ? std::exp(-(double)n0 * (double)n0 / (2.0 * sigma * sigma)) : 1.0;
   const double gre = mode == 1 && okind == 0 ? s * std::cos(xi * (double)n0) : s;
   const double gim = mode == 1 && okind == 0 ? s * std::sin(xi * (double)n0) : 0.0;
+  // Run sums, and so all states, are held at half their size, and their output weights at twice it: a state that
+  // is finite in float32 is then below the values whose nearest bfloat16 is infinite.
+  const double kHeld = 0.5;
   // output: (gre + i gim)(A - iB) for the wavelet, gre (A - B) for real output, with
   // A = cx y + sum_t mw_t Re v_t, B = sum_t lw_t Im v_t; weights of Re v, Im v per component
   double T[2][kRun] = {}, cx = 0;
@@ -420,14 +423,16 @@ void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, dou
       // run sums: input r = 15 - d; lane 16 (r / 4) + row, block kb = r % 4
       const int r = kRun - 1 - d, b = slot / 2, lq = 16 * (r / 4), kb = r % 4;
       const int v = 2 * (slot % 2);   // result registers v, v + 1 of lane row q: rows q + 4 v, q + 4 (v + 1)
-      td[lay.dP(b, kb) + lq + q + 4 * v] = re;
-      td[lay.dP(b, kb) + lq + q + 4 * (v + 1)] = im;
+      td[lay.dP(b, kb) + lq + q + 4 * v] = kHeld * re;
+      td[lay.dP(b, kb) + lq + q + 4 * (v + 1)] = kHeld * im;
       for (int c = 0; c < 2; ++c) {
-        td[lay.dPA(c, b, kb) + lq + q + 4 * v] = wr[c] * re + wi[c] * im;
-        td[lay.dPA(c, b, kb) + lq + q + 4 * (v + 1)] = wr[c] * im - wi[c] * re;
+        td[lay.dPA(c, b, kb) + lq + q + 4 * v] = kHeld * (wr[c] * re + wi[c] * im);
+        td[lay.dPA(c, b, kb) + lq + q + 4 * (v + 1)] = kHeld * (wr[c] * im - wi[c] * re);
       }
       // outputs at position d from the state before the run
       apow(p, d + 1, L, alpha, re, im);
+      re /= kHeld;
+      im /= kHeld;
       ca[2 * slot][16 * q + d] = (float)re;
       ca[2 * slot + 1][16 * q + d] = (float)-im;
       tf[lay.fCre(2 * slot) + 16 * q + d] = (float)(wr[0] * re + wi[0] * im);

@@ -79,7 +79,8 @@ struct Quad {
 };
 
 // Four float32 values as bfloat16 thirds, middle, high, low (two registers each): every value is the
-// exact sum of its thirds, if its nearest bfloat16 is finite (no_thirds). The remainder after a third is one
+// exact sum of its thirds, if its nearest bfloat16 is finite and the lowest third does not vanish
+// (no_thirds). The remainder after a third is one
 // dot product with (-1, 0) or (0, -1).
 __device__ __forceinline__ int bf16_pair(float a, float b) {
   return __builtin_bit_cast(int, __builtin_convertvector(v2f{a, b}, v2b));
@@ -107,8 +108,12 @@ __device__ __forceinline__ void keep_top(uint32_t& top, const float (&x)[4]) {
   top = m > top ? m : top;
 }
 // Whether some value of the wave's is infinite, NaN or so near the end of the range that its high third may be
-// infinite.
-__device__ __forceinline__ bool no_thirds(uint32_t top) { return __ballot(top >= __float_as_uint(0x1p126f)) != 0; }
+// infinite, or all are so small (not all zero) that their low thirds fall below bfloat16's smallest value, 2^-133:
+// from 2^-110 down thirds are not exact (signals of 1e-36 gave outputs off by 3e-5).
+__device__ __forceinline__ bool no_thirds(uint32_t top) {
+  return __ballot(top >= __float_as_uint(0x1p126f)) != 0 ||
+         (__ballot(top >= __float_as_uint(0x1p-106f)) == 0 && __ballot(top != 0) != 0);
+}
 // Weights of four inputs per lane as thirds: middle, high, low.
 struct Weights {
   v6i w;

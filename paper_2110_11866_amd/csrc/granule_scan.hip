@@ -28,8 +28,8 @@
 //
 // Zeros of T meet inputs of the same run at later positions: where a run has an infinite or NaN input,
 // the product takes zero for it and its outputs from that position on are set to NaN, so no output
-// depends on a later input. A wave with such inputs, or finite ones so large that their nearest bfloat16 is
-// infinite, repeats its products in float32. The states are held at half their size (the weights P at half, C
+// depends on a later input. A wave with such inputs, with finite ones so large that their nearest bfloat16 is
+// infinite, or with nothing but values below 2^-106, repeats its products in float32. The states are held at half their size (the weights P at half, C
 // at twice theirs): one that is finite in float32 always has thirds.
 #include <hip/hip_runtime.h>
 

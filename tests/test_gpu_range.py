@@ -86,3 +86,19 @@ def test_largest_states(N, sigma, L):
         y[at:at + 2] = 1.6995e38
         got = plan.forward(torch.from_numpy(y).cuda()).cpu().numpy()
         assert _rel(got, O.forward(y.astype(np.float64), p)) <= TOL[N]
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e-33, 1e-35, 1e-36])
+@pytest.mark.parametrize("mode", ["sft", "asft"])
+@pytest.mark.parametrize("N,sigma,L", SIZES)
+def test_smallest_values(N, sigma, L, mode, scale):
+    # a whole signal (its first part zero) near the lower end: as accurate as at any other size
+    for kind in ("morlet", "gauss"):
+        _say("smallest", kind, N, mode, scale)
+        plan, p = _plans(kind, N, sigma, L, mode)
+        x = (np.random.default_rng(8).standard_normal(N) * scale).astype(np.float32)
+        x[:N // 3] = 0
+        got = plan.forward(torch.from_numpy(x).cuda()).cpu().numpy()
+        assert _rel(got / scale, O.forward(x.astype(np.float64), p) / scale) <= TOL[N]
+        gx = plan.backward(None, torch.from_numpy(x.astype(got.dtype)).cuda(), want_params=False)[0].cpu().numpy()
+        assert _rel(gx / scale, O.adjoint(x.astype(np.complex128), p) / scale) <= TOL[N]

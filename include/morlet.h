@@ -311,7 +311,8 @@ morlet_status morlet_plan_set_boundary(morlet_plan_t plan, morlet_boundary bound
  * summing the window before it, so no wave waits on another and the workspace is not used; float64
  * states), or, for rows of one length whose window is much longer than a piece, the carried scan (two
  * launches, the first for the pieces' sums, 16 K bytes each in the workspace), for the forward and the adjoint
- * (not of an edge-extended signal); else rows when the longest row has no
+ * (not of an edge-extended signal), where its estimated time is below the tile scan's (it is not for several
+ * scales with windows much longer than the pieces); else rows when the longest row has no
  * more tiles than one block's share of all tiles; else segments (forward) for at most eight rows with at
  * least two tiles per resident block; else tiles. The schedules are deterministic; they differ
  * in the float64 rounding of the carried states and in how float32 rounding enters the outputs. The gradient
@@ -390,7 +391,8 @@ morlet_status morlet_plan_info(morlet_plan_t plan, int64_t* L, int32_t* P_S, int
  * only, not the multiplication method. Errors: as morlet_forward / morlet_scalogram_forward
  * (MORLET_ERR_INVALID_ARG for a plan that is not a Morlet plan, MORLET_ERR_UNSUPPORTED for edge
  * extension, multiplication-method and image plans); MORLET_ERR_WORKSPACE, with nothing
- * launched, when the launch needs more than the array: the granule scan needs none, the carried
+ * launched, when the launch needs more than the array (where the granule scan applies it is then taken, whatever
+ * its time): the granule scan needs none, the carried
  * scan 64 bytes plus 16 K per piece (at most one per compute unit), the row-serial schedule of a scalogram 64 bytes, the tiles schedule 64 bytes plus one tile state per tile of 256 R positions
  * (256 bytes at K <= 5, 640 at K = 12), so a single signal of up to about 2^27 samples at K = 5,
  * R = 16; the segments schedule 64 bytes plus

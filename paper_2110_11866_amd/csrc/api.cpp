@@ -215,7 +215,7 @@ void build_gran_segs(morlet_plan_s* p) {
     else shapes.push_back(g);
   }
   if (shapes.empty() || ng_max > INT32_MAX) return;
-  const mk::GranSplit split = mk::split_granules(shapes, p->num_cus);
+  const mk::GranSplit split = p->gran_split = mk::split_granules(shapes, p->num_cus);
   const int nq = mk::kQueues;
   const bool by_signal = (int64_t)p->B >= 4 * nq;
   std::vector<int> order(p->B);
@@ -422,9 +422,10 @@ morlet_status init_morlet_rows(morlet_plan_s* p, int B, int64_t len, double sigm
 }
 
 // Granule scan, or carried scan (a.gran_sums set): a forward or adjoint launch under the automatic schedule
-// and tile shape, float32 or mixed accumulation. Returns whether the launch takes one (a.row0 set for a
-// single row, a.ws and a.ntiles set).
-bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant) {
+// and tile shape, float32 or mixed accumulation, where its estimated time is below the tile scan's. Returns
+// whether the launch takes one (a.row0 set for a single row, a.ws and a.ntiles set). least_scratch: the granule
+// scan, which needs none, whatever its time.
+bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant, bool least_scratch = false) {
   a.gran_nseg = 0;
   a.gran_sums = nullptr;
   // not for the adjoint of an edge-extended row: its fold adds up 2L outputs whose sum is smaller by
@@ -435,8 +436,11 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant) {
     return false;
   a.gran_tabs = a.tabs + mk::TabLayout{plan->K, plan->R}.bytes();
   const int64_t nrows = plan->batched ? (int64_t)plan->rows.size() : 1;
+  const bool adj = variant == mk::kVarAdjoint, wide = a.acc == mk::kAccMixed;
+  const double tiles = mk::tiles_us(a.ntiles, a.kind, adj, plan->K, plan->num_cus);
   if (plan->batched && !equal_rows(plan)) {
     if (plan->gran_segs.empty() || plan->gran_segs.size() > (size_t)INT32_MAX) return false;
+    if (!least_scratch && mk::granule_us(plan->gran_split, a.kind, adj, wide, plan->K, plan->num_cus) > tiles) return false;
     const size_t rb = plan->rows.size() * sizeof(mk::Row);
     const size_t lists = (plan->tile_row.size() + plan->row_order.size()) * sizeof(int32_t);
     a.gran_segs = reinterpret_cast<const mk::GranSeg*>(static_cast<const char*>(plan->d_rows) + (rb + lists + 15) / 16 * 16);
@@ -453,17 +457,21 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant) {
   const int64_t n = split.piece(nw), ns = (ng + n - 1) / n;
   if (ns * nrows > INT32_MAX) return false;
   // A window much longer than a piece is summed by every piece. The carried scan sums no windows but reads
-  // the row twice, in two launches: about 8 us and 2.7 us per chunk of a block, a block per CU; the granule
-  // scan about 3 us and 1.8 us per unit of the split's cost. K = 5, us, granule | carried: N = 102400, 2L =
+  // the row twice, in two launches, a block per CU (K = 5, us, granule | carried: N = 102400, 2L =
   // 2664: 7 | 10.5, 10650: 15 | 10.2, 42600: 47 | 10.6; N = 2^22, 2L = 10650: 32 | 35, 42600: 72 | 35; N =
-  // 2^24, 2L = 10650: 66 | 96, 42600: 119 | 101. (The tiles schedule, whose tiles wait for the states of the
-  // tiles before them, takes 17, 60 and 111 us there.) The pieces' sums lie in the workspace after its
+  // 2^24, 2L = 10650: 66 | 96, 42600: 119 | 101; the tiles schedule, whose tiles wait for the states of the
+  // tiles before them, takes 17, 60 and 111 us there); it is taken where its estimate is a tenth below the
+  // granule scan's, which is the surer of the two. With so many rows that each is a piece, the tile scan wins
+  // (200 rows of 50000, 2L = 48000, K = 9: 136 us, carried 266). The pieces' sums lie in the workspace after its
   // header, within what the tiles schedule needs.
   const int64_t all = mk::chunks_for(row.N, row.jout0), most = std::min<int64_t>(all, std::max<int64_t>(1, plan->num_cus / nrows));
   const int64_t len = (all + most - 1) / most, np = (all + len - 1) / len;
   const int64_t rounds = (np * nrows + plan->num_cus - 1) / plan->num_cus;
-  if (3.0 + 1.8 * split.cost > 8.0 + 2.7 * (double)(len * rounds)) {
-    const int states = plan->K * (variant == mk::kVarAdjoint && a.kind == 0 ? 2 : 1);
+  const double granules = mk::granule_us(split, a.kind, adj, wide, plan->K, plan->num_cus);
+  const double carried = 1.1 * mk::carried_us(len * rounds, a.kind, adj, wide, plan->K);
+  if (!least_scratch && tiles < granules && tiles < carried) return false;
+  if (!least_scratch && carried < granules) {
+    const int states = plan->K * (adj && a.kind == 0 ? 2 : 1);
     if (nrows > 65535 || len > INT32_MAX ||
         (size_t)((np - 1) * nrows) * states * 16 > mk::tile_state_bytes(states) * (size_t)a.ntiles)
       return false;
@@ -491,7 +499,7 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant) {
 // accumulation it runs the mixed scan (float64 chunk sums), whose rounding stays below what the
 // float64 gradient reductions resolve.
 morlet_status make_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int variant, int mom, int dtype,
-                          bool recompute = false) {
+                          bool recompute = false, bool least_scratch = false) {
   if (const morlet_status inj = injected(); inj != MORLET_OK) return inj;
   const int64_t jend = plan->N + plan->L - plan->n0;
   const int64_t ntiles = plan->batched ? plan->ntiles : tiles_for(jend, plan->R);
@@ -540,7 +548,7 @@ morlet_status make_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int v
   a.f32_bytes = (int64_t)mk::TabLayout{plan->K, plan->R}.f32Bytes();
   a.ws = ws;
   a.dtype = dtype;
-  if (gran_launch(plan, a, variant)) return MORLET_OK;
+  if (gran_launch(plan, a, variant, least_scratch)) return MORLET_OK;
   const int occ = mk::scan_occupancy(a.K, a.R, variant, a.acc, a.kind, mom, dtype);
   if (occ <= 0) return fail(MORLET_ERR_UNSUPPORTED, "no kernel for this configuration");
   const int64_t cap = (int64_t)occ * plan->num_cus;
@@ -2223,7 +2231,12 @@ morlet_status morlet_forward_noalloc(morlet_plan_t plan, const void* x, morlet_d
   mk::ScanLaunch a;
   morlet_status st = make_launch(plan, a, ws, mk::kVarForward, 0, (int)dtype);
   if (st != MORLET_OK) return st;
-  const size_t need = launch_ws_bytes(a, plan->K, ntiles);
+  size_t need = launch_ws_bytes(a, plan->K, ntiles);
+  if (need > mk::kScratchBytes) {
+    st = make_launch(plan, a, ws, mk::kVarForward, 0, (int)dtype, false, true);
+    if (st != MORLET_OK) return st;
+    need = launch_ws_bytes(a, plan->K, ntiles);
+  }
   if (need > mk::kScratchBytes)
     return fail(MORLET_ERR_WORKSPACE, "the launch needs " + std::to_string(need) +
                                           " bytes of workspace, more than the fixed scratch of " +

@@ -526,22 +526,56 @@ GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus, double k
       GranSplit t;
       t.base = base;
       t.per_warm = pw;
-      double work = 0, longest = 0;
+      double longest = 0;
       for (const GranRow& r : rows) {
         const int64_t n = t.piece(r.nw), ns = (r.ng + n - 1) / n;
         // windows before the first piece's end reach the row's start
-        const double full = kWarm * (double)r.nw;
-        double warm = 0;
         const int64_t part = std::min<int64_t>(ns, r.nw / n + 1);   // pieces whose window is cut short
-        warm += kWarm * (double)n * 0.5 * (double)(part - 1) * (double)part;
-        warm += full * (double)(ns - part);
-        work += (double)r.count * ((double)r.ng + warm);
-        longest = std::max(longest, (double)std::min(n, r.ng) + (ns > part ? full : kWarm * (double)n * (double)(part - 1)));
+        t.out += (double)r.count * (double)r.ng;
+        t.window += (double)r.count * ((double)n * 0.5 * (double)(part - 1) * (double)part + (double)r.nw * (double)(ns - part));
+        const double o = (double)std::min(n, r.ng), w = ns > part ? (double)r.nw : (double)n * (double)(part - 1);
+        if (o + kWarm * w > longest) {
+          longest = o + kWarm * w;
+          t.wave_out = o;
+          t.wave_window = w;
+        }
       }
-      t.cost = std::max(work / slots, kAlone * longest) + 0.25 * longest;
+      t.cost = std::max((t.out + kWarm * t.window) / slots, kAlone * longest) + 0.25 * longest;
       if (best.cost < 0 || t.cost < best.cost) best = t;
     }
   return best;
+}
+
+// The three ways' measured times, fitted over 2400 calls in both directions (1 to 1000 rows of 2^13 to 2^24
+// samples, 1 to 16 scales, K 4 to 12, windows from 1/256 of a row to a whole one), to 10-20 %. A wave's own chain
+// bounds the granule scan in short launches, the issue of all waves in long ones; where windows are long against the
+// pieces both are mostly windows (one signal of 2^20, 2 scales, 2L up to 2^18, K = 5: 915 us, the tile scan 40).
+// Chosen by the least estimate, 1 call in 100 takes more than 1.05 of the tile scan's time.
+double granule_us(const GranSplit& s, int kind, bool adjoint, bool wide, int K, int num_cus) {
+  struct Us { double base, out, window, all_out, all_window; };   // a wave's granule, a granule of four waves per SIMD
+  static const Us us[3][2][2] = {   // real, complex forward, complex adjoint; float64 run sums; K > 8
+      {{{3.7, 1.1, 0.24, 0.1, 0.66}, {4.2, 0.68, 0.27, 1.5, 0.75}}, {{3.9, 0.77, 0.30, 2.8, 0.53}, {4.5, 0.25, 0.43, 7.7, 0.60}}},
+      {{{4.2, 0.05, 0.23, 2.6, 0.84}, {4.5, 0.05, 0.27, 4.2, 1.0}}, {{4.2, 0.05, 0.29, 2.8, 1.2}, {4.5, 0.05, 0.41, 4.8, 1.9}}},
+      {{{5.7, 0.88, 0.36, 3.5, 1.5}, {7.5, 0.05, 0.42, 5.9, 1.9}}, {{5.8, 0.57, 0.49, 4.0, 2.3}, {7.3, 0.05, 0.72, 7.4, 3.6}}}};
+  const Us& u = us[kind != 0 ? 0 : adjoint ? 2 : 1][wide][K > 8];
+  const double slots = 16.0 * num_cus;
+  return u.base + std::hypot(u.out * s.wave_out + u.window * s.wave_window, (u.all_out * s.out + u.all_window * s.window) / slots);
+}
+
+double carried_us(int64_t chunks, int kind, bool adjoint, bool wide, int K) {
+  struct Us { double base, chunk; };
+  static const Us us[3][2][2] = {{{{7.4, 2.2}, {8.9, 3.0}}, {{7.3, 2.4}, {9.0, 3.5}}},
+                                 {{{7.8, 1.5}, {10.4, 2.1}}, {{8.0, 1.7}, {10.6, 2.5}}},
+                                 {{{8.6, 2.3}, {11.4, 3.6}}, {{8.8, 2.9}, {12.1, 4.4}}}};
+  const Us& u = us[kind != 0 ? 0 : adjoint ? 2 : 1][wide][K > 8];
+  return u.base + u.chunk * (double)chunks;
+}
+
+double tiles_us(int64_t ntiles, int kind, bool adjoint, int K, int num_cus) {
+  struct Us { double base, base_k, tile, tile_k; };   // per term; per tile of 4096 positions on 256 CUs
+  static const Us us[3] = {{11.0, 0.76, 0.025, 0.0023}, {12.2, 0.60, 0.020, 0.0016}, {12.4, 1.6, 0.0002, 0.0086}};
+  const Us& u = us[kind != 0 ? 0 : adjoint ? 2 : 1];
+  return u.base + u.base_k * K + (u.tile + u.tile_k * K) * (double)ntiles * 256.0 / num_cus;
 }
 
 void set_split(morlet_plan_s* p, int64_t N, int64_t L, int64_t count) {

@@ -14,6 +14,8 @@ struct GranSplit {
   int64_t base = 1;      // granules per piece, at least
   double per_warm = 0;   // and at least this many per granule of the window
   double cost = 0;       // estimated time of the launch, in granule times of a wave on a full device
+  double out = 0, window = 0;             // granules of all pieces, with outputs and of the windows before them
+  double wave_out = 0, wave_window = 0;   // of the longest wave
   int64_t piece(int64_t nw) const;   // even with two()
   // two granules at a time: halves the scans across lanes, but starts and ends cost more; from pieces of
   // eight granules on (4096^2 image, pieces of four: 98 us with two, 93 with one)
@@ -138,6 +140,11 @@ struct GranRow {
 };
 // warm: cost of a window granule relative to one with outputs.
 GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus, double warm = 0.3);
+// Estimated times in us of a launch's three ways. kind: the launch's (0 complex output, else real); wide: float64
+// run sums (the mixed scan).
+double granule_us(const GranSplit& s, int kind, bool adjoint, bool wide, int K, int num_cus);
+double carried_us(int64_t chunks, int kind, bool adjoint, bool wide, int K);   // chunks that a CU runs in turn
+double tiles_us(int64_t ntiles, int kind, bool adjoint, int K, int num_cus);
 // The split of `count` rows of N samples with half width L, kept in the plan.
 void set_split(morlet_plan_s* p, int64_t N, int64_t L, int64_t count);
 

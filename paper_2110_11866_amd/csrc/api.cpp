@@ -424,8 +424,9 @@ morlet_status init_morlet_rows(morlet_plan_s* p, int B, int64_t len, double sigm
 // Granule scan, or carried scan (a.gran_sums set): a forward or adjoint launch under the automatic schedule
 // and tile shape, float32 or mixed accumulation, where its estimated time is below the tile scan's. Returns
 // whether the launch takes one (a.row0 set for a single row, a.ws and a.ntiles set). least_scratch: the granule
-// scan, which needs none, whatever its time.
-bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant, bool least_scratch = false) {
+// scan, which needs none, whatever its time. least_us: the least estimate, left alone where the launch is not one
+// of the automatic choice.
+bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant, bool least_scratch = false, double* least_us = nullptr) {
   a.gran_nseg = 0;
   a.gran_sums = nullptr;
   // not for the adjoint of an edge-extended row: its fold adds up 2L outputs whose sum is smaller by
@@ -440,7 +441,8 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant, bool least_
   const double tiles = mk::tiles_us(a.ntiles, a.kind, adj, plan->K, plan->num_cus);
   if (plan->batched && !equal_rows(plan)) {
     if (plan->gran_segs.empty() || plan->gran_segs.size() > (size_t)INT32_MAX) return false;
-    if (!least_scratch && mk::granule_us(plan->gran_split, a.kind, adj, wide, plan->K, plan->num_cus) > tiles) return false;
+    const double granules = mk::granule_us(plan->gran_split, a.kind, adj, wide, plan->K, plan->num_cus);
+    if (!least_scratch && granules > tiles) return false;
     const size_t rb = plan->rows.size() * sizeof(mk::Row);
     const size_t lists = (plan->tile_row.size() + plan->row_order.size()) * sizeof(int32_t);
     a.gran_segs = reinterpret_cast<const mk::GranSeg*>(static_cast<const char*>(plan->d_rows) + (rb + lists + 15) / 16 * 16);
@@ -460,15 +462,16 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant, bool least_
   // the row twice, in two launches, a block per CU (K = 5, us, granule | carried: N = 102400, 2L =
   // 2664: 7 | 10.5, 10650: 15 | 10.2, 42600: 47 | 10.6; N = 2^22, 2L = 10650: 32 | 35, 42600: 72 | 35; N =
   // 2^24, 2L = 10650: 66 | 96, 42600: 119 | 101; the tiles schedule, whose tiles wait for the states of the
-  // tiles before them, takes 17, 60 and 111 us there); it is taken where its estimate is a tenth below the
-  // granule scan's, which is the surer of the two. With so many rows that each is a piece, the tile scan wins
+  // tiles before them, takes 17, 60 and 111 us there); it is taken where its estimate is a little below the
+  // granule scan's, the surer of the two. With so many rows that each is a piece, the tile scan wins
   // (200 rows of 50000, 2L = 48000, K = 9: 136 us, carried 266). The pieces' sums lie in the workspace after its
   // header, within what the tiles schedule needs.
   const int64_t all = mk::chunks_for(row.N, row.jout0), most = std::min<int64_t>(all, std::max<int64_t>(1, plan->num_cus / nrows));
   const int64_t len = (all + most - 1) / most, np = (all + len - 1) / len;
-  const int64_t rounds = (np * nrows + plan->num_cus - 1) / plan->num_cus;
   const double granules = mk::granule_us(split, a.kind, adj, wide, plan->K, plan->num_cus);
-  const double carried = 1.1 * mk::carried_us(len * rounds, a.kind, adj, wide, plan->K);
+  const double carried =
+      1.05 * mk::carried_us((double)len * std::max(1.0, (double)(np * nrows) / plan->num_cus), a.kind, adj, wide, plan->K);
+  if (least_us) *least_us = std::min(tiles, std::min(granules, carried));
   if (!least_scratch && tiles < granules && tiles < carried) return false;
   if (!least_scratch && carried < granules) {
     const int states = plan->K * (adj && a.kind == 0 ? 2 : 1);
@@ -499,7 +502,7 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant, bool least_
 // accumulation it runs the mixed scan (float64 chunk sums), whose rounding stays below what the
 // float64 gradient reductions resolve.
 morlet_status make_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int variant, int mom, int dtype,
-                          bool recompute = false, bool least_scratch = false) {
+                          bool recompute = false, bool least_scratch = false, double* least_us = nullptr) {
   if (const morlet_status inj = injected(); inj != MORLET_OK) return inj;
   const int64_t jend = plan->N + plan->L - plan->n0;
   const int64_t ntiles = plan->batched ? plan->ntiles : tiles_for(jend, plan->R);
@@ -548,7 +551,7 @@ morlet_status make_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int v
   a.f32_bytes = (int64_t)mk::TabLayout{plan->K, plan->R}.f32Bytes();
   a.ws = ws;
   a.dtype = dtype;
-  if (gran_launch(plan, a, variant, least_scratch)) return MORLET_OK;
+  if (gran_launch(plan, a, variant, least_scratch, least_us)) return MORLET_OK;
   const int occ = mk::scan_occupancy(a.K, a.R, variant, a.acc, a.kind, mom, dtype);
   if (occ <= 0) return fail(MORLET_ERR_UNSUPPORTED, "no kernel for this configuration");
   const int64_t cap = (int64_t)occ * plan->num_cus;
@@ -601,18 +604,25 @@ morlet_status make_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int v
 }
 
 // The launch of an image's second axis (plan: its batched plan over lines of length H) down the columns
-// of an H x cols float32 matrix, where the granule scan would take its lines (taken = true). A wave
+// of an H x cols float32 matrix, under the automatic schedule where that is estimated to take less time than
+// its lines between two transposes (taken = true). A wave
 // runs 32 columns; pieces of the rows fill the device, two waves per SIMD (four, with shorter pieces and
 // more windows, 94 against 92 us a 4096 x 4096 image). With 16-row runs the sums over the window before a
 // piece cost about half of a run with outputs.
 morlet_status column_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int variant, int64_t cols, bool& taken) {
   taken = false;
-  const morlet_status st = make_launch(plan, a, ws, variant, 0, 0);
-  if (st != MORLET_OK || a.gran_nseg == 0 || a.gran_sums) return st;
+  double lines = -1;
+  const morlet_status st = make_launch(plan, a, ws, variant, 0, 0, false, false, &lines);
+  if (st != MORLET_OK || lines < 0) return st;
   const int64_t nw = (2 * plan->rows[0].L + mk::kRun - 1) / mk::kRun, ng = (plan->rows[0].N + mk::kRun - 1) / mk::kRun;
   const int64_t blocks = (cols + mk::kColWave - 1) / mk::kColWave;
   const mk::GranSplit split = mk::split_granules({{ng, nw, blocks}}, plan->num_cus / 2, 0.5);
+  // windows long against the pieces: 4000 x 500, 2L = 4000, K = 8: columns 287 us, transposed lines 54
+  if (mk::columns_us(split, plan->K, plan->num_cus) > lines + mk::transposes_us((double)plan->rows[0].N * (double)cols)) return MORLET_OK;
   const int64_t np = (ng + split.piece(nw) - 1) / split.piece(nw);
+  a.gran_nseg = 0;
+  a.gran_sums = nullptr;
+  a.gran_tabs = a.tabs + mk::TabLayout{plan->K, plan->R}.bytes();
   a.col_cols = cols;
   a.col_piece = mk::kRun * ((ng + np - 1) / np);
   if (np > 65535) a.col_piece = mk::kRun * ((ng + 65534) / 65535);

@@ -526,57 +526,81 @@ GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus, double k
       GranSplit t;
       t.base = base;
       t.per_warm = pw;
-      double longest = 0;
+      double work = 0, longest = 0;
       for (const GranRow& r : rows) {
         const int64_t n = t.piece(r.nw), ns = (r.ng + n - 1) / n;
         // windows before the first piece's end reach the row's start
         const int64_t part = std::min<int64_t>(ns, r.nw / n + 1);   // pieces whose window is cut short
-        t.out += (double)r.count * (double)r.ng;
-        t.window += (double)r.count * ((double)n * 0.5 * (double)(part - 1) * (double)part + (double)r.nw * (double)(ns - part));
         const double o = (double)std::min(n, r.ng), w = ns > part ? (double)r.nw : (double)n * (double)(part - 1);
-        if (o + kWarm * w > longest) {
-          longest = o + kWarm * w;
+        work += (double)r.count * ((double)r.ng + kWarm * ((double)n * 0.5 * (double)(part - 1) * (double)part + (double)r.nw * (double)(ns - part)));
+        longest = std::max(longest, o + kWarm * w);
+        // as the kernel sums them: the first output lies half a window past the row's start
+        const double half = 0.5 * (double)r.nw;
+        const int64_t cut = std::min<int64_t>(ns, (int64_t)(half / (double)n) + 1);
+        const double wave = ns > cut ? (double)r.nw : std::min((double)r.nw, half + (double)n * (double)(cut - 1));
+        t.out += (double)r.count * (double)r.ng;
+        t.window += (double)r.count * (half * (double)cut + (double)n * 0.5 * (double)(cut - 1) * (double)cut + (double)r.nw * (double)(ns - cut));
+        if (o + kWarm * wave > t.wave_out + kWarm * t.wave_window) {
           t.wave_out = o;
-          t.wave_window = w;
+          t.wave_window = wave;
         }
       }
-      t.cost = std::max((t.out + kWarm * t.window) / slots, kAlone * longest) + 0.25 * longest;
+      t.cost = std::max(work / slots, kAlone * longest) + 0.25 * longest;
       if (best.cost < 0 || t.cost < best.cost) best = t;
     }
   return best;
 }
 
-// The three ways' measured times, fitted over 2400 calls in both directions (1 to 1000 rows of 2^13 to 2^24
-// samples, 1 to 16 scales, K 4 to 12, windows from 1/256 of a row to a whole one), to 10-20 %. A wave's own chain
+// The three ways' measured times, fitted over 4400 calls in both directions (1 to 1000 rows of 300 to 2^25
+// samples, 1 to 16 scales, K 4 to 12, windows of 60 samples to a whole row), to 10-20 %. A wave's own chain
 // bounds the granule scan in short launches, the issue of all waves in long ones; where windows are long against the
 // pieces both are mostly windows (one signal of 2^20, 2 scales, 2L up to 2^18, K = 5: 915 us, the tile scan 40).
-// Chosen by the least estimate, 1 call in 100 takes more than 1.05 of the tile scan's time.
+// Chosen by the least estimate, 6 calls in 1000 take more than 1.05 times the tile scan's time, none 1.6.
 double granule_us(const GranSplit& s, int kind, bool adjoint, bool wide, int K, int num_cus) {
   struct Us { double base, out, window, all_out, all_window; };   // a wave's granule, a granule of four waves per SIMD
-  static const Us us[3][2][2] = {   // real, complex forward, complex adjoint; float64 run sums; K > 8
-      {{{3.7, 1.1, 0.24, 0.1, 0.66}, {4.2, 0.68, 0.27, 1.5, 0.75}}, {{3.9, 0.77, 0.30, 2.8, 0.53}, {4.5, 0.25, 0.43, 7.7, 0.60}}},
-      {{{4.2, 0.05, 0.23, 2.6, 0.84}, {4.5, 0.05, 0.27, 4.2, 1.0}}, {{4.2, 0.05, 0.29, 2.8, 1.2}, {4.5, 0.05, 0.41, 4.8, 1.9}}},
-      {{{5.7, 0.88, 0.36, 3.5, 1.5}, {7.5, 0.05, 0.42, 5.9, 1.9}}, {{5.8, 0.57, 0.49, 4.0, 2.3}, {7.3, 0.05, 0.72, 7.4, 3.6}}}};
-  const Us& u = us[kind != 0 ? 0 : adjoint ? 2 : 1][wide][K > 8];
+  static const Us us[3][2][3] = {   // real, complex forward, complex adjoint; float64 run sums; slots of states
+      {{{4, 0.8, 0.23, 1.8, 0.58}, {4.1, 0.67, 0.24, 2, 0.62}, {4.8, 0.15, 0.27, 2.8, 0.71}},
+       {{3.9, 0.74, 0.28, 2, 0.61}, {4.2, 0.59, 0.29, 2.3, 0.7}, {4.9, 0.22, 0.4, 3.6, 1.1}}},
+      {{{3.7, 0.72, 0.22, 2.2, 0.65}, {4.3, 0.29, 0.23, 2.6, 0.73}, {4.8, 0.02, 0.26, 3.7, 0.94}},
+       {{4, 0.32, 0.28, 2.4, 0.93}, {4.4, 0.02, 0.29, 2.8, 1}, {4.7, 0.02, 0.4, 4.3, 1.7}}},
+      {{{5.3, 0.87, 0.32, 2.9, 1.1}, {5.6, 0.72, 0.34, 3.2, 1.3}, {6.2, 0.02, 0.4, 4.8, 1.7}},
+       {{5.4, 0.61, 0.47, 3.3, 1.8}, {5.6, 0.42, 0.48, 3.6, 2}, {5.9, 0.02, 0.7, 6.1, 3.2}}}};
+  const Us& u = us[kind != 0 ? 0 : adjoint ? 2 : 1][wide][(K - 1) / 4];
   const double slots = 16.0 * num_cus;
   return u.base + std::hypot(u.out * s.wave_out + u.window * s.wave_window, (u.all_out * s.out + u.all_window * s.window) / slots);
 }
 
-double carried_us(int64_t chunks, int kind, bool adjoint, bool wide, int K) {
+double carried_us(double chunks, int kind, bool adjoint, bool wide, int K) {
   struct Us { double base, chunk; };
-  static const Us us[3][2][2] = {{{{7.4, 2.2}, {8.9, 3.0}}, {{7.3, 2.4}, {9.0, 3.5}}},
-                                 {{{7.8, 1.5}, {10.4, 2.1}}, {{8.0, 1.7}, {10.6, 2.5}}},
-                                 {{{8.6, 2.3}, {11.4, 3.6}}, {{8.8, 2.9}, {12.1, 4.4}}}};
-  const Us& u = us[kind != 0 ? 0 : adjoint ? 2 : 1][wide][K > 8];
-  return u.base + u.chunk * (double)chunks;
+  static const Us us[3][2][3] = {
+      {{{7.3, 1.7}, {7.5, 2.2}, {9, 2.8}},
+       {{7, 2}, {7.5, 2.4}, {9.2, 3.3}}},
+      {{{7.2, 1.5}, {7.9, 2.1}, {9.9, 2.5}},
+       {{7.1, 1.8}, {8, 2.3}, {10, 3}}},
+      {{{7.6, 2.4}, {8.5, 3.3}, {11, 4.3}},
+       {{7.6, 3}, {8.2, 4.2}, {11, 5.4}}}};
+  const Us& u = us[kind != 0 ? 0 : adjoint ? 2 : 1][wide][(K - 1) / 4];
+  return u.base + u.chunk * chunks;
 }
 
 double tiles_us(int64_t ntiles, int kind, bool adjoint, int K, int num_cus) {
   struct Us { double base, base_k, tile, tile_k; };   // per term; per tile of 4096 positions on 256 CUs
-  static const Us us[3] = {{11.0, 0.76, 0.025, 0.0023}, {12.2, 0.60, 0.020, 0.0016}, {12.4, 1.6, 0.0002, 0.0086}};
+  static const Us us[3] = {{12, 0.72, 0.013, 0.0031}, {13, 0.55, 0.015, 0.002}, {12, 1.6, -0.00056, 0.0084}};
   const Us& u = us[kind != 0 ? 0 : adjoint ? 2 : 1];
   return u.base + u.base_k * K + (u.tile + u.tile_k * K) * (double)ntiles * 256.0 / num_cus;
 }
+
+// Fitted over 900 images and their adjoints (64 x 64 to 4096 x 4096, 8 to 4096 columns, windows of 1/64 to 2 columns'
+// lengths, K = 4, 8, 12), to 20 %: the least of columns and transposed lines is then chosen but for 5 in 100.
+double columns_us(const GranSplit& s, int K, int num_cus) {
+  struct Us { double base, out, window, all_out, all_window; };   // a wave's run, a run of two waves per SIMD
+  static const Us us[3] = {{3.6, 1.2, 0.8, 3.8, 0.72}, {3.1, 2.2, 0.81, 2.8, 0.71}, {5.6, 0.01, 1, 6.8, 1.6}};
+  const Us& u = us[(K - 1) / 4];
+  const double slots = 8.0 * num_cus;
+  return u.base + std::hypot(u.out * s.wave_out + u.window * s.wave_window, (u.all_out * s.out + u.all_window * s.window) / slots);
+}
+
+double transposes_us(double cells) { return 19 + 4.6e-6 * cells; }
 
 void set_split(morlet_plan_s* p, int64_t N, int64_t L, int64_t count) {
   p->gran_ng = granules_for(N);

@@ -143,8 +143,12 @@ GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus, double w
 // Estimated times in us of a launch's three ways. kind: the launch's (0 complex output, else real); wide: float64
 // run sums (the mixed scan).
 double granule_us(const GranSplit& s, int kind, bool adjoint, bool wide, int K, int num_cus);
-double carried_us(int64_t chunks, int kind, bool adjoint, bool wide, int K);   // chunks that a CU runs in turn
+double carried_us(double chunks, int kind, bool adjoint, bool wide, int K);   // chunks that a CU runs, in turn or at once
 double tiles_us(int64_t ntiles, int kind, bool adjoint, int K, int num_cus);
+// The column scan's, in runs of 16 rows on half the device's wave slots, and what the transposed route adds to its
+// lines' scan: two transposes of a matrix of `cells` float32 values.
+double columns_us(const GranSplit& s, int K, int num_cus);
+double transposes_us(double cells);
 // The split of `count` rows of N samples with half width L, kept in the plan.
 void set_split(morlet_plan_s* p, int64_t N, int64_t L, int64_t count);
 

@@ -66,3 +66,16 @@ def test_scalograms_with_wide_windows(lengths, widest, S, K, mode):
     ws = plan.workspace(x.device, backward=True)
     _compare((lengths[0], S, K, mode), plan,
              [lambda: plan.forward(x, out=out, ws=ws), lambda: plan.backward(None, g, want_params=False)[0]])
+
+
+@pytest.mark.parametrize("H,W,L,K", [(4000, 500, 2000, 8), (2000, 40, 1000, 12), (20000, 16, 1250, 4), (1080, 1920, 30, 4)])
+def test_images_with_wide_windows(H, W, L, K):
+    # down the columns every piece sums its window; between transposes the lines take the cheapest scan
+    import paper_2110_11866_amd as M
+    img = torch.from_numpy(np.random.default_rng(3).standard_normal((H, W)).astype(np.float32)).cuda()
+    for mode in ("sft", "asft"):
+        plan = M.Gauss2DPlan(H, W, L / 3.3, 2.0, K, L, max(K, 7), mode=mode)
+        _compare(("image", H, W, L, K, mode), plan, [lambda: plan.forward(img), lambda: plan.backward(img)])
+        gab = M.Gabor2DPlan(H, W, 3.0, 2.0, 5, L / 3.3, K, 9, L, mode=mode)
+        cot = torch.view_as_complex(torch.stack([img, img.flip(0)], dim=-1).contiguous())
+        _compare(("gabor", H, W, L, K, mode), gab, [lambda: gab.forward(img), lambda: gab.backward(cot)])

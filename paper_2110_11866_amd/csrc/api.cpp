@@ -497,6 +497,61 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant, bool least_
   return true;
 }
 
+// The grid and schedule of a launch of the tile scan over its rows (a.nrows, a.row0 or the plan's rows, a.ntiles and
+// a.ws set).
+morlet_status tile_schedule(morlet_plan_t plan, mk::ScanLaunch& a, int variant, int mom, int dtype) {
+  const int64_t ntiles = a.ntiles;
+  const int occ = mk::scan_occupancy(a.K, a.R, variant, a.acc, a.kind, mom, dtype);
+  if (occ <= 0) return fail(MORLET_ERR_UNSUPPORTED, "no kernel for this configuration");
+  const int64_t cap = (int64_t)occ * plan->num_cus;
+  a.grid = (int)(ntiles < cap ? ntiles : cap);
+  // Row-serial schedule when the longest row is no more than one block's share of the tiles:
+  // every block then runs whole rows, longest first, carrying the state from tile to tile
+  // in LDS, and no tile waits on another block.
+  a.serial = 0;
+  if (plan->batched && a.nrows > 1 && plan->row_serial != 0 && !(plan->row_serial == 2 && a.nrows <= mk::kQueues)) {
+    const int64_t share = (ntiles + cap - 1) / cap;
+    if (plan->row_serial == 1 || plan->max_row_tiles <= share) {
+      a.serial = 1;
+      a.grid = (int)(a.nrows < cap ? a.nrows : cap);
+    }
+  }
+  // Segments schedule for a forward launch of at most eight rows that the rows schedule did not
+  // take: chosen, or automatic when the launch has at least two tiles per resident block. About
+  // two segments per block over all rows (the ticket balances them), at most 64 x 64 tiles each
+  // (the reach of the table's look-back weights), every row cut on its own. The segment states
+  // sit in the workspace after its header (within what the tiles schedule needs).
+  a.nseg = 0;
+  if (variant == mk::kVarForward && !a.serial && a.nrows >= 1 && a.nrows <= mk::kQueues && ntiles >= 2 &&
+      (plan->row_serial == 2 || (plan->row_serial == -1 && ntiles >= 2 * cap))) {
+    // automatic length: about two segments per resident block, and at most 1024 segments per row
+    // (one round of the combination, which runs on one CU per row)
+    int64_t len = plan->seg_tiles;
+    if (len <= 0) {
+      int64_t longest = 0;
+      for (int r = 0; r < a.nrows; ++r)
+        longest = std::max<int64_t>(longest, a.nrows == 1 ? a.row0.ntiles : (int64_t)plan->rows[r].ntiles);
+      len = std::max<int64_t>((ntiles + 2 * cap - 1) / (2 * cap), (longest + 1023) / 1024);
+    }
+    if (len > (int64_t)mk::kLookback * mk::kLookback) len = (int64_t)mk::kLookback * mk::kLookback;
+    int64_t nseg = 0;
+    a.seg_start[0] = 0;
+    for (int r = 0; r < a.nrows; ++r) {
+      const int64_t nt = a.nrows == 1 ? a.row0.ntiles : (int64_t)plan->rows[r].ntiles;
+      nseg += (nt + len - 1) / len;
+      a.seg_start[r + 1] = (int32_t)std::min<int64_t>(nseg, INT32_MAX);
+    }
+    if (nseg > 0 && nseg <= INT32_MAX) {
+      a.seg_len = (int)len;
+      a.nseg = nseg;
+      a.serial = 1;
+      a.grid = (int)(a.nseg < cap ? a.nseg : cap);
+      a.segstate = reinterpret_cast<double*>(static_cast<unsigned char*>(a.ws) + sizeof(mk::WsHeader));
+    }
+  }
+  return MORLET_OK;
+}
+
 // Fill the launch descriptor for this plan (rows, tables, tiles, workspace, grid).
 // recompute = true: a forward pass recomputed inside a gradient call; under the default
 // accumulation it runs the mixed scan (float64 chunk sums), whose rounding stays below what the
@@ -552,55 +607,7 @@ morlet_status make_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int v
   a.ws = ws;
   a.dtype = dtype;
   if (gran_launch(plan, a, variant, least_scratch, least_us)) return MORLET_OK;
-  const int occ = mk::scan_occupancy(a.K, a.R, variant, a.acc, a.kind, mom, dtype);
-  if (occ <= 0) return fail(MORLET_ERR_UNSUPPORTED, "no kernel for this configuration");
-  const int64_t cap = (int64_t)occ * plan->num_cus;
-  a.grid = (int)(ntiles < cap ? ntiles : cap);
-  // Row-serial schedule when the longest row is no more than one block's share of the tiles:
-  // every block then runs whole rows, longest first, carrying the state from tile to tile
-  // in LDS, and no tile waits on another block.
-  a.serial = 0;
-  if (plan->batched && a.nrows > 1 && plan->row_serial != 0 && !(plan->row_serial == 2 && a.nrows <= mk::kQueues)) {
-    const int64_t share = (ntiles + cap - 1) / cap;
-    if (plan->row_serial == 1 || plan->max_row_tiles <= share) {
-      a.serial = 1;
-      a.grid = (int)(a.nrows < cap ? a.nrows : cap);
-    }
-  }
-  // Segments schedule for a forward launch of at most eight rows that the rows schedule did not
-  // take: chosen, or automatic when the launch has at least two tiles per resident block. About
-  // two segments per block over all rows (the ticket balances them), at most 64 x 64 tiles each
-  // (the reach of the table's look-back weights), every row cut on its own. The segment states
-  // sit in the workspace after its header (within what the tiles schedule needs).
-  a.nseg = 0;
-  if (variant == mk::kVarForward && !a.serial && a.nrows >= 1 && a.nrows <= mk::kQueues && ntiles >= 2 &&
-      (plan->row_serial == 2 || (plan->row_serial == -1 && ntiles >= 2 * cap))) {
-    // automatic length: about two segments per resident block, and at most 1024 segments per row
-    // (one round of the combination, which runs on one CU per row)
-    int64_t len = plan->seg_tiles;
-    if (len <= 0) {
-      int64_t longest = 0;
-      for (int r = 0; r < a.nrows; ++r)
-        longest = std::max<int64_t>(longest, a.nrows == 1 ? a.row0.ntiles : (int64_t)plan->rows[r].ntiles);
-      len = std::max<int64_t>((ntiles + 2 * cap - 1) / (2 * cap), (longest + 1023) / 1024);
-    }
-    if (len > (int64_t)mk::kLookback * mk::kLookback) len = (int64_t)mk::kLookback * mk::kLookback;
-    int64_t nseg = 0;
-    a.seg_start[0] = 0;
-    for (int r = 0; r < a.nrows; ++r) {
-      const int64_t nt = a.nrows == 1 ? a.row0.ntiles : (int64_t)plan->rows[r].ntiles;
-      nseg += (nt + len - 1) / len;
-      a.seg_start[r + 1] = (int32_t)std::min<int64_t>(nseg, INT32_MAX);
-    }
-    if (nseg > 0 && nseg <= INT32_MAX) {
-      a.seg_len = (int)len;
-      a.nseg = nseg;
-      a.serial = 1;
-      a.grid = (int)(a.nseg < cap ? a.nseg : cap);
-      a.segstate = reinterpret_cast<double*>(static_cast<unsigned char*>(ws) + sizeof(mk::WsHeader));
-    }
-  }
-  return MORLET_OK;
+  return tile_schedule(plan, a, variant, mom, dtype);
 }
 
 // The launch of an image's second axis (plan: its batched plan over lines of length H) down the columns
@@ -695,17 +702,15 @@ EdgeLayout edge_layout(morlet_plan_t plan) {
 }
 
 // The launch of a single-signal plan moved onto its padded row of Ne samples.
-void pad_launch(morlet_plan_t plan, mk::ScanLaunch& a, int64_t Ne, int variant, int mom, int dtype) {
+morlet_status pad_launch(morlet_plan_t plan, mk::ScanLaunch& a, int64_t Ne, int variant, int mom, int dtype) {
   const int64_t jend = Ne + plan->L - plan->n0;
   const int64_t ntiles = tiles_for(jend, plan->R);
   a.row0.N = Ne;
   a.row0.jend = jend;
   a.row0.ntiles = (int32_t)ntiles;
   a.ntiles = ntiles;
-  if (gran_launch(plan, a, variant)) return;
-  const int occ = mk::scan_occupancy(a.K, a.R, variant, a.acc, a.kind, mom, dtype);
-  const int64_t cap = (int64_t)(occ > 0 ? occ : 1) * plan->num_cus;
-  a.grid = (int)(ntiles < cap ? ntiles : cap);
+  if (gran_launch(plan, a, variant)) return MORLET_OK;
+  return tile_schedule(plan, a, variant, mom, dtype);
 }
 
 // Edge extension (Sec. II): every output reads at most 2L samples outside [0, N-1], so the
@@ -729,9 +734,9 @@ morlet_status run_edge(morlet_plan_t plan, const void* x, int dtype, void* out, 
   hipError_t err = mk::launch_edge_extend(x, dtype, plan->N, P, xe, s);
   if (err != hipSuccess) return fail(MORLET_ERR_HIP, std::string("launch failed: ") + hipGetErrorString(err));
   mk::ScanLaunch a;
-  const morlet_status st = make_launch(plan, a, ws, mk::kVarForward, 0, 0);
+  morlet_status st = make_launch(plan, a, ws, mk::kVarForward, 0, 0);
+  if (st == MORLET_OK) st = pad_launch(plan, a, Ne, mk::kVarForward, 0, 0);
   if (st != MORLET_OK) return st;
-  pad_launch(plan, a, Ne, mk::kVarForward, 0, 0);
   a.x = xe;
   a.dtype = 0;
   a.out = oe;
@@ -975,8 +980,8 @@ morlet_status run_backward_edge(morlet_plan_t plan, const void* x, int dtype, co
   hipError_t e = mk::launch_pad_center(g, plan->kind == 0 ? 8 : 4, plan->N, P, ge, s);
   mk::ScanLaunch a;
   morlet_status st = make_launch(plan, a, ws, mk::kVarAdjoint, 0, 0);
+  if (st == MORLET_OK) st = pad_launch(plan, a, Ne, mk::kVarAdjoint, 0, 0);
   if (st != MORLET_OK) return st;
-  pad_launch(plan, a, Ne, mk::kVarAdjoint, 0, 0);
   a.x = ge;
   a.dtype = 0;
   a.out = gxe;
@@ -987,8 +992,8 @@ morlet_status run_backward_edge(morlet_plan_t plan, const void* x, int dtype, co
   const int mom = plan->mode == 1 ? 1 : 0;
   e = mk::launch_edge_extend(x, dtype, plan->N, P, xe, s);
   st = make_launch(plan, a, ws, mk::kVarParamGrad, mom, 0);
+  if (st == MORLET_OK) st = pad_launch(plan, a, Ne, mk::kVarParamGrad, mom, 0);
   if (st != MORLET_OK) return st;
-  pad_launch(plan, a, Ne, mk::kVarParamGrad, mom, 0);
   a.x = xe;
   a.dtype = 0;
   a.g = ge;
@@ -1088,9 +1093,9 @@ morlet_status run_deriv_backward(morlet_plan_t plan, const float* gy, float* gx,
     e = mk::launch_reverse(gy, B, m.Ne, s);
   }
   mk::ScanLaunch a;
-  const morlet_status st = make_launch(plan, a, ws, mk::kVarForward, 0, 0);
+  morlet_status st = make_launch(plan, a, ws, mk::kVarForward, 0, 0);
+  if (st == MORLET_OK && edge) st = pad_launch(plan, a, m.Ne, mk::kVarForward, 0, 0);
   if (st != MORLET_OK) return st;
-  if (edge) pad_launch(plan, a, m.Ne, mk::kVarForward, 0, 0);
   a.x = B;
   a.dtype = 0;
   a.out = A;

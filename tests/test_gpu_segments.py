@@ -217,3 +217,31 @@ def test_edge_extension_segments(kind, mode):
          else O.plan_gauss(sigma, K, info["L"], mode=mode, n0=n0))
     want = O.forward_edge(x.astype(np.float64), p)
     assert rel_l2(got, want) <= 1e-5, rel_l2(got, want)
+
+
+@pytest.mark.parametrize("kind", ["morlet", "gauss", "deriv"])
+def test_segments_cover_the_padded_row(kind):
+    # with edge extension the segments are those of the padded row, 4L samples longer than the signal: here
+    # 20 tiles more, with one tile per segment by default
+    import paper_2110_11866_amd as M
+    _announce("segments-padded", kind)
+    N, sigma, K, L = 1 << 17, 6000.0, 5, 20000
+    x = (np.random.default_rng(41).standard_normal(N) + 2.0).astype(np.float32)
+    xt = torch.from_numpy(x).cuda()
+    if kind == "morlet":
+        plan = M.MorletPlan(N, sigma, 6.0 / sigma, K, L, mode="asft")
+        p = O.plan_morlet(sigma, 6.0 / sigma, K, L, mode="asft", n0=plan.info()["n0"], P_S=plan.info()["P_S"])
+    elif kind == "gauss":
+        plan = M.GaussPlan(N, sigma, K, L)
+        p = O.plan_gauss(sigma, K, L)
+    else:
+        plan = M.GaussDerivPlan(N, sigma, K, L, order=1, mode="asft")
+        p = O.plan_gauss_deriv(sigma, K, L, 1, "asft", n0=plan.info()["n0"])
+    plan.set_boundary("edge").set_schedule("segments")
+    got = plan.forward(xt).cpu().numpy()
+    assert rel_l2(got, O.forward_edge(x.astype(np.float64), p)) <= 1e-5
+    if kind == "deriv":
+        gy = torch.from_numpy(np.random.default_rng(42).standard_normal(N).astype(np.float32)).cuda()
+        gx = plan.backward(None, gy)[0]
+        want = plan.set_schedule("tiles").backward(None, gy)[0]
+        assert rel_l2(gx.cpu().numpy(), want.cpu().numpy()) <= 1e-5

@@ -345,7 +345,7 @@ morlet_status morlet_plan_set_segments(morlet_plan_t plan, int32_t tiles_per_seg
  * morlet_forward, MORLET_ERR_ALLOC if the trial workspace cannot be allocated; on error the
  * plan keeps its tile shape and schedule.
  * Persisted choices: when the environment variable MORLET_TUNE_CACHE names a file, a choice
- * is appended to it as one text line (key, R, schedule, time per launch), the key made of the
+ * is appended to it as one text line (key, R, schedule, time per launch), the key made of the kernels' revision, the
  * device architecture and the launch shape (plan kind, mode, accumulation, dtype, K, batch
  * shape, total scan positions and largest window in powers of two); a later call whose key is in
  * the file applies the recorded choice without timing (the last line for a key wins). */

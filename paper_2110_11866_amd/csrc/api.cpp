@@ -1367,6 +1367,11 @@ namespace {
 // powers of two).
 std::mutex g_tune_mu;
 
+// Revision of the kernels and schedules that the autotuner chooses among, part of every recorded key: a choice
+// made among others is not applied. Raised when one is added or changes its speed (2: the automatic schedule's
+// granule and carried scans).
+constexpr int kTuneRevision = 2;
+
 std::string tune_key(morlet_plan_t plan, int dtype) {
   static std::string arch = [] {
     int dev = 0;
@@ -1386,7 +1391,7 @@ std::string tune_key(morlet_plan_t plan, int dtype) {
   }
   auto lg = [](int64_t v) { int b = 0; while (v > 1) { v >>= 1; ++b; } return b; };
   std::ostringstream k;
-  k << "arch=" << arch << " kind=" << plan->kind << " deriv=" << plan->deriv << " mult=" << (plan->multiply ? 1 : 0)
+  k << "arch=" << arch << " kernels=" << kTuneRevision << " kind=" << plan->kind << " deriv=" << plan->deriv << " mult=" << (plan->multiply ? 1 : 0)
     << " mode=" << plan->mode << " accum=" << plan->accum << " dtype=" << dtype << " K=" << plan->K
     << " batched=" << (plan->batched ? 1 : 0) << " B=" << plan->B << " S=" << plan->S << " lgpos=" << lg(positions)
     << " lgL=" << lg(maxL + 1);

@@ -72,3 +72,24 @@ def test_autotune_choice_is_persisted_and_reused(tmp_path, monkeypatch):
     W = plan2.forward(x)
     torch.cuda.synchronize()
     assert torch.isfinite(torch.view_as_real(W)).all()
+
+
+def test_autotune_ignores_a_choice_among_other_kernels(tmp_path, monkeypatch):
+    # a line without the kernels' revision (as earlier builds wrote it) or with another one is not applied: the
+    # automatic schedule and its scans were not among the candidates that it was chosen from
+    import paper_2110_11866_amd as M
+    _announce("tune-cache-revision")
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("MORLET_TUNE_CACHE", str(cache))
+    N = 300000
+    x = torch.from_numpy(np.random.default_rng(5).standard_normal(N).astype(np.float32)).cuda()
+    new = lambda: M.MorletPlan(N, 64.0, 6.0 / 64.0, 5, 0, mode="asft")
+    chosen = new().autotune(x, reps=3)
+    key = cache.read_text().split("\t")[0]
+    fields = key.split()
+    rev = [f for f in fields if f.startswith("kernels=")]
+    assert len(rev) == 1
+    for other in (" ".join(f for f in fields if f != rev[0]), key.replace(rev[0], rev[0] + "1")):
+        cache.write_text(f"{other}\t4\t0\t0\n")
+        assert new().autotune(x, reps=3)["R"] == chosen["R"]
+        assert len(cache.read_text().splitlines()) == 2   # timed anew and recorded

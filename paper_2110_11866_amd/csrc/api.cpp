@@ -195,9 +195,10 @@ bool equal_rows(const morlet_plan_s* p) {
 // round-robin, so position k of the list runs on XCD k mod 8: like the row queues, the pieces of one
 // signal's rows, which read the same input, go to one XCD (signals longest first, each to the XCD with
 // the least work; with fewer than 4 signals per XCD the pieces are dealt in turn), the lists
-// interleaved.
+// interleaved. They depend on lengths and windows alone, which a plan keeps: found once.
 void build_gran_segs(morlet_plan_s* p) {
-  p->gran_segs.clear();
+  if (p->gran_rows) return;
+  p->gran_rows = true;
   if (equal_rows(p)) {   // their pieces follow from the index
     mk::set_split(p, p->rows.empty() ? 0 : p->rows[0].N, p->rows.empty() ? 0 : p->rows[0].L, (int64_t)p->rows.size());
     return;
@@ -205,16 +206,12 @@ void build_gran_segs(morlet_plan_s* p) {
   const int S = p->S > 0 ? p->S : 1;
   if ((int64_t)p->rows.size() != (int64_t)p->B * S) return;
   auto window = [](const mk::Row& r) { return (2 * r.L + mk::kGran - 1) / mk::kGran; };
-  std::vector<mk::GranRow> shapes;
   int64_t ng_max = 0;
-  for (const mk::Row& r : p->rows) {
-    const mk::GranRow g{mk::granules_for(r.N), window(r), 1};
-    ng_max = std::max(ng_max, g.ng);
-    if (g.ng == 0) continue;
-    if (!shapes.empty() && shapes.back().ng == g.ng && shapes.back().nw == g.nw) ++shapes.back().count;
-    else shapes.push_back(g);
-  }
-  if (shapes.empty() || ng_max > INT32_MAX) return;
+  for (int64_t n : p->lengths) ng_max = std::max(ng_max, mk::granules_for(n));
+  if (ng_max == 0 || ng_max > INT32_MAX) return;
+  std::vector<int64_t> windows(S);
+  for (int s = 0; s < S; ++s) windows[s] = window(p->rows[s]);
+  const std::vector<mk::GranRow> shapes = mk::gran_shapes(p->lengths, windows);
   const mk::GranSplit split = p->gran_split = mk::split_granules(shapes, p->num_cus);
   const int nq = mk::kQueues;
   const bool by_signal = (int64_t)p->B >= 4 * nq;
@@ -234,6 +231,11 @@ void build_gran_segs(morlet_plan_s* p) {
   std::stable_sort(so.begin(), so.end(), [&](int x, int y) { return p->rows[x].L > p->rows[y].L; });
   std::vector<std::vector<mk::GranSeg>> q(by_signal ? nq : 1);
   std::vector<int64_t> load(q.size(), 0);
+  size_t total = 0;
+  for (int64_t n : p->lengths)
+    for (int s = 0; s < S; ++s) total += (size_t)((mk::granules_for(n) + piece[s] - 1) / piece[s]);
+  for (auto& list : q) list.reserve(by_signal ? total / nq + total / 64 : total);
+  p->gran_segs.reserve(total);
   for (int b : order) {
     size_t best = 0;
     for (size_t i = 1; i < q.size(); ++i)

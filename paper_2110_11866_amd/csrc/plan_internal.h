@@ -76,6 +76,7 @@ struct morlet_plan_s {
   int64_t ntiles = 0, ntiles_max = 0;
   int64_t gran_ng = -1, gran_nw = -1;      // rows of one length: the granules, window granules and split
   mk::GranSplit gran_split;
+  bool gran_rows = false;                  // batched plans: whether the split and pieces have been found
   bool gran_two = false;                   // granule scan: every piece starts on an even granule
   std::vector<mk::GranSeg> gran_segs;      // granule scan: pieces of the rows in launch order
   void* d_rows = nullptr;                  // device rows, then tile_row, row_order, gran_segs
@@ -138,6 +139,8 @@ int out_kind(const morlet_plan_s* p);
 struct GranRow {
   int64_t ng, nw, count;   // granules, window granules, rows of this shape
 };
+// The shapes of the rows of every length at every window (granules), each once.
+std::vector<GranRow> gran_shapes(const std::vector<int64_t>& lengths, const std::vector<int64_t>& windows);
 // warm: cost of a window granule relative to one with outputs.
 GranSplit split_granules(const std::vector<GranRow>& rows, int num_cus, double warm = 0.3);
 // Estimated times in us of a launch's three ways. kind: the launch's (0 complex output, else real); wide: float64

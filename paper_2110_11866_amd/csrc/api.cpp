@@ -183,14 +183,6 @@ void build_row_queues(morlet_plan_s* p) {
   p->qstart[nq] = (int32_t)p->row_order.size();
 }
 
-// Whether all rows have one length and one scale (images, the multiplication method).
-bool equal_rows(const morlet_plan_s* p) {
-  if (p->S != 1) return false;
-  for (int64_t n : p->lengths)
-    if (n != p->lengths[0]) return false;
-  return true;
-}
-
 // Pieces of the rows for the granule scan, in launch order. Workgroups are dispatched to the XCDs
 // round-robin, so position k of the list runs on XCD k mod 8: like the row queues, the pieces of one
 // signal's rows, which read the same input, go to one XCD (signals longest first, each to the XCD with
@@ -199,7 +191,8 @@ bool equal_rows(const morlet_plan_s* p) {
 void build_gran_segs(morlet_plan_s* p) {
   if (p->gran_rows) return;
   p->gran_rows = true;
-  if (equal_rows(p)) {   // their pieces follow from the index
+  p->equal_rows = p->S == 1 && std::all_of(p->lengths.begin(), p->lengths.end(), [&](int64_t n) { return n == p->lengths[0]; });
+  if (p->equal_rows) {   // their pieces follow from the index
     mk::set_split(p, p->rows.empty() ? 0 : p->rows[0].N, p->rows.empty() ? 0 : p->rows[0].L, (int64_t)p->rows.size());
     return;
   }
@@ -441,7 +434,7 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant, bool least_
   const int64_t nrows = plan->batched ? (int64_t)plan->rows.size() : 1;
   const bool adj = variant == mk::kVarAdjoint, wide = a.acc == mk::kAccMixed;
   const double tiles = mk::tiles_us(a.ntiles, a.kind, adj, plan->K, plan->num_cus);
-  if (plan->batched && !equal_rows(plan)) {
+  if (plan->batched && !plan->equal_rows) {
     if (plan->gran_segs.empty() || plan->gran_segs.size() > (size_t)INT32_MAX) return false;
     const double granules = mk::granule_us(plan->gran_split, a.kind, adj, wide, plan->K, plan->num_cus);
     if (!least_scratch && granules > tiles) return false;

@@ -77,6 +77,7 @@ struct morlet_plan_s {
   int64_t gran_ng = -1, gran_nw = -1;      // rows of one length: the granules, window granules and split
   mk::GranSplit gran_split;
   bool gran_rows = false;                  // batched plans: whether the split and pieces have been found
+  bool equal_rows = false;                 // all rows have one length and one scale (images, the multiplication method)
   bool gran_two = false;                   // granule scan: every piece starts on an even granule
   std::vector<mk::GranSeg> gran_segs;      // granule scan: pieces of the rows in launch order
   void* d_rows = nullptr;                  // device rows, then tile_row, row_order, gran_segs

@@ -39,8 +39,25 @@ static void row_shapes() {
   EXPECT(a.base == b.base && a.per_warm == b.per_warm);
 }
 
+// Whether a batch's rows are all alike is found when the plan is built, not by a pass over the lengths in
+// every launch.
+static void equal_rows() {
+  const double sig[2] = {16.0, 32.0}, xi[2] = {0.4, 0.2};
+  const int64_t same[3] = {500, 500, 500}, other[3] = {500, 501, 500}, none[2] = {0, 0};
+  struct { const int64_t* len; int B, S; bool equal; } cases[] = {{same, 3, 1, true}, {same, 3, 2, false}, {other, 3, 1, false}, {same, 1, 1, true}, {none, 2, 1, true}};
+  for (const auto& c : cases) {
+    morlet_plan_t p = nullptr;
+    EXPECT(morlet_scalogram_plan(&p, c.B, c.len, c.S, sig, xi, 4, 3.0) == MORLET_OK);
+    EXPECT(p && p->equal_rows == c.equal);
+    EXPECT(morlet_plan_set_tile(p, 8) == MORLET_OK && p->equal_rows == c.equal);
+    EXPECT(c.equal == p->gran_segs.empty());
+    morlet_destroy(p);
+  }
+}
+
 int main() {
   row_shapes();
+  equal_rows();
   if (g_fail == 0) std::printf("all checks passed\n");
   return g_fail ? 1 : 0;
 }

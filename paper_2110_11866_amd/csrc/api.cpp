@@ -662,7 +662,7 @@ int64_t plan_ntiles_max(morlet_plan_t plan) {
 }
 
 // Backward workspace: header + tile states (2K complex states) | per-tile partials |
-// (batched) per-scale adjoint scratch [S][sum lengths] float32.
+// (several scales) per-scale adjoint scratch [S][sum lengths] float32.
 struct BwdLayout {
   size_t states_end, partials_off, scratch_off, rowpart_off, total;
 };
@@ -673,7 +673,7 @@ BwdLayout bwd_layout(morlet_plan_t plan) {
   b.partials_off = (b.states_end + 255) / 256 * 256;
   const size_t pbytes = (size_t)nt * mk::pg_partials(plan->K) * sizeof(double);
   b.scratch_off = (b.partials_off + pbytes + 255) / 256 * 256;
-  const size_t sbytes = plan->batched ? (size_t)plan->S * (size_t)plan->N * sizeof(float) : 0;
+  const size_t sbytes = plan->batched && plan->S > 1 ? (size_t)plan->S * (size_t)plan->N * sizeof(float) : 0;
   b.rowpart_off = (b.scratch_off + sbytes + 255) / 256 * 256;
   const size_t nrows = plan->batched ? plan->rows.size() : 1;
   b.total = b.rowpart_off + nrows * mk::pg_partials(plan->K) * sizeof(double);

@@ -55,8 +55,26 @@ static void equal_rows() {
   }
 }
 
+// The backward workspace holds per-scale adjoints only where several are added up: with one scale a batch of one
+// signal needs what the signal's own plan needs (up to its padding), not N floats more.
+static void backward_scratch() {
+  const int64_t N = 1 << 20;
+  const double sig[2] = {16.0, 32.0}, xi[2] = {0.4, 0.2};
+  morlet_plan_t one = nullptr, row = nullptr, two = nullptr;
+  EXPECT(morlet_plan(&one, N, 16.0, 0.4, 5, 48) == MORLET_OK);
+  EXPECT(morlet_scalogram_plan(&row, 1, &N, 1, sig, xi, 5, 3.0) == MORLET_OK);
+  EXPECT(morlet_scalogram_plan(&two, 1, &N, 2, sig, xi, 5, 3.0) == MORLET_OK);
+  size_t a = 0, b = 0, c = 0;
+  EXPECT(morlet_backward_workspace_size(one, &a) == MORLET_OK && morlet_backward_workspace_size(row, &b) == MORLET_OK &&
+         morlet_backward_workspace_size(two, &c) == MORLET_OK);
+  EXPECT(b <= a + 4096 && a <= b + 4096);
+  EXPECT(c >= 2 * a - 4096 + 2 * (size_t)N * sizeof(float));
+  for (morlet_plan_t p : {one, row, two}) morlet_destroy(p);
+}
+
 int main() {
   row_shapes();
+  backward_scratch();
   equal_rows();
   if (g_fail == 0) std::printf("all checks passed\n");
   return g_fail ? 1 : 0;

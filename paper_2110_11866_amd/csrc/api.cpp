@@ -435,7 +435,7 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant, bool least_
   const bool adj = variant == mk::kVarAdjoint, wide = a.acc == mk::kAccMixed;
   const double tiles = mk::tiles_us(a.ntiles, a.kind, adj, plan->K, plan->num_cus);
   if (plan->batched && !plan->equal_rows) {
-    if (plan->gran_segs.empty() || plan->gran_segs.size() > (size_t)INT32_MAX) return false;
+    if (plan->gran_segs.empty() || !mk::launchable((int64_t)plan->gran_segs.size(), 64)) return false;
     const double granules = mk::granule_us(plan->gran_split, a.kind, adj, wide, plan->K, plan->num_cus);
     if (!least_scratch && granules > tiles) return false;
     const size_t rb = plan->rows.size() * sizeof(mk::Row);
@@ -452,7 +452,7 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant, bool least_
   const mk::GranSplit split = ng == plan->gran_ng && nw == plan->gran_nw ? plan->gran_split
                                                                         : mk::split_granules({{ng, nw, nrows}}, plan->num_cus);
   const int64_t n = split.piece(nw), ns = (ng + n - 1) / n;
-  if (ns * nrows > INT32_MAX) return false;
+  if (!mk::launchable(ns * nrows, 64)) return false;   // (the tile scan's grid does not grow with the rows)
   // A window much longer than a piece is summed by every piece. The carried scan sums no windows but reads
   // the row twice, in two launches, a block per CU (K = 5, us, granule | carried: N = 102400, 2L =
   // 2664: 7 | 10.5, 10650: 15 | 10.2, 42600: 47 | 10.6; N = 2^22, 2L = 10650: 32 | 35, 42600: 72 | 35; N =
@@ -618,6 +618,7 @@ morlet_status column_launch(morlet_plan_t plan, mk::ScanLaunch& a, void* ws, int
   if (st != MORLET_OK || lines < 0) return st;
   const int64_t nw = (2 * plan->rows[0].L + mk::kRun - 1) / mk::kRun, ng = (plan->rows[0].N + mk::kRun - 1) / mk::kRun;
   const int64_t blocks = (cols + mk::kColWave - 1) / mk::kColWave;
+  if (!mk::launchable(blocks, 64)) return MORLET_OK;
   const mk::GranSplit split = mk::split_granules({{ng, nw, blocks}}, plan->num_cus / 2, 0.5);
   // windows long against the pieces: 4000 x 500, 2L = 4000, K = 8: columns 287 us, transposed lines 54
   if (mk::columns_us(split, plan->K, plan->num_cus) > lines + mk::transposes_us((double)plan->rows[0].N * (double)cols)) return MORLET_OK;

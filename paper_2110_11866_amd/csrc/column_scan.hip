@@ -193,7 +193,7 @@ __global__ __launch_bounds__(64) void column_kernel(ColumnLaunch P) {
 hipError_t launch_columns(const ColumnLaunch& a, hipStream_t s) {
   if (a.rows <= 0 || a.cols <= 0) return hipSuccess;
   const int64_t bx = (a.cols + kCols - 1) / kCols, by = a.piece > 0 ? (a.rows + a.piece - 1) / a.piece : 0;
-  if (a.K < 1 || a.K > kMaxTerms || by < 1 || by > 65535 || bx > 0x7fffffff) return hipErrorInvalidValue;
+  if (a.K < 1 || a.K > kMaxTerms || by < 1 || by > 65535 || !launchable(bx, 64)) return hipErrorInvalidValue;
   const int ns = GranLayout{a.K}.NS();
   void (*fn)(ColumnLaunch) = a.adjoint ? (ns == 1 ? column_kernel<1, true> : ns == 2 ? column_kernel<2, true> : column_kernel<3, true>)
                                        : (ns == 1 ? column_kernel<1, false> : ns == 2 ? column_kernel<2, false> : column_kernel<3, false>);

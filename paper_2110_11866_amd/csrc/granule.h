@@ -68,6 +68,9 @@ struct GranSeg {
 // Granules that cover a row of N outputs at any alignment.
 inline int64_t granules_for(int64_t N) { return N <= 0 ? 0 : (N + 31 + kGran - 1) / kGran; }
 
+// A launch holds fewer than 2^32 threads along its first dimension.
+inline bool launchable(int64_t blocks, int threads) { return blocks <= (int64_t)0xffffffff / threads; }
+
 struct GranLaunch {
   int K, acc, kind, dtype;      // acc: kAccF32 or kAccMixed; kind: 0 complex transform, else real
   int adjoint;                  // x is the cotangent, out the float32 gradient

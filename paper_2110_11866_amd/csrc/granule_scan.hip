@@ -471,7 +471,7 @@ GranFn pick(bool cplx, int in, bool two, bool wide) {
 
 hipError_t launch_granules(const GranLaunch& a, hipStream_t s) {
   if (a.nseg <= 0) return hipSuccess;
-  if (a.K < 1 || a.K > kMaxTerms || a.nseg > 0x7fffffff || (!a.segs && (a.pieces < 1 || a.nseg != (int64_t)a.nrows * a.pieces)))
+  if (a.K < 1 || a.K > kMaxTerms || !launchable(a.nseg, 64) || (!a.segs && (a.pieces < 1 || a.nseg != (int64_t)a.nrows * a.pieces)))
     return hipErrorInvalidValue;
   const bool cplx = a.kind == 0;
   const int ns = GranLayout{a.K}.NS();

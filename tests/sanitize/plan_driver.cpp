@@ -1,12 +1,12 @@
 // Checks of what a plan holds on the host, for the same build as abi_driver.cpp. Exit status 0 when all hold.
 #include <cstdio>
 #include <map>
+#include <memory>
 #include <random>
 #include <utility>
 #include <vector>
 
-#include "morlet.h"
-#include "plan_internal.h"
+#include "api.cpp"   // its internal functions too
 
 static int g_fail = 0;
 #define EXPECT(cond)                                                               \
@@ -72,7 +72,26 @@ static void backward_scratch() {
   for (morlet_plan_t p : {one, row, two}) morlet_destroy(p);
 }
 
+// A batch of more pieces than a launch has room for (64 threads each, fewer than 2^32 in all) is left to the tile
+// scan, whose grid is bounded.
+static void launch_limit() {
+  EXPECT(mk::launchable(((int64_t)1 << 26) - 1, 64) && !mk::launchable((int64_t)1 << 26, 64));
+  EXPECT(mk::launchable(((int64_t)1 << 23) - 1, 512) && !mk::launchable((int64_t)1 << 23, 512));
+  auto p = std::make_unique<morlet_plan_s>();
+  p->batched = true;
+  p->K = 5;
+  p->rows.resize(4);
+  mk::ScanLaunch a{};
+  a.acc = mk::kAccF32;
+  a.ntiles = (int64_t)1 << 30;
+  p->gran_segs.resize(((size_t)1 << 26) - 1);
+  EXPECT(gran_launch(p.get(), a, mk::kVarForward) && a.gran_nseg == ((int64_t)1 << 26) - 1);
+  p->gran_segs.push_back({});
+  EXPECT(!gran_launch(p.get(), a, mk::kVarForward) && a.gran_nseg == 0);
+}
+
 int main() {
+  launch_limit();
   row_shapes();
   backward_scratch();
   equal_rows();

@@ -18,7 +18,7 @@ def test_plan_state(tmp_path):
         pytest.skip("needs g++ and the HIP headers")
     exe = str(tmp_path / "plan_driver")
     subprocess.run([cxx, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
-                    "-I", os.path.join(ROOT, "include"), "-I", CSRC, os.path.join(CSRC, "api.cpp"),
+                    "-I", os.path.join(ROOT, "include"), "-I", CSRC,
                     os.path.join(CSRC, "plan.cpp"), os.path.join(HERE, "host_stubs.cpp"),
                     os.path.join(HERE, "plan_driver.cpp"), "-L", os.path.join(ROCM, "lib"),
                     "-Wl,-rpath," + os.path.join(ROCM, "lib"), "-lamdhip64", "-o", exe],

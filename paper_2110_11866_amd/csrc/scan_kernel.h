@@ -832,9 +832,22 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
           for (int t = 0; t < K; ++t) { vr[K + t] -= vr[t]; vi[K + t] -= vi[t]; }
         }
-        // One branch for the wave and clamped addresses at the row's ends: lanes that branch apart here,
-        // where the state fills the registers, let the compiler move live values aside under part of the
-        // lanes (seen in the assembly of the K = 12, R = 8 Gaussian pass: a stale address, a fault).
+        // Loads in this loop take one branch for the wave and clamped addresses at the row's ends: lanes that
+        // branch apart here, where the state fills the registers, let the compiler move live values aside under
+        // part of the lanes (seen in the assembly of the K = 12, R = 8 Gaussian pass: a stale address, a fault).
+        auto load_x = [&](int64_t j, float (&v)[4]) {
+          const void* xs = static_cast<const char*>(P.x) + row.x_off * (DT == 0 ? 4 : 2);
+          if (__all(j >= 0 && j + 4 <= row.N)) {
+            ld4_fast<DT>(xs, j, v);
+          } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int64_t m = j + r, c = m < 0 ? 0 : m < row.N ? m : row.N - 1;
+              const float x = load1(xs, DT, c);
+              v[r] = m == c ? x : 0.f;
+            }
+          }
+        };
         auto load_g = [&](int q, float (&gr)[4], float (&gi)[4]) {
           const int64_t n = nb + 4 * q;
           if (__all(n >= 0 && n + 4 <= row.N)) {
@@ -875,7 +888,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
             ya[0][0] = v0.x; yb[0][0] = v0.y; ya[0][1] = v0.z; yb[0][1] = v0.w;
             ya[0][2] = v1.x; yb[0][2] = v1.y; ya[0][3] = v1.z; yb[0][3] = v1.w;
           } else {
-            load_quad(j0 + 4 * q, ya, yb);
+            load_x(j0 + 4 * q, ya[0]);
+            load_x(j0 + 4 * q - 2 * row.L, yb[0]);
           }
 #pragma unroll
           for (int r = 0; r < 4; ++r) {

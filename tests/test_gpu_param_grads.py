@@ -47,3 +47,29 @@ def test_tiles_terms_and_alignments(tile, K, L):
                 want = O.param_grads(xd, g.astype(np.complex128), p)
                 size = np.abs(want).max() + 1e-30
                 assert np.abs(got - want).max() <= TOL * size, (got, want)
+
+
+@pytest.mark.parametrize("tile", [4, 8, 32])
+@pytest.mark.parametrize("K", [2, 3, 4, 7, 8, 9, 10, 11])
+def test_terms_between_at_every_tile(tile, K):
+    # the other term counts, each its own kernels, with float32 and (at tile 32, where the inputs are loaded
+    # again) 16-bit inputs
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    test_tiles_terms_and_alignments(tile, K, 41)
+    import paper_2110_11866_amd as M
+    N, sigma, L = 9001, 17.0, 41
+    rng = np.random.default_rng(K)
+    for dtype in (torch.float16, torch.bfloat16) if tile == 32 else ():
+        x = torch.from_numpy(rng.standard_normal(N + 1).astype(np.float32)).cuda().to(dtype)[1:]
+        xd = x.double().cpu().numpy()
+        for mode in ("sft", "asft"):
+            print("[case]", tile, K, dtype, mode, flush=True)
+            sys.stdout.flush()
+            plan = M.MorletPlan(N, sigma, 6 / sigma, K, L, mode=mode).set_tile(tile)
+            i = plan.info()
+            p = O.plan_morlet(sigma, 6 / sigma, K, L, mode=mode, n0=i["n0"] if mode == "asft" else None, P_S=i["P_S"])
+            g = (2 * rng.uniform(size=N) * O.forward(xd, p)).astype(np.complex64)
+            got = plan.backward(x, torch.from_numpy(g).cuda())[1].cpu().numpy()
+            want = O.param_grads(xd, g.astype(np.complex128), p)
+            assert np.abs(got - want).max() <= TOL * (np.abs(want).max() + 1e-30), (got, want)

@@ -85,7 +85,7 @@ __global__ __launch_bounds__(64) void column_kernel(ColumnLaunch P) {
     }
   };
 
-  // states before position js of the lane's four columns
+  // states before position js of the lane's two columns
   double zr[kG][NS], zi[kG][NS];
 #pragma unroll
   for (int g = 0; g < kG; ++g)

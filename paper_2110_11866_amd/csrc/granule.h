@@ -1,4 +1,4 @@
-// Granule scan (granule_scan.h): the constants it reads, the pieces of rows it runs and its launch.
+// Granule scan (granule_scan.hip): the constants it reads, the pieces of rows it runs and its launch.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -17,26 +17,23 @@ struct GranLayout {
   int K;
   MK_HD int NS() const { return (K + 3) / 4; }            // state slots per lane
   MK_HD int MB() const { return K > 8 ? 2 : 1; }          // matrix blocks of the run sums
-  // float32, 64 lanes each: run outputs from run inputs, T[4 q + kb -> r] (lane 16 q + r), real then
-  // imaginary component; run outputs from the state before the run, component k = 2 s + (0 re, 1 im)
+  // float32, 64 lanes each: run outputs from run inputs, T[4 q + kb -> r] (lane 16 q + r), of the real component;
+  // run outputs from the state before the run, component k = 2 s + (0 re, 1 im)
   MK_HD int fTre(int kb) const { return 64 * kb; }
-  MK_HD int fTim(int kb) const { return 64 * (4 + kb); }
-  MK_HD int fCre(int k) const { return 64 * (8 + k); }
-  MK_HD int fCim(int k) const { return 64 * (8 + 2 * NS() + k); }
+  MK_HD int fCre(int k) const { return 64 * (4 + k); }
   // scalars: weight of y[j - 2L] in the output (real, imaginary component)
-  MK_HD int fYre() const { return 64 * (8 + 4 * NS()); }
+  MK_HD int fYre() const { return 64 * (4 + 2 * NS()); }
   MK_HD int fYim() const { return fYre() + 1; }
   MK_HD int nFloats() const { return (fYre() + 4 + 31) / 32 * 32; }
   // float64: run sums B / 2, B = sum_r a^{15 - r} dy[r] (states are held at half their size, the weights fC*,
   // bC and bCA are for such states), lane 16 q + m holding the weight of input 4 q + kb for
-  // row m of the product; a^{16 c} per lane (64); a^{16 2^d}, d < 6, one value per q; a^{256 k},
-  // k in [0, 16];
-  // e^{-2 alpha L}. Parts of slot s: 0 real, 1 imaginary
+  // row m of the product; a^{16 c} per lane (64); a^{16 2^d}, d < 5, one value per q; a^{256 k},
+  // k in [0, 8]; e^{-2 alpha L}. Parts of slot s: 0 real, 1 imaginary
   MK_HD int dP(int mb, int kb) const { return 64 * (4 * mb + kb); }
   MK_HD int dLANE(int s, int part) const { return 64 * (4 * MB() + 2 * s + part); }
   MK_HD int dSC(int d, int s, int part) const { return 64 * (4 * MB() + 2 * NS()) + 4 * ((d * NS() + s) * 2 + part); }
-  MK_HD int dG(int k, int s, int part) const { return dSC(6, 0, 0) + 4 * ((k * NS() + s) * 2 + part); }
-  MK_HD int dD() const { return dG(17, 0, 0); }
+  MK_HD int dG(int k, int s, int part) const { return dSC(5, 0, 0) + 4 * ((k * NS() + s) * 2 + part); }
+  MK_HD int dD() const { return dG(9, 0, 0); }
   // run sums of the complex adjoint, from stream c (real, imaginary part of the cotangent): dP times the
   // term's output weight of component c
   MK_HD int dPA(int c, int mb, int kb) const { return (dD() + 64) / 64 * 64 + 64 * (4 * (c * MB() + mb) + kb); }
@@ -92,8 +89,8 @@ struct GranLaunch {
 hipError_t launch_granules(const GranLaunch& a, hipStream_t s);
 
 // Carried scan (carry_scan.hip): rows of one length in `pieces` pieces of seg_n chunks, a block each; the
-// states pass from piece to piece through sums. A row's pieces start at or before position
-// jout0 - 31 - kChunk; together they reach its last output.
+// states pass from piece to piece through sums. A row's first piece starts at a position in (-kChunk, 0], its
+// outputs on 128-byte lines (within 31 of jout0 where that is negative); together they reach its last output.
 constexpr int kCarryWaves = 8;
 constexpr int64_t kChunk = kCarryWaves * kGran;
 inline int64_t chunks_for(int64_t N, int64_t jout0) {   // chunks of a row of N outputs at any alignment

@@ -59,7 +59,8 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
   using Sums = RunSums<NS, WIDE>;
   constexpr int G = kGran * NST;        // positions at a time
   constexpr int PS = NST == 1 ? kGran : kGran + 16;   // floats from one run of the columns to the next
-  constexpr int LV = NST == 1 ? 0 : NST == 2 ? 1 : 2;  // log2 NST
+  constexpr int LV = NST - 1;           // log2 NST
+  static_assert(NST == 1 || NST == 2);
   static_assert(!REV || CPLX == (IN == 3), "the adjoint's input is the cotangent of the transform's output");
   __shared__ __align__(16) float s_y[ST][NST * PS];   // y[j], by run of the columns, column and quad
   __shared__ __align__(16) float s_b[ST][NST * PS];   // y[j - 2L]

@@ -408,6 +408,7 @@ void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, dou
   // A = cx y + sum_t mw_t Re v_t, B = sum_t lw_t Im v_t; weights of Re v, Im v per component
   double T[2][kRun] = {}, cx = 0;
   float ca[8][64] = {};   // outputs of the complex adjoint from its state: component 2 slot + part
+  float tim[4][64] = {}, cim[8][64] = {};   // the imaginary component's fTre, fCre
   for (int i = 0; i < K; ++i) {
     const int64_t p = P_S + i;
     const int slot = i / 4, q = i % 4;
@@ -416,9 +417,11 @@ void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, dou
     const double wr[2] = {gre * mw, gim * mw};
     const double wi[2] = {okind == 0 ? gim * lw : -gre * lw, okind == 0 ? -gre * lw : 0.0};
     if (okind != 2) cx += sgn * cc[i] * dn;
-    double re, im;
+    double re, im, pr[kRun + 1], pi[kRun + 1];   // a^d
+    for (int d = 0; d <= kRun; ++d) apow(p, d, L, alpha, pr[d], pi[d]);
     for (int d = 0; d < kRun; ++d) {
-      apow(p, d, L, alpha, re, im);
+      re = pr[d];
+      im = pi[d];
       for (int c = 0; c < 2; ++c) T[c][d] += wr[c] * re + wi[c] * im;
       // run sums: input r = 15 - d; lane 16 (r / 4) + row, block kb = r % 4
       const int r = kRun - 1 - d, b = slot / 2, lq = 16 * (r / 4), kb = r % 4;
@@ -430,25 +433,24 @@ void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, dou
         td[lay.dPA(c, b, kb) + lq + q + 4 * (v + 1)] = kHeld * (wr[c] * im - wi[c] * re);
       }
       // outputs at position d from the state before the run
-      apow(p, d + 1, L, alpha, re, im);
-      re /= kHeld;
-      im /= kHeld;
+      re = pr[d + 1] / kHeld;
+      im = pi[d + 1] / kHeld;
       ca[2 * slot][16 * q + d] = (float)re;
       ca[2 * slot + 1][16 * q + d] = (float)-im;
       tf[lay.fCre(2 * slot) + 16 * q + d] = (float)(wr[0] * re + wi[0] * im);
       tf[lay.fCre(2 * slot + 1) + 16 * q + d] = (float)(-wr[0] * im + wi[0] * re);
-      tf[lay.fCim(2 * slot) + 16 * q + d] = (float)(wr[1] * re + wi[1] * im);
-      tf[lay.fCim(2 * slot + 1) + 16 * q + d] = (float)(-wr[1] * im + wi[1] * re);
+      cim[2 * slot][16 * q + d] = (float)(wr[1] * re + wi[1] * im);
+      cim[2 * slot + 1][16 * q + d] = (float)(-wr[1] * im + wi[1] * re);
       apow(p, (int64_t)kRun * d, L, alpha, re, im);
       td[lay.dLANE(slot, 0) + 16 * q + d] = re;
       td[lay.dLANE(slot, 1) + 16 * q + d] = im;
     }
-    for (int d = 0; d < 6; ++d) {
+    for (int d = 0; d < 5; ++d) {
       apow(p, (int64_t)kRun << d, L, alpha, re, im);
       td[lay.dSC(d, slot, 0) + q] = re;
       td[lay.dSC(d, slot, 1) + q] = im;
     }
-    for (int k = 0; k <= 16; ++k) {
+    for (int k = 0; k <= 8; ++k) {
       apow(p, (int64_t)kGran * k, L, alpha, re, im);
       td[lay.dG(k, slot, 0) + q] = re;
       td[lay.dG(k, slot, 1) + q] = im;
@@ -457,7 +459,7 @@ void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, dou
   for (int r = 0; r < kRun; ++r)
     for (int rp = 0; rp <= r; ++rp) {
       tf[lay.fTre(rp % 4) + 16 * (rp / 4) + r] = (float)T[0][r - rp];
-      tf[lay.fTim(rp % 4) + 16 * (rp / 4) + r] = (float)T[1][r - rp];
+      tim[rp % 4][16 * (rp / 4) + r] = (float)T[1][r - rp];
     }
   // thirds: the nearest bfloat16 of the value, of what is left, and the rest
   auto thirds = [](float v, uint16_t* h, uint16_t* m, uint16_t* l) {
@@ -496,11 +498,11 @@ void fill_granules(unsigned char* dst, int okind, int K, int64_t L, int P_S, dou
   for (int c = 0; c < 2; ++c)
     for (int lane = 0; lane < 64; ++lane)
       for (int e = 0; e < 4; ++e) {
-        thirds(tf[(c ? lay.fTim(e) : lay.fTre(e)) + lane], bq + 4 * (lay.bT(c, 0) + lane) + e,
+        thirds(c ? tim[e][lane] : tf[lay.fTre(e) + lane], bq + 4 * (lay.bT(c, 0) + lane) + e,
                bq + 4 * (lay.bT(c, 1) + lane) + e, bq + 4 * (lay.bT(c, 2) + lane) + e);
         for (int set = 0; set < lay.SETS(); ++set)
           if (4 * set + e < 2 * lay.NS())
-            thirds(tf[(c ? lay.fCim(4 * set + e) : lay.fCre(4 * set + e)) + lane], bq + 4 * (lay.bC(c, set, 0) + lane) + e,
+            thirds(c ? cim[4 * set + e][lane] : tf[lay.fCre(4 * set + e) + lane], bq + 4 * (lay.bC(c, set, 0) + lane) + e,
                    bq + 4 * (lay.bC(c, set, 1) + lane) + e, bq + 4 * (lay.bC(c, set, 2) + lane) + e);
       }
   tf[lay.fYre()] = (float)(gre * cx);

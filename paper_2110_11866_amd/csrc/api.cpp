@@ -457,15 +457,14 @@ bool gran_launch(morlet_plan_t plan, mk::ScanLaunch& a, int variant, bool least_
   // the row twice, in two launches, a block per CU (K = 5, us, granule | carried: N = 102400, 2L =
   // 2664: 7 | 10.5, 10650: 15 | 10.2, 42600: 47 | 10.6; N = 2^22, 2L = 10650: 32 | 35, 42600: 72 | 35; N =
   // 2^24, 2L = 10650: 66 | 96, 42600: 119 | 101; the tiles schedule, whose tiles wait for the states of the
-  // tiles before them, takes 17, 60 and 111 us there); it is taken where its estimate is a little below the
-  // granule scan's, the surer of the two. With so many rows that each is a piece, the tile scan wins
+  // tiles before them, takes 17, 60 and 111 us there). With so many rows that each is a piece, the tile scan wins
   // (200 rows of 50000, 2L = 48000, K = 9: 136 us, carried 266). The pieces' sums lie in the workspace after its
   // header, within what the tiles schedule needs.
   const int64_t all = mk::chunks_for(row.N, row.jout0), most = std::min<int64_t>(all, std::max<int64_t>(1, plan->num_cus / nrows));
   const int64_t len = (all + most - 1) / most, np = (all + len - 1) / len;
   const double granules = mk::granule_us(split, a.kind, adj, wide, plan->K, plan->num_cus);
-  const double carried =
-      1.05 * mk::carried_us((double)len * std::max(1.0, (double)(np * nrows) / plan->num_cus), a.kind, adj, wide, plan->K);
+  const double carried = (nrows > 1 ? 1.0 : a.kind == 0 ? 1.18 : 1.05) *   // one row: what the common fit leaves
+                         mk::carried_us((double)len * std::max(1.0, (double)(np * nrows) / plan->num_cus), a.kind, adj, wide, plan->K);
   if (least_us) *least_us = std::min(tiles, std::min(granules, carried));
   if (!least_scratch && tiles < granules && tiles < carried) return false;
   if (!least_scratch && carried < granules) {

@@ -151,3 +151,10 @@ def test_columns_in_pieces_and_non_finite():
         got = plan.forward(torch.from_numpy(bad).cuda()).cpu().numpy()
         assert np.array_equal(got[:at - L, :], clean[:at - L, :]) or _rel(got[:at - L], clean[:at - L]) <= TOL
         assert not np.isfinite(got[at - L:at + L + 1, 33]).any()
+
+
+@pytest.mark.parametrize("W", [31, 32, 33, 97])
+@pytest.mark.parametrize("K", [4, 9])
+def test_columns_around_a_waves_width(W, K):
+    # a wave of the column scan takes 32 columns, two a lane
+    test_columns(40, W, K)

@@ -386,7 +386,7 @@ def bench_image2d(args, torch, M):
                    "tile_R": args.tile, "schedule": args.schedule},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                     "scope": "whole path (two scans, two transposes) against 8 B per pixel"},
+                     "scope": "whole path (rows and columns) against 8 B per pixel"},
         "kernel_ms": kern_ms,
     }
 
@@ -420,7 +420,7 @@ def bench_gabor2d(args, torch, M):
                    "tile_R": args.tile, "schedule": args.schedule},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                     "scope": "whole path (two scans, two transposes) against 12 B per pixel"},
+                     "scope": "whole path (rows and columns) against 12 B per pixel"},
         "kernel_ms": kern_ms,
     }
 

@@ -177,9 +177,10 @@ morlet_status morlet_plan_multiply(morlet_plan_t* out, int64_t N, double sigma, 
  *   y = G_y *_columns (G_x *_rows img),
  * each axis by eq. aproGauss with orders 0..K-1 on its own window [-L_x, L_x], [-L_y, L_y]
  * (0: the error-optimal window of the fit), zero outside the image. Evaluated as one scan
- * launch over the H rows and one down the W columns (with accumulations, tile shapes or schedules
- * that the granule scan does not take: a transpose, one scan launch over the W rows of the
- * transposed image and a transpose back). morlet_plan_set (SFT/ASFT with one n0 for both axes, 0 = each
+ * launch over the H rows and one down the W columns, or, where that is estimated to take longer (windows
+ * long against the pieces of a column) and with accumulations, tile shapes or schedules that the granule
+ * scan does not take, a transpose, one scan launch over the W rows of the transposed image and a
+ * transpose back. morlet_plan_set (SFT/ASFT with one n0 for both axes, 0 = each
  * axis's default; accumulation), _set_tile and _set_schedule apply to both axes; autotune
  * and the 1-D backward calls return MORLET_ERR_UNSUPPORTED (gauss_smooth2d_backward is the
  * image's backward); morlet_plan_info returns
@@ -230,9 +231,9 @@ morlet_status morlet_plan_gabor2d(morlet_plan_t* out, int64_t H, int64_t W, doub
 
 /* 2-D Gabor filter: x (device, H x W elements of dtype, row-major) -> y (device complex64
  * [re, im] pairs, H x W, row-major). Two launches on the stream: the batched Morlet scan of
- * the H rows into the workspace and one Gaussian scan down its 2W real columns into y (where the
- * granule scan does not apply four: a transpose into the real and imaginary planes, the scan over
- * their 2W lines, a transpose back). Workspace: morlet_workspace_size
+ * the H rows into the workspace and one Gaussian scan down its 2W real columns into y; or four, where
+ * morlet_plan_gauss2d's would transpose: a transpose into the real and imaginary planes, the scan over
+ * their 2W lines, a transpose back. Workspace: morlet_workspace_size
  * (zero-filled once): the tile states and two H W complex64 buffers. Errors: a non-Gabor plan
  * is MORLET_ERR_INVALID_ARG; otherwise as gauss_smooth2d. */
 morlet_status gabor2d(morlet_plan_t plan, const void* x, morlet_dtype dtype, void* y, void* ws, size_t ws_bytes,
@@ -392,11 +393,11 @@ morlet_status morlet_plan_info(morlet_plan_t plan, int64_t* L, int32_t* P_S, int
  * (MORLET_ERR_INVALID_ARG for a plan that is not a Morlet plan, MORLET_ERR_UNSUPPORTED for edge
  * extension, multiplication-method and image plans); MORLET_ERR_WORKSPACE, with nothing
  * launched, when the launch needs more than the array (where the granule scan applies it is then taken, whatever
- * its time): the granule scan needs none, the carried
- * scan 64 bytes plus 16 K per piece (at most one per compute unit), the row-serial schedule of a scalogram 64 bytes, the tiles schedule 64 bytes plus one tile state per tile of 256 R positions
- * (256 bytes at K <= 5, 640 at K = 12), so a single signal of up to about 2^27 samples at K = 5,
- * R = 16; the segments schedule 64 bytes plus
- * 16 K bytes per segment (about two segments per resident block); MORLET_ERR_HIP if the
+ * its time): the granule scan needs none, the carried scan 64 bytes plus 16 K per piece (at most one per
+ * compute unit), the row-serial schedule of a scalogram 64 bytes, the tiles schedule 64 bytes plus one tile
+ * state per tile of 256 R positions (256 bytes at K <= 5, 640 at K = 12), so a single signal of up to about
+ * 2^27 samples at K = 5, R = 16; the segments schedule 64 bytes plus 16 K bytes per segment (about two
+ * segments per resident block); MORLET_ERR_HIP if the
  * array's address cannot be resolved or a launch fails. */
 #define MORLET_NOALLOC_SCRATCH_BYTES (8u << 20)
 morlet_status morlet_forward_noalloc(morlet_plan_t plan, const void* x, morlet_dtype dtype, void* W, void* stream);

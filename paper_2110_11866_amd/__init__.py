@@ -105,7 +105,8 @@ class _PlanBase:
     def autotune(self, x: torch.Tensor, reps: int = 5) -> dict:
         """Time the forward on x for each tile shape (and schedule, for scalograms) and keep
         the fastest; returns {"R": 4 | 8 | 16 | 32, "schedule": "tiles" | "rows" | "segments"}
-        ("tiles" also when the automatic schedule, which stays, won)."""
+        ("tiles" also when the automatic schedule won: the plan keeps that one, and
+        set_schedule("tiles") would take the granule scan from it)."""
         self._check_x(x)
         out = self._out_like(x)
         R, sched = _abi.morlet_plan_autotune(self.handle, x.data_ptr(), torch_dtype_code(x.dtype), out.data_ptr(),

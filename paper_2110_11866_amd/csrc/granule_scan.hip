@@ -24,13 +24,13 @@
 //
 // Bound: issue of vector and matrix instructions (about 680 cycles of a SIMD per 256 outputs at K = 5,
 // 683 us of a 488e6-output scalogram without its stores), then the stores (3.9 GB at 5.3-5.8 TB/s, 740 us
-// without the products); together 1000 us, the tile scan 1390.
+// without the products); together 910 us back to back (a launch timed alone 1030), the tile scan 1390.
 //
 // Zeros of T meet inputs of the same run at later positions: where a run has an infinite or NaN input,
 // the product takes zero for it and its outputs from that position on are set to NaN, so no output
 // depends on a later input. A wave with such inputs, with finite ones so large that their nearest bfloat16 is
-// infinite, or with nothing but values below 2^-106, repeats its products in float32. The states are held at half their size (the weights P at half, C
-// at twice theirs): one that is finite in float32 always has thirds.
+// infinite, or with nothing but values below 2^-106, repeats its products in float32. The states are held at
+// half their size (the weights P at half, C at twice theirs): one that is finite in float32 always has thirds.
 #include <hip/hip_runtime.h>
 
 #include "granule.h"
@@ -477,8 +477,8 @@ hipError_t launch_granules(const GranLaunch& a, hipStream_t s) {
   const bool cplx = a.kind == 0;
   const int ns = GranLayout{a.K}.NS();
   const int in = a.adjoint ? (cplx ? 3 : 4) : a.dtype;
-  // two runs per lane column halve the scans across lanes in long pieces (ragged scalogram 1000 us a
-  // launch against 1090); four leave two waves per SIMD (1005). In the complex adjoint two already do
+  // two runs per lane column halve the scans across lanes in long pieces (ragged scalogram, each launch
+  // timed alone: 1000 us against 1090); four leave two waves per SIMD (1005). In the complex adjoint two already do
   // (202 registers, 166 us at 64 x 32768 x 16 scales): one, three waves (142)
   const bool two = a.two != 0;
   const GranFn fn = ns == 1 ? pick<1>(cplx, in, two, a.acc == kAccMixed) : ns == 2 ? pick<2>(cplx, in, two, a.acc == kAccMixed) : pick<3>(cplx, in, two, a.acc == kAccMixed);

@@ -99,7 +99,7 @@ template <int VAR, int K, int R, int ACC, int KIND, bool MOM, int DT>
 // Occupancy: the float32-state forward scans fit four waves per SIMD (at most 128 VGPRs). The
 // gradient pass runs three up to K = 5: its LDS at R = 16 (41 KB per block) leaves no room for a
 // fourth, and at K = 5 the few float64 registers it spills cost less than the third wave gains
-// (about 40 us of a 450 us pass at 64 x 32768 x 16 scales); at K = 6 it would spill 65. The rest
+// (about 40 us of a pass that then took 450, at 64 x 32768 x 16 scales); at K = 6 it would spill 65. The rest
 // leave the register count to the compiler.
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
     (VAR == kFwd && (ACC == kAccF32 || (ACC == kAccMixed && R <= 16))) ? 4
@@ -824,7 +824,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
         // recurrence is then that of v with r dy + ddy as input, and r times what A and B hold is
         // taken off the weighted sums (float64 operations per position at K = 5: 125, with w itself and the
         // sums of each term apart 163; 442 us at 64 x 32768 x 16 scales,
-        // with the inputs loaded whole at any alignment and the cotangent a quad ahead 388; plain SFT 332 and 247).
+        // with the inputs loaded whole at any alignment and the cotangent a quad ahead 375; plain SFT 332 and 247).
         acc_t sv_re[K], sv_im[K], s_w = 0, s_xb = 0, q_im = 0;
 #pragma unroll
         for (int t = 0; t < K; ++t) { sv_re[t] = 0; sv_im[t] = 0; }

@@ -348,7 +348,7 @@ __global__ __launch_bounds__(64 * kCW) void carry_kernel(GranLaunch P) {
 #pragma unroll
       for (int s = 0; s < NS; ++s) { fr[t][s] = br[s]; fi[t][s] = bi[s]; }
     }
-    const bool slow = no_thirds(top);
+    bool slow = no_thirds(top);
     if (slow) {   // the run sums of the inputs as they are
 #pragma unroll
       for (int t = 0; t < ST; ++t) {
@@ -401,6 +401,10 @@ __global__ __launch_bounds__(64 * kCW) void carry_kernel(GranLaunch P) {
         const double2 l = s_lane[s][lane];
         mac(l.x, l.y, xr, xi, er[t][s], ei[t][s]);
       }
+    if (all_small(top) && !slow) {   // zeros: outputs of the entering states
+#pragma unroll
+      for (int t = 0; t < ST; ++t) slow = slow || no_thirds(er[t], ei[t]);
+    }
 
     auto components = [&](int e, int t, float (&x)[4]) {   // states 2 e, 2 e + 1 of stream t in float32
 #pragma unroll

@@ -110,9 +110,17 @@ __device__ __forceinline__ void keep_top(uint32_t& top, const float (&x)[4]) {
 // Whether some value of the wave's is infinite, NaN or so near the end of the range that its high third may be
 // infinite, or all are so small (not all zero) that their low thirds fall below bfloat16's smallest value, 2^-133:
 // from 2^-110 down thirds are not exact (signals of 1e-36 gave outputs off by 3e-5).
+__device__ __forceinline__ bool all_small(uint32_t top) { return __ballot(top >= __float_as_uint(0x1p-106f)) == 0; }
 __device__ __forceinline__ bool no_thirds(uint32_t top) {
-  return __ballot(top >= __float_as_uint(0x1p126f)) != 0 ||
-         (__ballot(top >= __float_as_uint(0x1p-106f)) == 0 && __ballot(top != 0) != 0);
+  return __ballot(top >= __float_as_uint(0x1p126f)) != 0 || (all_small(top) && __ballot(top != 0) != 0);
+}
+// The same of states, which make the outputs where the inputs are zeros (off by up to 7e-4 after a signal of 1e-36).
+template <int NS>
+__device__ __forceinline__ bool no_thirds(const double (&zr)[NS], const double (&zi)[NS]) {
+  float m = 0;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) m = fmaxf(m, fmaxf(fabsf((float)zr[s]), fabsf((float)zi[s])));
+  return no_thirds(__float_as_uint(m));
 }
 // Weights of four inputs per lane as thirds: middle, high, low.
 struct Weights {

@@ -29,7 +29,7 @@
 // Zeros of T meet inputs of the same run at later positions: where a run has an infinite or NaN input,
 // the product takes zero for it and its outputs from that position on are set to NaN, so no output
 // depends on a later input. A wave with such inputs, with finite ones so large that their nearest bfloat16 is
-// infinite, or with nothing but values below 2^-106, repeats its products in float32. The states are held at
+// infinite, or with nothing but values below 2^-106 (zeros after such values), repeats its products in float32. The states are held at
 // half their size (the weights P at half, C at twice theirs): one that is finite in float32 always has thirds.
 #include <hip/hip_runtime.h>
 
@@ -285,7 +285,8 @@ __global__ __launch_bounds__(64) void granule_kernel(GranLaunch P) {
       }
       Sums::states(acc, br[i], bi[i]);
     }
-    const bool slow = no_thirds(top);
+    bool slow = no_thirds(top);
+    if (all_small(top) && !slow) slow = no_thirds(zr, zi);   // zeros: outputs of the entering state
     if (!WIDE && slow) {   // the run sums of the inputs as they are
 #pragma unroll
       for (int i = 0; i < NST; ++i) {

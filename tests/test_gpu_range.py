@@ -102,3 +102,25 @@ def test_smallest_values(N, sigma, L, mode, scale):
         assert _rel(got / scale, O.forward(x.astype(np.float64), p) / scale) <= TOL[N]
         gx = plan.backward(None, torch.from_numpy(x.astype(got.dtype)).cuda(), want_params=False)[0].cpu().numpy()
         assert _rel(gx / scale, O.adjoint(x.astype(np.complex128), p) / scale) <= TOL[N]
+
+
+@pytest.mark.parametrize("scale", [1e-33, 1e-35, 1e-36])
+@pytest.mark.parametrize("mode", ["sft", "asft"])
+@pytest.mark.parametrize("N,sigma,L", [(8192, 200.0, 600), (60000, 6000.0, 20000)])
+def test_smallest_states(N, sigma, L, mode, scale):
+    # a short signal near the lower end, then zeros over more than a granule: those outputs come from the state alone
+    for kind in ("morlet", "gauss"):
+        _say("smallest states", kind, N, mode, scale)
+        plan, p = _plans(kind, N, sigma, L, mode)
+        n0 = plan.info()["n0"]
+        at = N // 2
+        x = np.zeros(N, np.float32)
+        x[at:at + 40] = np.random.default_rng(8).standard_normal(40) * scale
+        got = plan.forward(torch.from_numpy(x).cuda()).cpu().numpy()
+        ref = O.forward(x.astype(np.float64), p)
+        seen = slice(at + n0 - L // 2, at + n0 + L // 2)
+        assert _rel(got[seen] / scale, ref[seen] / scale) <= 1e-5
+        gx = plan.backward(None, torch.from_numpy(x.astype(got.dtype)).cuda(), want_params=False)[0].cpu().numpy()
+        ref = O.adjoint(x.astype(np.complex128), p)
+        seen = slice(at - n0 - L // 2, at - n0 + L // 2)
+        assert _rel(gx[seen] / scale, ref[seen] / scale) <= 1e-5
